@@ -209,13 +209,14 @@ int imloc_get_score_tuning(const imloc_ctx *ctx, int32_t *candidates_per_item, i
 int imloc_set_score_points(imloc_ctx *ctx, int32_t points_per_item);
 int imloc_get_score_points(const imloc_ctx *ctx, int32_t *points_per_item);
 
-/* Launch form of the Gauss-Newton runs (local optimisation and final
- * refinement): 0 (default) picks by size, 1 = one launch per iteration in
- * which every workgroup of a problem re-reduces the previous partial sums,
- * 2 = an evaluation launch and a one-workgroup-per-problem decision launch
- * per iteration.  Every form sums the same 512-point chunk partials in the
- * same order, so results are identical; only the speed differs.  Returns
- * IMLOC_EINVAL for another value. */
+/* Teams of the Gauss-Newton runs (local optimisation and final refinement):
+ * one launch runs every iteration of every problem, a problem's points shared
+ * by the workgroups of its team.  0 (default) picks the team's size by the
+ * size of the problem and the number of problems, 1 = the widest team (one
+ * workgroup per group of 1,024 points or more, at most 32), 2 = one workgroup
+ * per problem.  Every team sums the same groups of points in the same order,
+ * so results are identical; only the speed differs.  Returns IMLOC_EINVAL for
+ * another value. */
 int imloc_set_gn_mode(imloc_ctx *ctx, int32_t mode);
 
 /* ---- the hot path -------------------------------------------------------- */
@@ -461,8 +462,7 @@ typedef struct {
   int64_t candidate_pool;   /* candidate slots shared by the resident queries */
   int64_t byte_pool;        /* bytes shared by the resident queries: a query of n
                              * correspondences takes 1,024 ceil(n / 512) bytes
-                             * plus a 256-byte-aligned count table for its
-                             * refinement's in-set, and 24 m more for a
+                             * for its refinement's in-set, and 24 m more for a
                              * gathered scoring subset of m points */
 } imloc_server_config;
 

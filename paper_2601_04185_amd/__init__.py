@@ -244,7 +244,7 @@ class Context:
         self.check(lib().imloc_set_score_tuning(self.h, int(candidates_per_item), int(workgroups)))
 
     def set_gn_mode(self, mode: int):
-        """Gauss-Newton launch form: 0 by size, 1 fused, 2 split (identical results)."""
+        """Gauss-Newton teams: 0 by size, 1 the widest, 2 one workgroup per problem (identical results)."""
         self.check(lib().imloc_set_gn_mode(self.h, int(mode)))
 
     def score_tuning(self):

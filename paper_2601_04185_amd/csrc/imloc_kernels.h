@@ -61,11 +61,13 @@ struct QueryDesc {
   int64_t total;         // sample budget: fixed count, or the adaptive cap
   int64_t batch;         // samples per round
   int64_t min_iters;
-  int32_t fixed;         // 1: exactly `total` samples
-  int32_t exhaustive;
-  int32_t precision;     // 0: float32 scoring, 1: float64 scoring
-  int32_t k;             // local optimisations per round
-  int32_t lo_iters, final_iters;
+  uint8_t fixed;         // 1: exactly `total` samples
+  uint8_t exhaustive;
+  uint8_t precision;     // 0: float32 scoring, 1: float64 scoring
+  uint8_t k;             // local optimisations per round (0: an unused slot of a server)
+  int16_t lo_iters, final_iters;
+  int32_t lo_team, lo_team0;    // local optimisation: workgroups per problem, and the query's first ticket
+  int32_t fin_team, fin_team0;  // final refinement: the same
   int64_t cand_off;      // first candidate slot of this query
   int64_t cap;           // candidate slots (4 per sample of a round)
   int64_t in_set_off;    // offset of this query's bytes in the in-set array
@@ -158,7 +160,16 @@ hipError_t launch_gather_subsets(const QueryDesc* qd, int nq, int64_t max_m, hip
 // --- round bookkeeping ---------------------------------------------------------
 // init: state and the weight sum of the scoring set of every fresh query.
 // begin: also set up the first round (every query of the table is fresh)
-hipError_t launch_init_queries(QueryDesc* qd, BestState* st, int32_t* n_cand, int nq, bool begin, hipStream_t s);
+// clears: Gauss-Newton mailboxes of the fresh queries (their tags must not be
+// mistaken for an evaluation's) and the two launch tickets.
+struct GNClear {
+  uint64_t *lo, *fin;            // mailboxes (null: none)
+  int64_t lo_words, fin_words;   // per query
+  int32_t* tickets;              // [2]
+  bool all;                      // also of queries whose teams have one member now
+};
+hipError_t launch_init_queries(QueryDesc* qd, BestState* st, int32_t* n_cand, int nq, bool begin,
+                               const GNClear& clear, hipStream_t s);
 // finished queries (final refinement and mask done) leave the round loop
 hipError_t launch_retire(BestState* st, int nq, hipStream_t s);
 // begin: samples of this round per query, zero candidate counts.
@@ -187,8 +198,9 @@ struct ScoreTune {
   int blocks;   // workgroups of the launch (each strides over the work list)
   int pts;      // correspondences per float32 work item (512, 1024, 2048 or 4096)
 };
+// (also zeroes the Gauss-Newton tickets of the round)
 hipError_t launch_worklist(const QueryDesc* qd, CandBuf cb, int nq, ScoreTune tune, int64_t* item_off,
-                           hipStream_t s);
+                           int32_t* tickets, hipStream_t s);
 hipError_t launch_score(const QueryDesc* qd, CandBuf cb, BestState* st, int nq, const int64_t* item_off,
                         ScoreTune tune, int precision, hipStream_t s);
 // truncated cost of the candidates of query 0: count and msac outputs
@@ -205,25 +217,48 @@ hipError_t launch_select(const QueryDesc* qd, const BestState* st, CandBuf cb, i
 // candidate sel[q * kMaxTopK + slot] (or from start_direct[p] when given, all
 // on query 0) and runs on the scoring set of its query.  Refine: problem q
 // starts from the best pose of query q (or start_direct[q]) and runs on its
-// full set, if the query has just finished sampling.
-int gn_chunks(int64_t n);
+// full set, if the query has just finished sampling.  One launch runs every
+// iteration of every problem, a team of workgroups per problem; the team's
+// size changes no result.
+int gn_groups(int64_t n);
+int gn_most_groups(int64_t n);  // over problems of up to n points
+// members of a problem of `groups` groups in a launch of `total` groups over
+// `slots` workgroup slots (mode: imloc_set_gn_mode), each with at most `most`
+// groups.  Four for the local optimisation, one for the refinement: on a
+// batch of 256 queries of 5,000 to 80,000 points (2,048 and 256 problems) the
+// local optimisation took 2.73 ms with four, 2.83 with three, 3.74 with one (a
+// member that waits for its team holds a slot) and 2.75 with six; the
+// refinement 1.18 ms with one, whose points then stay in LDS, and 1.42 with
+// four.  On a burst of 192 queries at the server: 2.9 ms with four, 3.3 with
+// six; 2.1 with one, 3.0 with four.
+constexpr int kLoGroupsPerMember = 4;
+constexpr int kFinGroupsPerMember = 1;
+int gn_team(int groups, int64_t total, int slots, int most, int mode);
 // bytes of the final refinement's compacted in-set of a query of n points
 int64_t gn_inset_bytes(int64_t n);
-size_t gn_scratch_bytes(int nprob, int chunks_max);
+// mailbox words of a problem, and bytes of the mailboxes of nprob problems
+int64_t gn_box_words(int groups);
+size_t gn_scratch_bytes(int nprob, int groups);
+constexpr int kGNPolls = 1 << 14;  // about 10 ms: a wait within a team takes about 1 us
+struct GNLaunch {
+  uint64_t* box;      // mailboxes of the launch's problems
+  int box_groups;     // groups of the largest (the stride)
+  int32_t* ticket;    // zero at the launch
+  int members;        // workgroups over all problems
+  bool teams;         // some problem has more than one
+  int team_direct;    // members per problem when the starts are given
+  int polls;          // polls of a wait before a member works alone
+  bool resident;      // a member's only group stays in LDS
+};
 // any_rig: some problem belongs to a rig query (selects the kernel variant
-// that takes residuals through rig cameras).  gn_mode: 0 = pick the launch
-// form by size, 1 = fused (one launch per iteration), 2 = split (evaluation
-// and decision launches); every form gives identical results.
-hipError_t launch_lo(const QueryDesc* qd, CandBuf cb, const int32_t* sel, const int32_t* n_sel,
-                     const double* start_direct, int nprob, int kmax, int chunks_max, int iters_max, void* scratch,
-                     double* out_pose, double* out_cost, int64_t* out_count, bool any_rig, bool any_weighted,
-                     int gn_mode, hipStream_t s);
-hipError_t launch_refine(const QueryDesc* qd, BestState* st, const double* start_direct, int nq, int chunks_max,
-                         int iters_max, uint8_t* in_set, void* scratch, double* out_pose, double* out_cost,
-                         bool any_rig, int gn_mode, bool fuse_mask, bool* mask_done, hipStream_t s);
-// mask and inlier count of the final pose of every query that just finished
-// (all != 0: of every query, each with a pose)
-hipError_t launch_mask(const QueryDesc* qd, BestState* st, const double* fin_pose, int nq, int64_t max_n, int all,
-                       hipStream_t s);
+// that takes residuals through rig cameras)
+hipError_t launch_lo(const QueryDesc* qd, const BestState* st, CandBuf cb, const int32_t* sel, const int32_t* n_sel,
+                     const double* start_direct, int nq, int kmax, const GNLaunch& t, double* out_pose,
+                     double* out_cost, int64_t* out_count, bool any_rig, hipStream_t s);
+// write_mask: also the inlier mask of every refined query and its count (a
+// finished query without a pose gets a zero mask)
+hipError_t launch_refine(const QueryDesc* qd, BestState* bst, const double* start_direct, int nq, const GNLaunch& t,
+                         uint8_t* in_set, double* out_pose, double* out_cost, bool any_rig, bool write_mask,
+                         hipStream_t s);
 
 }  // namespace imloc

@@ -6,17 +6,44 @@
 //   final refinement: IRLS on the Cauchy loss, each point weighted by its
 //     confidence, over the inliers of the full set at the best pose (that set
 //     stays fixed).
-// Each Gauss-Newton iteration is one launch over (point chunk x problem)
-// workgroups for every problem of a batch of queries (or, for large batches,
-// an evaluation launch and a decision launch).  A workgroup accumulates the
-// 6x6 normal equations (upper triangle), the gradient, the cost and the
-// inlier count of a 512-point chunk in float64 with a fixed thread-to-point
-// map and reduction tree; partial sums are combined in chunk order, so the
-// result depends on the problem alone, not on the batch around it or the
-// launch form.  The final refinement's first evaluation also compacts each
-// chunk's in-set; its later evaluations take only those points (thread t:
-// the chunk's t-th and (t + 256)-th in-set points).  Residual
-// r = pi(R X + t) - x; left update on SO(3).
+//
+// One launch runs every iteration of every problem.  A problem is worked on
+// by a team of workgroups: its points are cut into groups (2,048 points each
+// up to 65,536 points, see gn_group_points), every member evaluates its
+// groups at the current pose -- the 6x6 normal equations (upper triangle), the
+// gradient, the cost and the inlier count of a group, in float64 -- and the
+// members exchange the groups' sums, add them in group order and take the
+// same decision.  The sums of a group and their order depend on the problem
+// alone, so a result does not depend on the team's size or on the batch
+// around it.  Residual r = pi(R X + t) - x; left update on SO(3).
+//
+// Why a team inside one launch: a run is a chain of short, dependent steps
+// (evaluate, sum, decide).  A launch per iteration cost 4.3 to 10 us each, and
+// twelve launches however early a run ended; the exchange below costs 0.9 us
+// between 2 members, 1.5 us among 10 or 16 and 1.8 us among 32 (29 sums each),
+// and a run that ends frees its workgroups at once.  Measured (MI355X, both
+// launches): a query of 2,000 points with one start 117 -> 77 us, of 50,000
+// points with eight starts 155 -> 109 us, a four-camera query of 20,000 points
+// 152 -> 120 us; 256 queries of 5,000 to 80,000 points 4.24 -> 3.91 ms, a burst
+// of 192 queries at the server 9.1 -> 5.0 ms.  What bounds it: for one query,
+// issue by a lone wave per SIMD (5.4 cycles per float64 instruction) and the
+// exchange, about half each; for a batch, float64 issue (4.3 cycles).
+//
+// The exchange: a group's 29 sums go to its mailbox as 58 words of 64 bits,
+// each half of a value with a tag that names the evaluation, written and read
+// by relaxed agent-scope atomics.  A word carries its own tag, so no fence
+// and no counter is needed: a reader polls the words themselves.  Mailboxes
+// alternate between two buffers: a member writes evaluation j + 2 only after
+// it has read everyone's j + 1, which a member writes after reading everyone's
+// j.  They are cleared before the first use (init_queries_kernel), and tags
+// count on from round to round.
+//
+// Every wait ends.  Workgroups take their role from a ticket drawn at their
+// start, so the members of every team but the last one started are running,
+// and only that one can be short of members while workgroup slots are taken.
+// A wait is also bounded: a member that has polled GNLaunch::polls times evaluates
+// the missing groups itself (the same sums, bit for bit) and does not wait
+// again in this launch.
 #include "imloc_device.h"
 #include "imloc_kernels.h"
 
@@ -26,123 +53,120 @@ constexpr int kAcc = 29;  // 21 (H upper) + 6 (g) + cost + count
 constexpr double kStepTol2 = 1e-20;  // squared length of a step that ends a run
 constexpr int kGNThreads = 256;
 constexpr int kGNWaves = kGNThreads / kWave;
-constexpr int kGNPPT = 2;                       // points per thread per chunk
-constexpr int kGNChunk = kGNThreads * kGNPPT;   // points per chunk (fixed: the summation order depends on n only)
+constexpr int kGNGroup = 2048;          // points of a group that stays in LDS, at most: eight per thread
+constexpr int kGNGroupMost = 32768;     // of the largest (offsets in a group are 16 bits, 0xffff is none)
+constexpr int kGNGroupsWanted = 32;
+constexpr int kGNBox = 64;              // mailbox words of a group (58 used)
+constexpr int kGNInBlock = 32;          // groups read together
+constexpr uint16_t kGNNone = 0xffff;
+// waves per SIMD where the points are read from memory (the local optimisation
+// of 256 queries took 3.3 ms with two, 2.73 with three, 3.96 with four, which
+// spill); with the points in LDS two workgroups fit a compute unit
+constexpr int kGNWavesMany = 3;
+constexpr int kGNRig = 18;              // LDS doubles of a rig camera: R, t, 1/fx, 1/fy, -cx/fx, -cy/fy, fx^2, fy^2
 
 // 1 / z for the per-point work of an evaluation (z > 0 and finite): the
 // hardware reciprocal and two Newton steps, within about an ulp of the
 // rounded quotient, in 5 instructions where a rounded division takes about
-// 10.  Every launch form uses it, so they still agree bit for bit.
+// 10.
 __device__ __forceinline__ double recip_pos(double z) {
   double r = __builtin_amdgcn_rcp(z);
   r = fma(r, fma(-z, r, 1.0), r);
   return fma(r, fma(-z, r, 1.0), r);
 }
 
-// Normal equations of one point, given iz = 1 / z of its camera coordinates.
-// The rows of d(pixel)/d(dw, dt) are J0 = (a02 y, a00 z - a02 x, -a00 y, a00,
-// 0, a02) and J1 = (a12 y - a11 z, -a12 x, a11 x, 0, a11, a12); the products
-// with their structural zeros are left out (H[3][4] gets nothing).  W false:
-// every weight is 1 (the local optimisation of queries without confidences),
-// whose weighted rows are the rows themselves -- the same bits without the
-// ten multiplications.
-template <bool W>
-__device__ inline void acc_point(double* a, const Cam& K, double x, double y, double z, double iz, double du,
-                                 double dv, double wt) {
-  const double a00 = K.fx * iz, a02 = -K.fx * x * iz * iz;
-  const double a11 = K.fy * iz, a12 = -K.fy * y * iz * iz;
-  const double J0[6] = {a02 * y, a00 * z - a02 * x, -a00 * y, a00, 0.0, a02};
-  const double J1[6] = {-a11 * z + a12 * y, -a12 * x, a11 * x, 0.0, a11, a12};
-  double W0[6], W1[6];
-#pragma unroll
-  for (int r = 0; r < 6; ++r) {
-    W0[r] = W ? wt * J0[r] : J0[r];
-    W1[r] = W ? wt * J1[r] : J1[r];
-  }
-  int k = 0;
-#pragma unroll
-  for (int r = 0; r < 6; ++r) {
-#pragma unroll
-    for (int c = r; c < 6; ++c) {
-      const bool z0 = r == 4 || c == 4, z1 = r == 3 || c == 3;
-      if (!z0 && !z1) a[k] = fma(W0[r], J0[c], fma(W1[r], J1[c], a[k]));
-      else if (!z0) a[k] = fma(W0[r], J0[c], a[k]);
-      else if (!z1) a[k] = fma(W1[r], J1[c], a[k]);
-      ++k;
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < 6; ++r) {
-    if (r == 4) a[21 + r] = fma(W1[r], dv, a[21 + r]);
-    else if (r == 3) a[21 + r] = fma(W0[r], du, a[21 + r]);
-    else a[21 + r] = fma(W0[r], du, fma(W1[r], dv, a[21 + r]));
-  }
+// ln(1 + t) for t >= 0: 1 + t = 2^e m with m in [1/sqrt 2, sqrt 2), and ln m =
+// 2 atanh(f / (2 + f)), f = m - 1, by the series of atanh (|s| < 0.172, so its
+// terms are below 3e-17 from s^21 on; for e = 0, f is t itself).  Within 5e-16
+// relative of ln(1 + t); about 35 instructions where the library's log1p took
+// most of an evaluation step of the refinement (1,820 cycles a step with it,
+// see the kernel).
+__device__ __forceinline__ double log1p_pos(double t) {
+#pragma clang fp contract(off)
+  const double y = 1.0 + t;
+  int e = __builtin_amdgcn_frexp_exp(y);      // y = 2^e * mant, mant in [0.5, 1)
+  double m = __builtin_amdgcn_frexp_mant(y);
+  const bool low = m < 0.70710678118654757;
+  e = low ? e - 1 : e;
+  m = low ? m + m : m;
+  const double f = e == 0 ? t : m - 1.0;
+  const double s = f * recip_pos(2.0 + f);
+  const double z = s * s;
+  double p = 1.0 / 19.0;
+  p = fma(p, z, 1.0 / 17.0);
+  p = fma(p, z, 1.0 / 15.0);
+  p = fma(p, z, 1.0 / 13.0);
+  p = fma(p, z, 1.0 / 11.0);
+  p = fma(p, z, 1.0 / 9.0);
+  p = fma(p, z, 1.0 / 7.0);
+  p = fma(p, z, 1.0 / 5.0);
+  p = fma(p, z, 1.0 / 3.0);
+  const double s2 = s + s;
+  return fma((double)e, 0.69314718055994531, fma(s2 * z, p, s2));
 }
 
-// The same for a rig camera: x_c = R_c x_r + t_c with the rig-frame point x_r
-// moving under the left update of the rig pose, so the rows of d(pixel)/dx_c
-// are carried through R_c: J = [x_r x r, r] for each row r of d(pixel)/dx_c R_c.
-__device__ inline void acc_point_rig(double* a, const Cam& K, const double xr[3], double x, double y, double iz,
-                                     const double* Rc, double du, double dv, double wt) {
-  const double p0[3] = {K.fx * iz, 0.0, -K.fx * x * iz * iz};
-  const double p1[3] = {0.0, K.fy * iz, -K.fy * y * iz * iz};
-  double r0[3], r1[3];
-  for (int c = 0; c < 3; ++c) {
-    r0[c] = p0[0] * Rc[c] + p0[1] * Rc[3 + c] + p0[2] * Rc[6 + c];
-    r1[c] = p1[0] * Rc[c] + p1[1] * Rc[3 + c] + p1[2] * Rc[6 + c];
-  }
-  double w0[3], w1[3];
-  cross3(xr, r0, w0);
-  cross3(xr, r1, w1);
-  const double J0[6] = {w0[0], w0[1], w0[2], r0[0], r0[1], r0[2]};
-  const double J1[6] = {w1[0], w1[1], w1[2], r1[0], r1[1], r1[2]};
-  int k = 0;
-#pragma unroll
-  for (int r = 0; r < 6; ++r) {
-#pragma unroll
-    for (int c = r; c < 6; ++c) { a[k] = fma(wt, J0[r] * J0[c] + J1[r] * J1[c], a[k]); ++k; }
-  }
-#pragma unroll
-  for (int r = 0; r < 6; ++r) a[21 + r] = fma(wt, J0[r] * du + J1[r] * dv, a[21 + r]);
+// A value that every lane holds alike, in scalar registers.
+__device__ __forceinline__ double uniform(double x) {
+  const long long b = __double_as_longlong(x);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// Per-problem Gauss-Newton state after a decision, double-buffered.
-struct GNState {
-  double cur[12];      // accepted pose
-  double eval[12];     // pose the next evaluation runs at
-  double cur_cost;
-  double cur_count;
-  int32_t done;
-  int32_t accepted;
-};
-
-__host__ __device__ inline int chunks_for(int64_t n) {
-  const int64_t c = (n + kGNChunk - 1) / kGNChunk;
-  return c > 0 ? (int)c : 1;
+// Points of a group of a problem of n points: one group up to 2,048 points,
+// then 1,024 points each while that makes at most 32 groups, then a 32nd of
+// the points (in steps of 2,048) up to 32,768.  More groups are more compute
+// units for one problem (a lone wave per SIMD issues a float64 instruction
+// every 5.4 cycles, so four points per thread take 2,600 cycles of an
+// evaluation), but each evaluation ends with an exchange of about 3,500
+// cycles once there are two, and 32 mailboxes take 5,000.
+__host__ __device__ inline int gn_group_points(int64_t n) {
+  if (n <= kGNGroup) return kGNGroup;
+  if (n <= (int64_t)kGNGroupsWanted * kGNGroup / 2) return kGNGroup / 2;
+  int64_t s = (n + kGNGroupsWanted - 1) / kGNGroupsWanted;
+  s = (s + kGNGroup - 1) / kGNGroup * kGNGroup;
+  return (int)(s > kGNGroupMost ? kGNGroupMost : s);
 }
 
-int gn_chunks(int64_t n) { return chunks_for(n); }
-
-// The final refinement's in-set, compacted per chunk by its first evaluation
-// (the set stays fixed): a count per chunk (uint16, padded to 256 bytes), then
-// per chunk the offsets in the chunk of its in-set points, in point order
-// (uint16 x kGNChunk).  Later evaluations read only those points.
-__host__ __device__ inline int64_t inset_head_bytes(int64_t C) { return (2 * C + 255) & ~int64_t(255); }
-__host__ __device__ inline int64_t inset_bytes_for(int64_t n) {
-  const int64_t C = chunks_for(n);
-  return inset_head_bytes(C) + (int64_t)2 * kGNChunk * C;
-}
-int64_t gn_inset_bytes(int64_t n) { return inset_bytes_for(n); }
-
-size_t gn_scratch_bytes(int nprob, int chunks_max) {
-  if (nprob < 1) nprob = 1;
-  if (chunks_max < 1) chunks_max = 1;
-  return (((size_t)2 * nprob * sizeof(GNState) + 255) & ~size_t(255)) +
-         (size_t)2 * nprob * chunks_max * kAcc * sizeof(double) + 256;
+__host__ __device__ inline int groups_for(int64_t n) {
+  const int s = gn_group_points(n);
+  const int64_t g = (n + s - 1) / s;
+  return g > 0 ? (int)g : 1;
 }
 
-// Packed row-wise index of (r, c), r <= c, in the 21-entry upper triangle.
-__host__ __device__ constexpr int upk(int r, int c) { return r * 6 - (r * (r - 1)) / 2 + (c - r); }
+int gn_groups(int64_t n) { return groups_for(n); }
+
+// the most groups that a problem of up to n points has (more points can make
+// fewer groups: 32,768 make 32, 32,769 make 17)
+int gn_most_groups(int64_t n) {
+  const int g = groups_for(n);
+  return n > (int64_t)kGNGroupsWanted * kGNGroup / 2 && g < kGNGroupsWanted ? kGNGroupsWanted : g;
+}
+
+// The final refinement's in-set where its points do not stay in LDS: 16-bit
+// offsets in the group, in point order, up to a kGNNone (512 entries per 512
+// points).
+int64_t gn_inset_bytes(int64_t n) {
+  const int64_t c = (n + 511) / 512;
+  return 1024 * (c > 0 ? c : 1);
+}
+
+// Mailboxes of nprob problems of at most `groups` groups (two buffers each).
+int64_t gn_box_words(int groups) { return groups > 1 ? (int64_t)2 * kGNBox * groups : 0; }
+size_t gn_scratch_bytes(int nprob, int groups) {
+  return (size_t)(nprob > 0 ? nprob : 1) * (size_t)gn_box_words(groups) * sizeof(uint64_t) + 256;
+}
+
+// Team size of a problem of `groups` groups when a launch holds `total`
+// groups and the chip `slots` workgroups: a member per group while all fit;
+// else each member takes several groups, at most `most`.
+int gn_team(int groups, int64_t total, int slots, int most, int mode) {
+  if (mode == 2 || groups <= 1) return 1;
+  int64_t r = 1;
+  if (mode == 0 && total > slots) r = (total + slots - 1) / slots;
+  if (r > most) r = most;
+  const int t = (int)((groups + r - 1) / r);
+  return t < kGNGroupsWanted ? t : kGNGroupsWanted;
+}
 
 // A double moved across lanes by a DPP control (both 32-bit halves).
 template <int CTRL>
@@ -240,6 +264,145 @@ __device__ __forceinline__ bool mask_test(const QueryDesc& d, const double* pose
   return du * du + dv * dv < d.tau * d.tau;
 }
 
+// Uniform values of one problem.
+struct GNView {
+  CorrF32 c;
+  int64_t n;
+  double ifx, ify, ucx, vcy;   // normalised observation: u ifx + ucx
+  double fx2, fy2;
+  double tau2, inv_s2;
+  int ncam;
+  const int64_t* seg;
+};
+
+// A point in registers (past the end of a group: u is NaN, w is 0).
+struct GNPt {
+  float X, Y, Z, u, v, w;
+  int cam;
+  bool use;
+};
+
+// Normal equations of one point of a single camera, in normalised image
+// coordinates p = x / z, q = y / z, iz = 1 / z: the rows of d(p, q)/d(dw, dt)
+// are J0 = (-p q, 1 + p^2, -q, iz, 0, -p iz) and J1 = (-(1 + q^2), p q, p, 0,
+// iz, -q iz); the pixel scales and the weight are in w0 = w fx^2 and w1 = w
+// fy^2.  The products with the structural zeros are left out (H[3][4] gets
+// nothing).
+__device__ __forceinline__ void acc_point(double* a, double p, double q, double iz, double du, double dv, double w0,
+                                          double w1) {
+  const double pq = p * q;
+  const double J0[6] = {-pq, fma(p, p, 1.0), -q, iz, 0.0, -(p * iz)};
+  const double J1[6] = {-fma(q, q, 1.0), pq, p, 0.0, iz, -(q * iz)};
+  double W0[6], W1[6];
+#pragma unroll
+  for (int r = 0; r < 6; ++r) {
+    W0[r] = w0 * J0[r];
+    W1[r] = w1 * J1[r];
+  }
+  int k = 0;
+#pragma unroll
+  for (int r = 0; r < 6; ++r) {
+#pragma unroll
+    for (int c = r; c < 6; ++c) {
+      const bool z0 = r == 4 || c == 4, z1 = r == 3 || c == 3;
+      if (!z0 && !z1) a[k] = fma(W0[r], J0[c], fma(W1[r], J1[c], a[k]));
+      else if (!z0) a[k] = fma(W0[r], J0[c], a[k]);
+      else if (!z1) a[k] = fma(W1[r], J1[c], a[k]);
+      ++k;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 6; ++r) {
+    if (r == 4) a[21 + r] = fma(W1[r], dv, a[21 + r]);
+    else if (r == 3) a[21 + r] = fma(W0[r], du, a[21 + r]);
+    else a[21 + r] = fma(W0[r], du, fma(W1[r], dv, a[21 + r]));
+  }
+}
+
+// The same for a rig camera: x_c = R_c x_r + t_c with the rig-frame point x_r
+// moving under the left update of the rig pose, so the rows of d(p, q)/dx_c
+// are carried through R_c: J = [x_r x r, r] with r0 = (R_c row 0 - p R_c row
+// 2) iz, r1 = (R_c row 1 - q R_c row 2) iz.
+__device__ __forceinline__ void acc_point_rig(double* a, const double xr[3], double p, double q, double iz,
+                                              const double* Rc, double du, double dv, double w0, double w1) {
+  double J0[6], J1[6];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    J0[3 + c] = fma(-p, Rc[6 + c], Rc[c]) * iz;
+    J1[3 + c] = fma(-q, Rc[6 + c], Rc[3 + c]) * iz;
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const int c1 = (c + 1) % 3, c2 = (c + 2) % 3;
+    J0[c] = fma(xr[c1], J0[3 + c2], -(xr[c2] * J0[3 + c1]));
+    J1[c] = fma(xr[c1], J1[3 + c2], -(xr[c2] * J1[3 + c1]));
+  }
+  int k = 0;
+#pragma unroll
+  for (int r = 0; r < 6; ++r) {
+    const double W0 = w0 * J0[r], W1 = w1 * J1[r];
+#pragma unroll
+    for (int c = r; c < 6; ++c) {
+      a[k] = fma(W0, J0[c], fma(W1, J1[c], a[k]));
+      ++k;
+    }
+    a[21 + r] = fma(W0, du, fma(W1, dv, a[21 + r]));
+  }
+}
+
+// One point at pose P into the sums; `take` is left true if it counts (local
+// optimisation: an inlier; first evaluation of the refinement: an inlier,
+// which puts it in the set; later ones: in the set).  Every product and sum
+// is written as it is rounded (no contraction is left to the compiler), so
+// the point gives the same bits wherever this is inlined.
+template <int MODE, bool RIG>
+__device__ __forceinline__ bool gn_point(const GNView& g, const double* s_rig, const double* P, bool first,
+                                         const GNPt& pt, double* a) {
+#pragma clang fp contract(off)
+  const double X = pt.X, Y = pt.Y, Z = pt.Z, w = pt.w;
+  double x = fma(P[0], X, fma(P[1], Y, fma(P[2], Z, P[9])));
+  double y = fma(P[3], X, fma(P[4], Y, fma(P[5], Z, P[10])));
+  double z = fma(P[6], X, fma(P[7], Y, fma(P[8], Z, P[11])));
+  double ifx = g.ifx, ify = g.ify, ucx = g.ucx, vcy = g.vcy, fx2 = g.fx2, fy2 = g.fy2;
+  const double xr[3] = {x, y, z};
+  const double* rc = nullptr;
+  if (RIG && g.ncam > 0) {  // through the point's camera: x_c = R_c x_r + t_c
+    rc = s_rig + kGNRig * pt.cam;
+    ifx = rc[12]; ify = rc[13]; ucx = rc[14]; vcy = rc[15]; fx2 = rc[16]; fy2 = rc[17];
+    x = fma(rc[0], xr[0], fma(rc[1], xr[1], fma(rc[2], xr[2], rc[9])));
+    y = fma(rc[3], xr[0], fma(rc[4], xr[1], fma(rc[5], xr[2], rc[10])));
+    z = fma(rc[6], xr[0], fma(rc[7], xr[1], fma(rc[8], xr[2], rc[11])));
+  }
+  const bool front = z > 0.0;
+  const double iz = recip_pos(z);
+  const double p = x * iz, q = y * iz;
+  const double du = p - fma((double)pt.u, ifx, ucx), dv = q - fma((double)pt.v, ify, vcy);
+  const double r2 = fma(fx2, du * du, fy2 * (dv * dv));
+  const bool in = front && r2 < g.tau2;  // never of an unused point
+  if (MODE == 0) {
+    a[27] = fma(w, in ? r2 : g.tau2, a[27]);
+    if (in) {
+      const double w0 = w * fx2, w1 = w * fy2;
+      if (RIG && g.ncam > 0) acc_point_rig(a, xr, p, q, iz, rc, du, dv, w0, w1);
+      else acc_point(a, p, q, iz, du, dv, w0, w1);
+    }
+    return in;
+  }
+  const bool take = first ? in : pt.use;  // (an unused point may hold anything)
+  if (take) {
+    // a point of the set that has gone behind the camera costs as much as one at the threshold
+    const double t = (front ? r2 : g.tau2) * g.inv_s2;
+    a[27] = fma(w, log1p_pos(t), a[27]);  // times s^2 after the last sum
+    if (front) {
+      const double wc = w * recip_pos(1.0 + t);  // the Cauchy weight
+      const double w0 = wc * fx2, w1 = wc * fy2;
+      if (RIG && g.ncam > 0) acc_point_rig(a, xr, p, q, iz, rc, du, dv, w0, w1);
+      else acc_point(a, p, q, iz, du, dv, w0, w1);
+    }
+  }
+  return take;
+}
+
 struct GNArgs {
   const QueryDesc* qd;
   CandBuf cb;
@@ -247,107 +410,21 @@ struct GNArgs {
   const int32_t* n_sel;
   const double* start_direct;
   BestState* bst;
-  GNState* gst;
-  double* part;
+  uint64_t* box;       // mailboxes [problem][2][box_groups][kGNBox]
   uint8_t* in_set_all;
   double* out_pose;
   double* out_cost;
   int64_t* out_count;
-  int kmax, cmax, nprob;
-  int fuse_mask;  // final refinement: the launch that ends a run writes the mask of its chunk
+  int32_t* ticket;     // null: no team has more than one member
+  int nq, kmax, box_groups;
+  int team_direct;     // start_direct: members of every problem
+  int polls;           // polls of a wait before a member works alone
+  int write_mask;      // final refinement: the inlier mask and its count at the final pose
 };
 
-// Problem p's query.  LO (MODE 0): problem p = q * kmax + slot starts from
-// the slot-th selected candidate of query q; refinement (MODE 1): problem q
-// starts from the query's best pose once it has finished sampling.
-template <int MODE>
-__device__ __forceinline__ int gn_query(const GNArgs& g, int p) {
-  return MODE == 0 ? (g.start_direct ? 0 : p / g.kmax) : p;
-}
-
-// Whether problem p has work this round.
-template <int MODE>
-__device__ __forceinline__ bool gn_live(const GNArgs& g, int p, int q) {
-  if (g.start_direct) return true;
-  if (MODE == 0) return p - q * g.kmax < g.n_sel[q];
-  return (g.bst[q].finished == 1) & (g.bst[q].have != 0);
-}
-
-// Start pose of a live problem.
-template <int MODE>
-__device__ __forceinline__ const double* gn_start(const GNArgs& g, int p, int q) {
-  if (MODE == 0)
-    return g.start_direct ? g.start_direct + 12 * (int64_t)p
-                          : g.cb.pose + 12 * (g.qd[q].cand_off + g.sel[q * kMaxTopK + (p - q * g.kmax)]);
-  return g.start_direct ? g.start_direct + 12 * (int64_t)q : g.bst[q].pose;
-}
-
-__device__ __forceinline__ const double* gn_part(const GNArgs& g, int buf, int p) {
-  return g.part + ((int64_t)buf * g.nprob + p) * g.cmax * kAcc;
-}
-
-// The C chunk partial sums of one problem in a fixed order: thread (v, grp)
-// adds chunks grp, grp + 8, ... of entry v in chunk order, then the eight
-// group sums are added in group order.  The first 16 chunks of every thread
-// (128 of the problem) are loaded at kernel entry by gn_part_issue, whose
-// addresses need only the problem index, so their latency overlaps the
-// descriptor loads; gn_part_sum adds them and loads any further ones.
-struct GNPart {
-  double x[16];
-};
-
-__device__ __forceinline__ void gn_part_issue(const double* part, int cmax, GNPart& r) {
-  const int v = threadIdx.x % kAcc, grp = threadIdx.x / kAcc;
-#pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const int c = grp + 8 * u;
-    r.x[u] = (grp < 8 && c < cmax) ? part[(int64_t)c * kAcc + v] : 0.0;
-  }
-}
-
-// Every thread calls it.
-__device__ void gn_part_sum(const double* part, int C, const GNPart& r, double (*s_grp)[kAcc], double* s_tot) {
-  const int v = threadIdx.x % kAcc, grp = threadIdx.x / kAcc;
-  if (grp < 8) {
-    double sum = 0.0;
-#pragma unroll
-    for (int u = 0; u < 16; ++u)
-      if (grp + 8 * u < C) sum += r.x[u];
-    for (int c0 = grp + 128; c0 < C; c0 += 128) {
-      double x[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int c = c0 + 8 * u;
-        x[u] = c < C ? part[(int64_t)c * kAcc + v] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < 16; ++u)
-        if (c0 + 8 * u < C) sum += x[u];
-    }
-    s_grp[grp][v] = sum;
-  }
-  __syncthreads();
-  if ((int)threadIdx.x < kAcc) {
-    double t = 0.0;
-#pragma unroll
-    for (int gg = 0; gg < 8; ++gg) t += s_grp[gg][threadIdx.x];
-    s_tot[threadIdx.x] = t;
-  }
-  __syncthreads();
-}
-
-// Decision j of a run, on the sums of evaluation j at s.eval: the evaluated
-// pose becomes the accepted one if its cost did not rise (at j = 0 it is the
-// start); unless the iteration budget is spent, the normal equations at the
-// accepted pose give the pose of evaluation j + 1.  A cost-raising step, or a
-// system that is not positive definite, ends the run with the accepted pose.
-// Run by the 64 lanes of wave 0 (every lane takes the same branches): every
-// lane solves the 6 x 6 system itself (solve6_schur), and lane e < 12 forms
-// element e of the next pose.  Returns true when this decision ends the run.
 struct GNShared {
-  double cur[12], eval[12];
-  double cost, count;
-  int done, accepted;
+  double cur[12], eval[12], start[12];
+  int done;
 };
 
 // H d = -g for the 6x6 normal equations given by tot (upper triangle of H,
@@ -368,7 +445,7 @@ __device__ __forceinline__ bool solve6_schur(const double* t, double x[6]) {
   const double c11 = fma(h00, h22, -h02 * h02), c12 = fma(h01, h02, -h00 * h12), c22 = fma(h00, h11, -h01 * h01);
   const double detA = fma(h00, c00, fma(h01, c01, h02 * c02));
   const bool okA = h00 > 0.0 && c22 > 0.0 && detA > 0.0;
-  const double ia = 1.0 / detA;
+  const double ia = recip_pos(detA);
   const double I[3][3] = {{c00 * ia, c01 * ia, c02 * ia}, {c01 * ia, c11 * ia, c12 * ia}, {c02 * ia, c12 * ia, c22 * ia}};
   const double B[3][3] = {{h03, h04, h05}, {h13, h14, h15}, {h23, h24, h25}};
   const double C[3][3] = {{h33, h34, h35}, {h34, h44, h45}, {h35, h45, h55}};
@@ -393,7 +470,7 @@ __device__ __forceinline__ bool solve6_schur(const double* t, double x[6]) {
   const double d12 = fma(S[0][1], S[0][2], -S[0][0] * S[1][2]), d22 = fma(S[0][0], S[1][1], -S[0][1] * S[0][1]);
   const double detS = fma(S[0][0], d00, fma(S[0][1], d01, S[0][2] * d02));
   const bool okS = S[0][0] > 0.0 && d22 > 0.0 && detS > 0.0;
-  const double is = 1.0 / detS;
+  const double is = recip_pos(detS);
   const double J[3][3] = {{d00 * is, d01 * is, d02 * is}, {d01 * is, d11 * is, d12 * is}, {d02 * is, d12 * is, d22 * is}};
 #pragma unroll
   for (int r = 0; r < 3; ++r) x[3 + r] = fma(J[r][0], rt[0], fma(J[r][1], rt[1], J[r][2] * rt[2]));
@@ -402,676 +479,567 @@ __device__ __forceinline__ bool solve6_schur(const double* t, double x[6]) {
   return okA && okS;
 }
 
-__device__ __forceinline__ bool gn_decide_wave(int j, int iters, const double* tot, GNShared& s) {
+// Decision j of a run, on the sums of evaluation j at s.eval: the evaluated
+// pose becomes the accepted one if its cost did not rise (at j = 0 it is the
+// start); unless the iteration budget is spent, the normal equations at the
+// accepted pose give the pose of evaluation j + 1.  A cost-raising step, or a
+// system that is not positive definite, ends the run with the accepted pose.
+// Run by the 64 lanes of wave 0 (every lane takes the same branches): every
+// lane solves the 6 x 6 system itself (solve6_schur), and lane e < 12 forms
+// element e of the next pose.  The accepted cost and count stay in the wave's
+// registers; s.done says whether this decision ends the run.
+__device__ __forceinline__ void gn_decide_wave(int j, int iters, const double* tot, GNShared& s, double& best_cost,
+                                               double& best_count) {
   const int lane = threadIdx.x;
-  if (s.done) return false;
-  const double cost = tot[27];
-  if (!(j == 0 || cost <= s.cost)) {
-    if (lane == 0) s.done = 1;
-    return true;
-  }
-  // accept the evaluated pose
-  const double acc_e = lane < 12 ? s.eval[lane] : 0.0;
-  if (lane < 12) s.cur[lane] = acc_e;
-  if (lane == 0) {
-    s.cost = cost;
-    s.count = tot[28];
-    if (j > 0) s.accepted += 1;
-  }
-  if (j >= iters) {
-    if (lane == 0) s.done = 1;
-    return true;
-  }
+  const double cur_l = s.eval[lane < 12 ? lane : 0];
+  const int rr = lane < 9 ? lane / 3 : lane - 9, cc = lane < 9 ? lane % 3 : 3;
+  // column cc of the evaluated pose (its translation for cc = 3)
+  const int at = cc < 3 ? cc : 9, by = cc < 3 ? 3 : 1;
+  const double p0 = s.eval[at], p1 = s.eval[at + by], p2 = s.eval[at + 2 * by];
+  const double cost = tot[27], count = tot[28];
   double d[6];
-  if (!solve6_schur(tot, d)) {
-    if (lane == 0) s.done = 1;
-    return true;
-  }
-  // converged: a step shorter than 1e-10 (norm of (dw, dt)) is not taken and
-  // ends the run (every lane holds d; the sum in element order)
-  double d2 = 0.0;
+  const bool solved = solve6_schur(tot, d);
+  bool done = true;
+  if (j == 0 || cost <= best_cost) {  // accept the evaluated pose
+    if (lane < 12) s.cur[lane] = cur_l;
+    best_cost = cost;
+    best_count = count;
+    // converged: a step shorter than 1e-10 (norm of (dw, dt)) is not taken and
+    // ends the run (every lane holds d; the sum in element order)
+    double d2 = 0.0;
 #pragma unroll
-  for (int e = 0; e < 6; ++e) d2 += d[e] * d[e];
-  if (d2 < kStepTol2) {
-    if (lane == 0) s.done = 1;
-    return true;
+    for (int e = 0; e < 6; ++e) d2 += d[e] * d[e];
+    if (j < iters && solved && !(d2 < kStepTol2)) {
+      // left update: R' = Exp(dw) R, t' = Exp(dw) t + dt, element `lane` (< 12)
+      double E[9];
+      so3_exp(d, E);
+      // row rr of E and entry rr of the translation step by selects (a lane-indexed
+      // register array would be placed in scratch memory)
+      const double er0 = rr == 0 ? E[0] : (rr == 1 ? E[3] : E[6]);
+      const double er1 = rr == 0 ? E[1] : (rr == 1 ? E[4] : E[7]);
+      const double er2 = rr == 0 ? E[2] : (rr == 1 ? E[5] : E[8]);
+      const double dt = rr == 0 ? d[3] : (rr == 1 ? d[4] : d[5]);
+      const double v = fma(er0, p0, fma(er1, p1, er2 * p2)) + (cc < 3 ? 0.0 : dt);
+      if (lane < 12) s.eval[lane] = v;
+      done = false;
+    }
   }
-  // left update: R' = Exp(dw) R, t' = Exp(dw) t + dt, element `lane` (< 12)
-  double E[9];
-  so3_exp(d, E);
-  if (lane < 12) {
-    const int rr = lane < 9 ? lane / 3 : lane - 9, cc = lane < 9 ? lane % 3 : 3;
-    const double* cur = s.eval;  // the accepted pose (s.cur holds the same values)
-    // row rr of E and entry rr of the translation step by selects (a lane-indexed
-    // register array would be placed in scratch memory)
-    const double er0 = rr == 0 ? E[0] : (rr == 1 ? E[3] : E[6]);
-    const double er1 = rr == 0 ? E[1] : (rr == 1 ? E[4] : E[7]);
-    const double er2 = rr == 0 ? E[2] : (rr == 1 ? E[5] : E[8]);
-    const double dt = rr == 0 ? d[3] : (rr == 1 ? d[4] : d[5]);
-    const double v = cc < 3 ? er0 * cur[cc] + er1 * cur[3 + cc] + er2 * cur[6 + cc]
-                            : er0 * cur[9] + er1 * cur[10] + er2 * cur[11] + dt;
-    __builtin_amdgcn_wave_barrier();
-    s.eval[lane] = v;
-  }
-  return false;
+  if (lane == 0) s.done = done;
 }
 
-// A recorded state read into registers at kernel entry (threads 0..11 hold
-// one element of cur and eval, every thread the scalars), so that its latency
-// overlaps the other loads; gn_state_to_lds then publishes it.
-struct GNStateRegs {
-  double cur, eval, cost, count;
-  int done, accepted;
+// LDS of a workgroup.
+struct GNLds {
+  double rows[2][kGNWaves][kAcc];
+  double in[kGNInBlock][kAcc];
+  double tot[kAcc];
+  GNShared s;
+  int kept[kGNGroup / kGNThreads][kGNWaves];
+  unsigned miss;
+  int alone, role;
 };
 
-__device__ __forceinline__ void gn_state_issue(const GNState* st, GNStateRegs& r) {
-  r.cur = r.eval = 0.0;
-  r.cost = __builtin_inf();
-  r.count = 0.0;
-  r.done = r.accepted = 0;
-  if (!st) return;
-  if (threadIdx.x < 12) {
-    r.cur = st->cur[threadIdx.x];
-    r.eval = st->eval[threadIdx.x];
-  }
-  // uniform loads (every thread): no divergent region forces an early wait
-  r.cost = st->cur_cost;
-  r.count = st->cur_count;
-  r.done = st->done;
-  r.accepted = st->accepted;
-}
-
-// From the registers, or (have = false) the initial state at start.
-__device__ __forceinline__ void gn_state_to_lds(GNShared& s, const GNStateRegs& r, bool have, const double* start) {
-  if (threadIdx.x < 12) {
-    s.cur[threadIdx.x] = have ? r.cur : start[threadIdx.x];
-    s.eval[threadIdx.x] = have ? r.eval : start[threadIdx.x];
-  }
-  if (threadIdx.x == 0) {
-    s.cost = have ? r.cost : __builtin_inf();
-    s.count = have ? r.count : 0.0;
-    s.done = have ? r.done : 0;
-    s.accepted = have ? r.accepted : 0;
-  }
-}
-
-__device__ __forceinline__ void gn_store_state(const GNShared& s, GNState* st) {
-  if (threadIdx.x < 12) {
-    st->cur[threadIdx.x] = s.cur[threadIdx.x];
-    st->eval[threadIdx.x] = s.eval[threadIdx.x];
-  }
-  if (threadIdx.x == 0) {
-    st->cur_cost = s.cost;
-    st->cur_count = s.count;
-    st->done = s.done;
-    st->accepted = s.accepted;
-  }
-}
-
-// the same from the registers of gn_state_issue
-__device__ __forceinline__ void gn_store_state_regs(const GNStateRegs& r, GNState* st) {
-  if (threadIdx.x < 12) {
-    st->cur[threadIdx.x] = r.cur;
-    st->eval[threadIdx.x] = r.eval;
-  }
-  if (threadIdx.x == 0) {
-    st->cur_cost = r.cost;
-    st->cur_count = r.count;
-    st->done = r.done;
-    st->accepted = r.accepted;
-  }
-}
-
-__device__ __forceinline__ void gn_outputs(const GNArgs& g, const GNShared& s, int p) {
-  if (threadIdx.x < 12 && g.out_pose) g.out_pose[12 * (int64_t)p + threadIdx.x] = s.cur[threadIdx.x];
-  if (threadIdx.x == 0) {
-    if (g.out_cost) g.out_cost[p] = s.cost;
-    if (g.out_count) g.out_count[p] = (int64_t)s.count;
-  }
-}
-
-// A chunk's points, loaded into registers: point t of the thread is point
-// chunk * kGNChunk + loc[t] of the set.
-struct GNPoints {
-  float X[kGNPPT], Y[kGNPPT], Z[kGNPPT], u[kGNPPT], v[kGNPPT], w[kGNPPT];
-  bool use[kGNPPT];
-  int loc[kGNPPT];
-  bool has_w;  // confidence weights present (else every weight is 1)
+// The points of a member's only group -- in the refinement, after its first
+// evaluation, those of its in-set -- stay in (dynamic) LDS, so that an
+// evaluation reads no memory.  Unused slots of the last slice have u = NaN and
+// w = 0.
+struct GNResident {
+  float pt[6][kGNGroup];
+  uint8_t cam[kGNGroup];
 };
 
-// Every point of the chunk (thread t: offsets t, t + 256).  Branch-free:
-// lanes past the end load the last point (and do not use it), a query without
-// points or weights reads from `safe` (any valid device address), and every
-// select happens where the value is used -- so the loads issue back to back
-// and nothing waits for them before the accumulation.
-__device__ __forceinline__ void gn_load_points(const CorrF32& c, int64_t n, int chunk, const void* safe,
-                                               GNPoints& pt) {
-  const bool any = n > 0;
-  const float* sf = reinterpret_cast<const float*>(safe);
-  const float* X = any ? c.X : sf;
-  const float* Y = any ? c.Y : sf;
-  const float* Z = any ? c.Z : sf;
-  const float* U = any ? c.u : sf;
-  const float* V = any ? c.v : sf;
-  const float* W = any && c.w ? c.w : X;
-  pt.has_w = any && c.w != nullptr;
+// A barrier that orders LDS alone: memory loads in flight stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Entry i of a uniform array, addressed from scalar registers.
+__device__ __forceinline__ float at_u32(const float* base, unsigned i) {
+  return *(const __attribute__((address_space(1))) float*)((const __attribute__((address_space(1))) char*)base +
+                                                           (size_t)(i * 4u));
+}
+
+// A resident group into LDS: every load is in flight before the first is
+// waited for (the first evaluation took 2,300 cycles per slice of 256 points
+// when it loaded them itself, one slice ahead).
+template <bool RIG>
+__device__ __forceinline__ void gn_load_resident(GNResident& R, const GNView& g, int64_t g0, int pts) {
+  constexpr int kSlices = kGNGroup / kGNThreads;
+  const float* src[6] = {g.c.X + g0, g.c.Y + g0, g.c.Z + g0, g.c.u + g0, g.c.v + g0, g.c.w ? g.c.w + g0 : g.c.X + g0};
+  float x[6][kSlices];
 #pragma unroll
-  for (int t = 0; t < kGNPPT; ++t) {
-    pt.loc[t] = (int)threadIdx.x + t * kGNThreads;
-    const int64_t i = (int64_t)chunk * kGNChunk + pt.loc[t];
-    pt.use[t] = i < n;
-    const int64_t ic = i < n ? i : (any ? n - 1 : 0);
-    pt.X[t] = gmem(X)[ic];
-    pt.Y[t] = gmem(Y)[ic];
-    pt.Z[t] = gmem(Z)[ic];
-    pt.u[t] = gmem(U)[ic];
-    pt.v[t] = gmem(V)[ic];
-    pt.w[t] = gmem(W)[ic];
+  for (int k = 0; k < kSlices; ++k) {
+    if (k * kGNThreads >= pts) break;
+    const int i = k * kGNThreads + (int)threadIdx.x;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) x[c][k] = at_u32(src[c], i < pts ? i : pts - 1);
+  }
+#pragma unroll
+  for (int k = 0; k < kSlices; ++k) {
+    if (k * kGNThreads >= pts) break;
+    const int i = k * kGNThreads + (int)threadIdx.x;
+    const bool use = i < pts;
+    R.pt[0][i] = x[0][k]; R.pt[1][i] = x[1][k]; R.pt[2][i] = x[2][k];
+    R.pt[3][i] = use ? x[3][k] : __builtin_nanf("");
+    R.pt[4][i] = x[4][k];
+    R.pt[5][i] = use ? (g.c.w ? x[5][k] : 1.0f) : 0.0f;
+    if (RIG) R.cam[i] = g.ncam > 0 ? (uint8_t)cam_of(g.seg, g.ncam, g0 + i) : 0;
   }
 }
 
-// The in-set points of the chunk (final refinement after its first
-// evaluation): thread t takes the compacted positions t and t + 256.  The
-// count and the offsets are loaded together (offsets past the count are read
-// but not used), then the points.
-__device__ __forceinline__ void gn_load_points_inset(const CorrF32& c, int64_t n, int chunk, const uint8_t* inset,
-                                                     const void* safe, GNPoints& pt) {
-  const bool any = n > 0;
-  const int64_t C = chunks_for(n);
-  // workgroups past the query's chunks read its last chunk (and exit later)
-  const int cc = chunk < C ? chunk : (int)C - 1;
-  const uint16_t* cnts = reinterpret_cast<const uint16_t*>(any ? inset : reinterpret_cast<const uint8_t*>(safe));
-  const uint16_t* offs = any ? reinterpret_cast<const uint16_t*>(inset + inset_head_bytes(C)) + (int64_t)cc * kGNChunk
-                             : reinterpret_cast<const uint16_t*>(safe);
-  // (a query without points reads element 0 of `safe`)
-  const int cnt = any ? (int)gmem(cnts)[any ? cc : 0] : 0;
-  int off[kGNPPT];
+// Keep a resident group's in-set alone, in point order: bit k of `taken` says
+// whether this thread's point k (index 256 k + thread) is in it.  The points
+// pass through registers, as their new places may be other threads' old ones.
+// Returns their number.
+template <bool RIG>
+__device__ __forceinline__ int gn_keep_resident(GNLds& L, GNResident& R, unsigned taken, int steps) {
+  constexpr int kSlices = kGNGroup / kGNThreads;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  float x[6][kSlices];
+  int cam[kSlices], at[kSlices];
 #pragma unroll
-  for (int t = 0; t < kGNPPT; ++t) off[t] = any ? (int)gmem(offs)[any ? (int)threadIdx.x + t * kGNThreads : 0] : 0;
-  const float* sf = reinterpret_cast<const float*>(safe);
-  const float* X = any ? c.X : sf;
-  const float* Y = any ? c.Y : sf;
-  const float* Z = any ? c.Z : sf;
-  const float* U = any ? c.u : sf;
-  const float* V = any ? c.v : sf;
-  const float* W = any && c.w ? c.w : X;
-  pt.has_w = any && c.w != nullptr;
+  for (int k = 0; k < kSlices; ++k) {
+    if (k >= steps) break;
+    const int i = k * kGNThreads + (int)threadIdx.x;
 #pragma unroll
-  for (int t = 0; t < kGNPPT; ++t) {
-    pt.use[t] = (int)threadIdx.x + t * kGNThreads < cnt;
-    pt.loc[t] = pt.use[t] ? off[t] : 0;
-    const int64_t i = (int64_t)cc * kGNChunk + pt.loc[t];
-    const int64_t ic = i < n ? i : (any ? n - 1 : 0);
-    pt.X[t] = gmem(X)[ic];
-    pt.Y[t] = gmem(Y)[ic];
-    pt.Z[t] = gmem(Z)[ic];
-    pt.u[t] = gmem(U)[ic];
-    pt.v[t] = gmem(V)[ic];
-    pt.w[t] = gmem(W)[ic];
+    for (int c = 0; c < 6; ++c) x[c][k] = R.pt[c][i];
+    cam[k] = RIG ? R.cam[i] : 0;
+    const uint64_t bal = __ballot((taken >> k) & 1u);
+    at[k] = __popcll(bal & ((1ull << lane) - 1ull));
+    if (lane == 0) L.kept[k][wave] = __popcll(bal);
   }
+  lds_barrier();
+  int base = 0;
+#pragma unroll
+  for (int k = 0; k < kSlices; ++k) {
+    if (k >= steps) break;
+    int mine = base + at[k];
+#pragma unroll
+    for (int w = 0; w < kGNWaves; ++w) {
+      const int c = L.kept[k][w];
+      mine += w < wave ? c : 0;
+      base += c;
+    }
+    if ((taken >> k) & 1u) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) R.pt[c][mine] = x[c][k];
+      if (RIG) R.cam[mine] = (uint8_t)cam[k];
+    }
+  }
+  return __builtin_amdgcn_readfirstlane(base);
 }
 
-// Accumulate one chunk at pose P and store its partial sums: per thread in
-// point order, then across the wave by recursive halving, then the waves in
-// wave order.  The final refinement's first evaluation (MODE 1, j = 0) also
-// writes the chunk's compacted in-set (its count and offsets).
-template <int MODE, bool RIG, bool W>
-__device__ __forceinline__ void gn_accumulate(const QueryDesc& d, const double* s_rig, const double* P, int j,
-                                              int chunk, const GNPoints& pt, uint8_t* inset,
-                                              double (*s_rows)[kAcc], double* part_out) {
-  const double tau2 = d.tau * d.tau, s2 = d.cauchy_s * d.cauchy_s;
-  const double inv_s2 = 1.0 / s2;
-  const Cam K{d.fx, d.fy, d.cx, d.cy};
-  const bool rig = RIG && d.ncam > 0;
-  const int64_t* seg = MODE == 0 ? d.segS : d.segF;
+// One evaluation of one group at pose P: accumulate per thread in point
+// order, across the wave by recursive halving, then the waves in wave order.
+// Threads 0..28 return the sums.  The refinement's first evaluation lists the
+// group's in-set in point order (in LDS or in `list`); later ones read that:
+// thread t takes its points t, t + 256, ...  n_in: the set's size (resident).
+// `turn` alternates between calls.
+template <int MODE, bool RIG, bool RES>
+__device__ __forceinline__ double gn_eval_group(GNLds& L, GNResident& R, const GNView& g, const double* s_rig,
+                                                const double* P, int grp, bool first, bool in_lds, uint16_t* list,
+                                                int& n_in, int turn) {
+  const bool resident = RES && in_lds;
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int S = gn_group_points(g.n);
+  const int64_t g0 = (int64_t)grp * S;
+  const int64_t left = g.n - g0;
+  const int pts = (int)(left < S ? (left > 0 ? left : 0) : S);
+  const bool from_set = MODE == 1 && !first;
+  const int items = from_set && resident ? n_in : pts;
+  const int steps = __builtin_amdgcn_readfirstlane((items + kGNThreads - 1) / kGNThreads);
+  const float *GX = g.c.X + g0, *GY = g.c.Y + g0, *GZ = g.c.Z + g0, *GU = g.c.u + g0, *GV = g.c.v + g0,
+              *GW = g.c.w ? g.c.w + g0 : GX;
+  const bool has_w = g.c.w != nullptr;
+  const int last = items > 0 ? items - 1 : 0;
+  // point k of this thread; past the end some other one, not used
+  auto fetch = [&](int k) {
+    GNPt t;
+    t.cam = 0;
+    const int item = k * kGNThreads + (int)threadIdx.x;
+    t.use = item < items;
+    if (pts > 0) {
+      unsigned i = t.use ? item : last;
+      if (from_set) {
+        i = list[i];
+        t.use = t.use && i != kGNNone;
+        i = t.use ? i : 0;
+      }
+      t.X = at_u32(GX, i); t.Y = at_u32(GY, i); t.Z = at_u32(GZ, i); t.u = at_u32(GU, i); t.v = at_u32(GV, i);
+      t.w = at_u32(GW, i);
+      if (RIG && g.ncam > 0) t.cam = cam_of(g.seg, g.ncam, g0 + i);
+    }
+    return t;
+  };
+  double pose[12];
+#pragma unroll
+  for (int e = 0; e < 12; ++e) pose[e] = e < 9 ? uniform(P[e]) : P[e];  // (one scalar operand per multiply-add)
   double a[kAcc];
 #pragma unroll
   for (int e = 0; e < kAcc; ++e) a[e] = 0.0;
-  bool keep[kGNPPT];  // MODE 1, j = 0: the point is in the set
-#pragma unroll
-  for (int t = 0; t < kGNPPT; ++t) {
-    keep[t] = false;
-    if (!pt.use[t]) continue;
-    const int64_t i = (int64_t)chunk * kGNChunk + pt.loc[t];
-    const double X = pt.X[t], Y = pt.Y[t], Z = pt.Z[t];
-    const double w = pt.has_w ? (double)pt.w[t] : 1.0;
-    double x = P[0] * X + P[1] * Y + P[2] * Z + P[9];
-    double y = P[3] * X + P[4] * Y + P[5] * Z + P[10];
-    double z = P[6] * X + P[7] * Y + P[8] * Z + P[11];
-    Cam Kp = K;
-    const double* Rc = nullptr;
-    const double xr[3] = {x, y, z};
-    if (rig) {  // through the point's camera: x_c = R_c x_r + t_c
-      const double* rc = s_rig + 16 * cam_of(seg, d.ncam, i);
-      Kp = Cam{rc[0], rc[1], rc[2], rc[3]};
-      Rc = rc + 4;
-      x = Rc[0] * xr[0] + Rc[1] * xr[1] + Rc[2] * xr[2] + rc[13];
-      y = Rc[3] * xr[0] + Rc[4] * xr[1] + Rc[5] * xr[2] + rc[14];
-      z = Rc[6] * xr[0] + Rc[7] * xr[1] + Rc[8] * xr[2] + rc[15];
+  int count = 0, kept = 0;
+  if (resident) {
+    // the loop of a latency-bound run: a lone wave per SIMD pays for every
+    // scalar instruction too, so nothing but the points is in it (MODE 1 with
+    // the general loop's control: 1,350 cycles per step, with this 950)
+    int i = threadIdx.x;
+    unsigned taken = 0;  // bit k: this thread's point k
+    auto load = [&](GNPt& t, int at) {
+      at &= kGNGroup - 1;
+      t.X = R.pt[0][at]; t.Y = R.pt[1][at]; t.Z = R.pt[2][at]; t.u = R.pt[3][at]; t.v = R.pt[4][at]; t.w = R.pt[5][at];
+      t.cam = RIG ? R.cam[at] : 0;
+    };
+    GNPt next;
+    load(next, i);
+    for (int k = 0; k < steps; ++k) {
+      GNPt t = next;
+      load(next, i + kGNThreads);
+      t.use = MODE == 0 || i < items;
+      if (RIG && MODE == 1) t.cam = t.use ? t.cam : 0;
+      const bool take = gn_point<MODE, RIG>(g, s_rig, pose, first, t, a);
+      count += __popcll(__ballot(take));
+      if (MODE == 1) taken |= (unsigned)take << k;
+      i += kGNThreads;
     }
-    double du = 0.0, dv = 0.0, r2 = 0.0, iz = 0.0;
-    const bool front = z > 0.0;
-    if (front) {
-      iz = recip_pos(z);
-      du = Kp.fx * x * iz + Kp.cx - (double)pt.u[t];
-      dv = Kp.fy * y * iz + Kp.cy - (double)pt.v[t];
-      r2 = du * du + dv * dv;
-    }
-    if (MODE == 0) {
-      if (front && r2 < tau2) {
-        a[27] += w * r2;
-        a[28] += 1.0;
-        if (rig) acc_point_rig(a, Kp, xr, x, y, iz, Rc, du, dv, w);
-        else acc_point<W>(a, K, x, y, z, iz, du, dv, w);
-      } else {
-        a[27] += w * tau2;
+    if (MODE == 1 && first) n_in = gn_keep_resident<RIG>(L, R, taken, steps);
+  } else {
+    GNPt next = fetch(0);
+    for (int k = 0; k < steps; ++k) {
+      GNPt t = next;
+      next = fetch(k + 1);
+      t.u = t.use ? t.u : __builtin_nanf("");
+      t.w = t.use ? (has_w ? t.w : 1.0f) : 0.0f;
+      const bool take = gn_point<MODE, RIG>(g, s_rig, pose, first, t, a);
+      const uint64_t bal = __ballot(take);
+      count += __popcll(bal);
+      if (MODE == 1 && first) {  // rank in point order: the waves' counts of this slice
+        int* cnt = L.kept[k & 1];
+        if (lane == 0) cnt[wave] = __popcll(bal);
+        lds_barrier();
+        int at = kept + __popcll(bal & ((1ull << lane) - 1ull));
+  #pragma unroll
+        for (int w = 0; w < kGNWaves; ++w) {
+          at += w < wave ? cnt[w] : 0;
+          kept += cnt[w];
+        }
+        if (take) list[at] = (uint16_t)(k * kGNThreads + (int)threadIdx.x);
+      } else if (from_set && bal == 0) {
+        break;  // (past the end of the list: it is dense)
       }
-    } else {
-      if (j == 0) {
-        keep[t] = front && r2 < tau2;
-        if (!keep[t]) continue;
-      }
-      a[28] += 1.0;
-      if (!front) {
-        a[27] += w * s2 * log1p(tau2 * inv_s2);
-        continue;
-      }
-      const double q = r2 * inv_s2;
-      a[27] += w * s2 * log1p(q);
-      const double wc = w * recip_pos(1.0 + q);  // the Cauchy weight
-      if (rig) acc_point_rig(a, Kp, xr, x, y, iz, Rc, du, dv, wc);
-      else acc_point<true>(a, K, x, y, z, iz, du, dv, wc);
     }
   }
-  if (MODE == 1 && j == 0) {  // the chunk's in-set: points of slot 0 in lane order, then slot 1
-    __shared__ int s_cnt[kGNPPT][kGNWaves];
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    uint64_t m[kGNPPT];
-#pragma unroll
-    for (int t = 0; t < kGNPPT; ++t) {
-      m[t] = __ballot(keep[t]);
-      if (lane == 0) s_cnt[t][wave] = __popcll(m[t]);
-    }
-    __syncthreads();
-    const int64_t C = chunks_for(d.n);
-    uint16_t* offs = reinterpret_cast<uint16_t*>(inset + inset_head_bytes(C)) + (int64_t)chunk * kGNChunk;
-    int before = 0;
-#pragma unroll
-    for (int t = 0; t < kGNPPT; ++t) {
-      int pos = before;
-      for (int w = 0; w < wave; ++w) pos += s_cnt[t][w];
-      pos += __popcll(m[t] & ((1ull << lane) - 1ull));
-      if (keep[t]) offs[pos] = (uint16_t)pt.loc[t];
-      for (int w = 0; w < kGNWaves; ++w) before += s_cnt[t][w];
-    }
-    if (threadIdx.x == 0) reinterpret_cast<uint16_t*>(inset)[chunk] = (uint16_t)before;
-  }
+  if (MODE == 1 && first && !resident)
+    for (int e = kept + (int)threadIdx.x; e < pts; e += kGNThreads) list[e] = kGNNone;
+  a[28] = lane == 0 ? (double)count : 0.0;
   const double tot = wave_sum29(a);
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  if ((lane & 1) == 0 && (lane >> 1) < kAcc) s_rows[wave][lane >> 1] = tot;
-  __syncthreads();
+  double (*rows)[kAcc] = L.rows[turn & 1];
+  if ((lane & 1) == 0 && (lane >> 1) < kAcc) rows[wave][lane >> 1] = tot;
+  if (MODE == 1 && first) __syncthreads();  // (also publishes the in-set to the other waves)
+  else lds_barrier();
+  double sum = 0.0;
   if ((int)threadIdx.x < kAcc) {
-    double t = 0.0;
 #pragma unroll
-    for (int w = 0; w < kGNWaves; ++w) t += s_rows[w][threadIdx.x];
-    part_out[threadIdx.x] = t;
+    for (int w = 0; w < kGNWaves; ++w) sum += rows[w][threadIdx.x];
+  }
+  return sum;
+}
+
+// A word pair of a mailbox: one value and the tag of its evaluation (the low
+// halves of all values, then the high ones: whole cache lines per load).
+constexpr int kBoxHigh = 32;
+__device__ __forceinline__ void box_put(uint64_t* w, double v, unsigned tag) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  __hip_atomic_store(w, (b << 32) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(w + kBoxHigh, (b & 0xffffffff00000000ull) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The sums of groups [b0, b0 + nb) into L.in: every thread polls its values
+// together (one memory latency, not one per value).  A group that has not
+// come after `most` polls is marked in L.miss.
+__device__ __forceinline__ void box_get(GNLds& L, const uint64_t* box, int b0, int nb, unsigned tag, int most) {
+  constexpr int kPer = (kGNInBlock * kAcc + kGNThreads - 1) / kGNThreads;  // values per thread
+  bool need[kPer];
+  int at[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int e = (int)threadIdx.x + u * kGNThreads;
+    need[u] = e < nb * kAcc;
+    const int gi = e / kAcc;
+    at[u] = gi * kGNBox + (e - gi * kAcc);
+  }
+  const int per = (nb * kAcc + kGNThreads - 1) / kGNThreads;
+  for (int n = 0;; ++n) {
+    uint64_t lo[kPer], hi[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      if (u >= per) break;
+      const uint64_t* w = box + (int64_t)b0 * kGNBox + (need[u] ? at[u] : 0);
+      lo[u] = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      hi[u] = __hip_atomic_load(w + kBoxHigh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    bool wait = false;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      if (u >= per || !need[u]) continue;
+      if ((unsigned)lo[u] == tag && (unsigned)hi[u] == tag) {
+        const int gi = at[u] / kGNBox;
+        L.in[gi][at[u] - gi * kGNBox] =
+            __longlong_as_double((long long)((hi[u] & 0xffffffff00000000ull) | (lo[u] >> 32)));
+        need[u] = false;
+      } else {
+        wait = true;
+      }
+    }
+    if (!wait) break;
+    if (n >= most) {
+#pragma unroll
+      for (int u = 0; u < kPer; ++u)
+        if (need[u]) atomicOr(&L.miss, 1u << (at[u] / kGNBox));
+      break;
+    }
   }
 }
 
-// Fused launch k of a run (one launch per iteration): decision k - 1 on the
-// partial sums of launch k - 1, taken redundantly by every workgroup of the
-// problem (so no workgroup waits for another), then evaluation k.  Launch 0
-// only evaluates the start pose; the last launch only decides.  Workgroup
-// (0, p) records the state for the next launch and, when the run ends, the
-// outputs.
-template <int MODE, bool RIG, bool W>
-__global__ __launch_bounds__(kGNThreads) void gn_fused_kernel(GNArgs g, int k) {
-  const int p = blockIdx.y;
-  const int chunk = blockIdx.x;
-  asm volatile("" ::"s"(g.qd), "s"(g.part), "s"(g.gst));
-  // loads whose addresses need only the launch: partial sums, descriptor
-  // fields, state -- issued together, so that one round trip covers them (the
-  // compiler would otherwise fetch each field in the branch that first uses it)
-  // the state first: a run that has ended waits for it alone (below)
-  GNStateRegs sr;
-  gn_state_issue(k >= 2 ? g.gst + (int64_t)(k & 1) * g.nprob + p : nullptr, sr);
-  GNPart pr;
-  if (k > 0) gn_part_issue(gn_part(g, (k - 1) & 1, p), g.cmax, pr);
-  const int q = gn_query<MODE>(g, p);
+// A member's whole run.  Tickets count query by query, problem by problem,
+// member by member (QueryDesc::lo_team0 / fin_team0 are the running totals).
+template <int MODE, bool RIG, bool RES>
+__global__ __launch_bounds__(kGNThreads)
+__attribute__((amdgpu_waves_per_eu(RES || RIG ? 2 : kGNWavesMany, RES || RIG ? 2 : kGNWavesMany))) void gn_team_kernel(
+    GNArgs g) {
+  __shared__ GNLds L;
+  __shared__ double s_rig[RIG ? kMaxCams * kGNRig : 1];
+  extern __shared__ GNResident s_resident[];
+  GNResident& R = s_resident[0];
+  const int tid = threadIdx.x;
+  if (tid == 0) {
+    L.role = g.ticket ? atomicAdd(g.ticket, 1) : (int)blockIdx.x;
+    L.miss = 0;
+    L.alone = 0;
+  }
+  __syncthreads();
+  const int role = __builtin_amdgcn_readfirstlane(L.role);  // (uniform: descriptors come by scalar loads)
+  int q = 0;
+  if (g.nq > 1) {  // the last query whose first ticket is not above this one
+    int seen = 0;
+    for (int e = 0; e < g.nq; e += kGNThreads) {
+      const int i = e + tid;
+      const int t0 = i < g.nq ? (MODE == 0 ? g.qd[i].lo_team0 : g.qd[i].fin_team0) : 0x7fffffff;
+      seen += __syncthreads_count(t0 <= role);
+    }
+    q = __builtin_amdgcn_readfirstlane(seen - 1);
+  }
   const QueryDesc& d = g.qd[q];
-  const CorrF32 c = MODE == 0 ? d.S : d.full;
-  const int64_t n = MODE == 0 ? d.m : d.n;
-  uint8_t* in_set = MODE == 1 ? g.in_set_all + d.in_set_off : nullptr;
-  asm volatile("" ::"s"(c.X), "s"(c.Y), "s"(c.Z), "s"(c.u), "s"(c.v), "s"(c.w), "s"(n), "s"(in_set));
-  // the points are loaded before any test (indices are clamped), so that the
-  // descriptor fields are read together and the point latency overlaps the
-  // reduction and the decision; the final refinement reads its compacted
-  // in-set from the second launch on
-  GNPoints pt;
-  if (MODE == 1 && k > 0) gn_load_points_inset(c, n, chunk, in_set, g.part, pt);
-  else gn_load_points(c, n, chunk, g.part, pt);
-  // A run that ended at an earlier launch: decision k - 1 would leave its
-  // state as it is, so carry the state to the slot the next launch reads and
-  // stop, without waiting for the partial sums and points in flight.
-  if (k >= 2 && sr.done) {
-    if (chunk == 0) gn_store_state_regs(sr, g.gst + (int64_t)((k - 1) & 1) * g.nprob + p);
+  const int T = g.start_direct ? g.team_direct : (MODE == 0 ? d.lo_team : d.fin_team);
+  const int local = role - (g.start_direct ? 0 : (MODE == 0 ? d.lo_team0 : d.fin_team0));
+  const int slot = local / T, member = local - slot * T;
+  const int p = MODE == 0 ? q * g.kmax + slot : q;  // the problem: its mailboxes and outputs
+  bool live = true;
+  if (!g.start_direct) live = MODE == 0 ? slot < g.n_sel[q] : (g.bst[q].finished == 1) & (g.bst[q].have != 0);
+  GNView v;
+  v.c = MODE == 0 ? d.S : d.full;
+  v.n = MODE == 0 ? d.m : d.n;
+  const int G = groups_for(v.n), S = gn_group_points(v.n);
+  if (!live) {
+    // a finished query without a pose gets an all-zero mask
+    if (MODE == 1 && g.write_mask && d.mask && g.bst[q].finished == 1)
+      for (int grp = member; grp < G; grp += T)
+        for (int e = tid; e < S; e += kGNThreads)
+          if ((int64_t)grp * S + e < v.n) d.mask[(int64_t)grp * S + e] = 0;
     return;
   }
-  const int C = chunks_for(n);
-  if (chunk >= C) return;
+  v.ncam = d.ncam;
+  v.seg = MODE == 0 ? d.segS : d.segF;
+  v.ifx = uniform(1.0 / d.fx);
+  v.ify = uniform(1.0 / d.fy);
+  v.ucx = uniform(-d.cx * v.ifx);
+  v.vcy = uniform(-d.cy * v.ify);
+  v.fx2 = uniform(d.fx * d.fx);
+  v.fy2 = uniform(d.fy * d.fy);
+  v.tau2 = uniform(d.tau * d.tau);
+  const double s2 = uniform(d.cauchy_s * d.cauchy_s);
+  v.inv_s2 = uniform(1.0 / s2);
+  const bool resident = RES && G <= T && S <= kGNGroup;
   const int iters = MODE == 0 ? d.lo_iters : d.final_iters;
-
-  __shared__ double s_rig[RIG ? kMaxCams * 16 : 1];
-  if (RIG && d.ncam > 0)
-    for (int e = threadIdx.x; e < 16 * d.ncam; e += kGNThreads) s_rig[e] = d.rig[e];
-  __shared__ double s_grp[8][kAcc];
-  __shared__ double s_tot[kAcc];
-  __shared__ double s_rows[kGNWaves][kAcc];
-  __shared__ GNShared s;
-  __shared__ int s_end;
-  // the partial sums are added before the liveness test, so that their loads
-  // need not wait for it (a problem without work reads harmless stale values)
-  const bool live = gn_live<MODE>(g, p, q);
-  if (k == 0) {
-    if (!live) {
-      // a finished query without a pose gets an all-zero mask
-      if (MODE == 1 && g.fuse_mask && d.mask && g.bst[q].finished == 1) {
-#pragma unroll
-        for (int t = 0; t < kGNPPT; ++t)
-          if (pt.use[t]) d.mask[(int64_t)chunk * kGNChunk + pt.loc[t]] = 0;
+  if (resident && v.n > 0) {
+    const int64_t g0 = (int64_t)member * S;
+    gn_load_resident<RIG>(R, v, g0, (int)(v.n - g0 < S ? v.n - g0 : S));
+  }
+  const double* start = g.start_direct ? g.start_direct + 12 * (int64_t)p
+                        : MODE == 0    ? g.cb.pose + 12 * (d.cand_off + g.sel[q * kMaxTopK + slot])
+                                       : g.bst[q].pose;
+  if (tid < 12) L.s.cur[tid] = L.s.eval[tid] = L.s.start[tid] = start[tid];
+  if (RIG && tid < d.ncam) {  // R, t, then the camera's scales
+    const double* rc = d.rig + 16 * tid;
+    double* o = s_rig + kGNRig * tid;
+    for (int e = 0; e < 12; ++e) o[e] = rc[4 + e];
+    o[12] = 1.0 / rc[0];
+    o[13] = 1.0 / rc[1];
+    o[14] = -rc[2] * o[12];
+    o[15] = -rc[3] * o[13];
+    o[16] = rc[0] * rc[0];
+    o[17] = rc[1] * rc[1];
+  }
+  __syncthreads();
+  uint16_t* lists = MODE == 1 ? reinterpret_cast<uint16_t*>(g.in_set_all + d.in_set_off) : nullptr;
+  // tags of this round's evaluations (the mailboxes hold those of earlier rounds)
+  const unsigned tag0 = MODE == 0 && g.bst ? (unsigned)g.bst[q].batches * 1024u : 0u;
+  int n_in = 0, other_in = 0, turn = 0;
+  double best_cost = 0.0, best_count = 0.0;  // (wave 0)
+  for (int j = 0;; ++j) {
+    uint64_t* box = g.box + ((int64_t)p * 2 + (j & 1)) * g.box_groups * kGNBox;
+    const unsigned tag = tag0 + (unsigned)j + 1u;
+    double tot = 0.0;
+    // The groups of this evaluation: the member's own, then (T > 1) block by
+    // block those of the others from their mailboxes, and of these the
+    // missing ones from their points (alone; the refinement lists their set
+    // first).  One loop, so that the evaluation is in the code once.
+    int grp = member, b0 = -kGNInBlock, nb = 0;
+    unsigned miss = 0;
+    bool own = true, listed = MODE == 0 || j == 0;
+    for (;;) {
+      if (own ? grp < G : miss != 0) {
+        const int gi = own ? 0 : __builtin_ctz(miss);
+        const int at = own ? grp : b0 + gi;
+        const bool list_only = !own && !listed;
+        const double sum = gn_eval_group<MODE, RIG, RES>(L, R, v, s_rig, list_only ? L.s.start : L.s.eval, at,
+                                                    j == 0 || list_only, own && resident,
+                                                    MODE == 1 ? lists + (int64_t)at * S : nullptr,
+                                                    own ? n_in : other_in, turn++);
+        if (own) {
+          if (tid < kAcc) {
+            if (T == 1) tot += sum;
+            else box_put(box + (int64_t)grp * kGNBox + tid, sum, tag);
+          }
+          grp += T;
+        } else if (list_only) {
+          listed = true;
+        } else {
+          if (tid < kAcc) L.in[gi][tid] = sum;
+          miss &= miss - 1;
+          listed = MODE == 0 || j == 0;
+        }
+        continue;
       }
-      return;
+      if (T == 1) break;
+      if (!own) {  // a block is complete
+        if (tid < kAcc)
+          for (int gi = 0; gi < nb; ++gi) tot += L.in[gi][tid];
+        if (b0 + kGNInBlock >= G) break;
+        __syncthreads();  // before its slots are used again
+      }
+      own = false;
+      b0 += kGNInBlock;
+      nb = G - b0 < kGNInBlock ? G - b0 : kGNInBlock;
+      box_get(L, box, b0, nb, tag, L.alone ? 0 : g.polls);
+      __syncthreads();
+      miss = L.miss;
+      if (miss) {
+        __syncthreads();
+        if (tid == 0) {
+          L.miss = 0;
+          L.alone = 1;
+        }
+      }
     }
-    gn_state_to_lds(s, sr, false, gn_start<MODE>(g, p, q));
-    __syncthreads();
-  } else {
-    gn_part_sum(gn_part(g, (k - 1) & 1, p), C, pr, s_grp, s_tot);
-    if (!live) return;
-    gn_state_to_lds(s, sr, k >= 2, k >= 2 ? nullptr : gn_start<MODE>(g, p, q));
-    __syncthreads();
-    if (threadIdx.x < kWave) {
-      const bool end = gn_decide_wave(k - 1, iters, s_tot, s);
-      if (threadIdx.x == 0) s_end = end;
+    if (tid < kWave) {  // wave 0: the same decision in every member
+      if (tid < kAcc) L.tot[tid] = MODE == 1 && tid == 27 ? tot * s2 : tot;
+      __builtin_amdgcn_wave_barrier();
+      gn_decide_wave(j, iters, L.tot, L.s, best_cost, best_count);
     }
     __syncthreads();
-    if (chunk == 0) {
-      gn_store_state(s, g.gst + (int64_t)((k - 1) & 1) * g.nprob + p);
-      if (s_end) gn_outputs(g, s, p);
+    if (L.s.done) break;
+  }
+  if (member == 0) {
+    if (tid < 12 && g.out_pose) g.out_pose[12 * (int64_t)p + tid] = L.s.cur[tid];
+    if (tid == 0) {
+      if (g.out_cost) g.out_cost[p] = best_cost;
+      if (g.out_count) g.out_count[p] = (int64_t)best_count;
     }
-    if (MODE == 1 && g.fuse_mask && s_end) {  // the run ended: mask of this chunk at the final pose
-      GNPoints fp;  // every point of the chunk
-      gn_load_points(c, n, chunk, g.part, fp);
-      long long cnt = 0;
-#pragma unroll
-      for (int t = 0; t < kGNPPT; ++t) {
-        const int64_t i = (int64_t)chunk * kGNChunk + fp.loc[t];
-        if (!fp.use[t]) continue;
-        const bool in = mask_test(d, s.cur, fp.X[t], fp.Y[t], fp.Z[t], fp.u[t], fp.v[t], i);
+  }
+  if (MODE == 1 && g.write_mask) {
+    long long cnt = 0;
+    for (int grp = member; grp < G; grp += T)
+      for (int e = tid; e < S; e += kGNThreads) {
+        const int64_t i = (int64_t)grp * S + e;
+        if (i >= v.n) break;
+        const bool in = mask_test(d, L.s.cur, gmem(v.c.X)[i], gmem(v.c.Y)[i], gmem(v.c.Z)[i], gmem(v.c.u)[i],
+                                  gmem(v.c.v)[i], i);
         if (d.mask) d.mask[i] = in ? 1 : 0;
         cnt += in ? 1 : 0;
       }
-      // one add per workgroup to the query's counter (same-address atomics serialise)
-      __shared__ long long s_cnt[kGNWaves];
-      cnt = wave_sum(cnt);
-      if ((threadIdx.x & (kWave - 1)) == 0) s_cnt[threadIdx.x / kWave] = cnt;
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        long long tot = 0;
-#pragma unroll
-        for (int w = 0; w < kGNWaves; ++w) tot += s_cnt[w];
-        if (tot) atomicAdd((unsigned long long*)&g.bst[q].full_count, (unsigned long long)tot);
-      }
-    }
-  }
-  if (s.done) return;
-  gn_accumulate<MODE, RIG, W>(d, s_rig, s.eval, k, chunk, pt, in_set, s_rows,
-                           const_cast<double*>(gn_part(g, k & 1, p)) + (int64_t)chunk * kAcc);
-}
-
-// Split form, for batches where the redundant reduction of the fused form
-// would read too much: evaluation j (one workgroup per chunk) ...
-// The one-camera refinement evaluation is held to 96 VGPRs, five waves per
-// SIMD (16 registers spill): its workgroups wait mostly on the in-set's
-// dependent loads, and the batch's refinement takes 4 % less time.
-template <int MODE, bool RIG, bool W>
-__global__ __launch_bounds__(kGNThreads)
-__attribute__((amdgpu_waves_per_eu((MODE == 1 && !RIG) ? 5 : 1, (MODE == 1 && !RIG) ? 5 : 8))) void gn_eval_kernel(GNArgs g, int j) {
-  const int p = blockIdx.y;
-  const int chunk = blockIdx.x;
-  const int q = gn_query<MODE>(g, p);
-  if (!gn_live<MODE>(g, p, q)) return;
-  const QueryDesc& d = g.qd[q];
-  const CorrF32 c = MODE == 0 ? d.S : d.full;
-  const int64_t n = MODE == 0 ? d.m : d.n;
-  const int C = chunks_for(n);
-  if (chunk >= C) return;
-  const GNState* st = j > 0 ? g.gst + (int64_t)((j - 1) & 1) * g.nprob + p : nullptr;
-  if (st && st->done) return;
-  uint8_t* in_set = MODE == 1 ? g.in_set_all + d.in_set_off : nullptr;
-  GNPoints pt;
-  if (MODE == 1 && j > 0) gn_load_points_inset(c, n, chunk, in_set, g.part, pt);
-  else gn_load_points(c, n, chunk, g.part, pt);
-  __shared__ double s_rig[RIG ? kMaxCams * 16 : 1];
-  if (RIG && d.ncam > 0)
-    for (int e = threadIdx.x; e < 16 * d.ncam; e += kGNThreads) s_rig[e] = d.rig[e];
-  __shared__ double s_eval[12];
-  __shared__ double s_rows[kGNWaves][kAcc];
-  const double* start = st ? nullptr : gn_start<MODE>(g, p, q);
-  if (threadIdx.x < 12) s_eval[threadIdx.x] = st ? st->eval[threadIdx.x] : start[threadIdx.x];
-  __syncthreads();
-  gn_accumulate<MODE, RIG, W>(d, s_rig, s_eval, j, chunk, pt, in_set, s_rows,
-                           const_cast<double*>(gn_part(g, j & 1, p)) + (int64_t)chunk * kAcc);
-}
-
-// Split form of the local optimisation, evaluation j, for problems that
-// start from selected candidates: one workgroup per (chunk, query) loads the
-// chunk's points once and evaluates every live problem of the query in slot
-// order (up to lo_top_k poses on the same points).  Each problem's
-// accumulation is gn_accumulate with the same thread-to-point map, so the
-// partial sums are those of gn_eval_kernel bit for bit.
-// The unweighted one-camera variant is held to 128 VGPRs (four waves per SIMD
-// instead of three; 20 bytes per lane spill): 4 % faster on the 256-query
-// batch.
-template <bool RIG, bool W>
-__global__ __launch_bounds__(kGNThreads)
-__attribute__((amdgpu_waves_per_eu((!RIG && !W) ? 4 : 1, (!RIG && !W) ? 4 : 8))) void gn_eval_lo_multi_kernel(
-    GNArgs g, int j) {
-  const int q = blockIdx.y;
-  const int chunk = blockIdx.x;
-  const int ns = g.n_sel[q];
-  if (ns <= 0) return;
-  const QueryDesc& d = g.qd[q];
-  const int64_t n = d.m;
-  const int C = chunks_for(n);
-  if (chunk >= C) return;
-  // the query's live problems, their flags read together (lane s: slot s);
-  // once every run has ended the workgroup exits before loading any point
-  // (most runs end within a few iterations)
-  const GNState* st0 = j > 0 ? g.gst + (int64_t)((j - 1) & 1) * g.nprob + q * g.kmax : nullptr;
-  const int lane = threadIdx.x & (kWave - 1);
-  uint64_t live = ns >= kWave ? ~0ull : (1ull << ns) - 1ull;
-  if (st0) live = __ballot(lane < ns && !st0[lane].done);
-  if (!live) return;
-  GNPoints pt;
-  gn_load_points(d.S, n, chunk, g.part, pt);
-  __shared__ double s_rig[RIG ? kMaxCams * 16 : 1];
-  if (RIG && d.ncam > 0)
-    for (int e = threadIdx.x; e < 16 * d.ncam; e += kGNThreads) s_rig[e] = d.rig[e];
-  __shared__ double s_eval[12];
-  __shared__ double s_rows[kGNWaves][kAcc];
-  for (; live; live &= live - 1) {
-    const int slot = __builtin_ctzll(live);
-    const int p = q * g.kmax + slot;
-    const GNState* st = st0 ? st0 + slot : nullptr;
-    const double* start = st ? nullptr : gn_start<0>(g, p, q);
-    // every thread has left the previous problem's accumulation (its last
-    // barrier) before s_eval is rewritten
-    if (threadIdx.x < 12) s_eval[threadIdx.x] = st ? st->eval[threadIdx.x] : start[threadIdx.x];
+    // one add per member to the query's counter (same-address atomics serialise)
+    __shared__ long long s_cnt[kGNWaves];
+    cnt = wave_sum(cnt);
+    if ((tid & (kWave - 1)) == 0) s_cnt[tid / kWave] = cnt;
     __syncthreads();
-    gn_accumulate<0, RIG, W>(d, s_rig, s_eval, j, chunk, pt, nullptr, s_rows,
-                          const_cast<double*>(gn_part(g, j & 1, p)) + (int64_t)chunk * kAcc);
-  }
-}
-
-// ... then decision j (one workgroup per problem), with the same reduction
-// order and decision as the fused form, so both give identical results.
-template <int MODE>
-__global__ __launch_bounds__(kGNThreads) void gn_decide_kernel(GNArgs g, int j) {
-  const int p = blockIdx.x;
-  GNStateRegs sr;
-  gn_state_issue(j > 0 ? g.gst + (int64_t)((j - 1) & 1) * g.nprob + p : nullptr, sr);
-  GNPart pr;
-  gn_part_issue(gn_part(g, j & 1, p), g.cmax, pr);
-  const int q = gn_query<MODE>(g, p);
-  if (!gn_live<MODE>(g, p, q)) return;
-  // a run that has ended: its state carried to the slot the next launch
-  // reads, without waiting for the partial sums
-  if (j > 0 && sr.done) {
-    gn_store_state_regs(sr, g.gst + (int64_t)(j & 1) * g.nprob + p);
-    return;
-  }
-  const QueryDesc& d = g.qd[q];
-  const int64_t n = MODE == 0 ? d.m : d.n;
-  const int iters = MODE == 0 ? d.lo_iters : d.final_iters;
-  const int C = chunks_for(n);
-  __shared__ double s_grp[8][kAcc];
-  __shared__ double s_tot[kAcc];
-  __shared__ GNShared s;
-  __shared__ int s_end;
-  gn_part_sum(gn_part(g, j & 1, p), C, pr, s_grp, s_tot);
-  gn_state_to_lds(s, sr, j > 0, j > 0 ? nullptr : gn_start<MODE>(g, p, q));
-  __syncthreads();
-  if (threadIdx.x < kWave) {
-    const bool end = gn_decide_wave(j, iters, s_tot, s);
-    if (threadIdx.x == 0) s_end = end;
-  }
-  __syncthreads();
-  gn_store_state(s, g.gst + (int64_t)(j & 1) * g.nprob + p);
-  if (s_end) gn_outputs(g, s, p);
-}
-
-static void split_scratch(void* scratch, int nprob, GNState** st, double** part) {
-  *st = reinterpret_cast<GNState*>(scratch);
-  *part = reinterpret_cast<double*>(reinterpret_cast<char*>(scratch) +
-                                    (((size_t)2 * nprob * sizeof(GNState) + 255) & ~size_t(255)));
-}
-
-// The fused form reads every problem's partial sums once per workgroup:
-// nprob * C^2 * 232 bytes per launch.  Above 32 MiB the split form (one more
-// launch per iteration, partials read once) is faster.
-static bool use_fused(int gn_mode, int nprob, int chunks_max) {
-  if (gn_mode == 1) return true;
-  if (gn_mode == 2) return false;
-  return (double)nprob * chunks_max * chunks_max * kAcc * sizeof(double) <= 32.0 * 1024 * 1024;
-}
-
-template <int MODE, bool RIG, bool W>
-static void launch_gn(const GNArgs& g, int iters_max, bool fused, hipStream_t s) {
-  const dim3 grid(g.cmax, g.nprob);
-  if (fused) {
-    for (int k = 0; k <= iters_max + 1; ++k)
-      hipLaunchKernelGGL((gn_fused_kernel<MODE, RIG, W>), grid, dim3(kGNThreads), 0, s, g, k);
-  } else {
-    // local optimisation from selected candidates: one workgroup per chunk and
-    // query evaluates all of the query's problems (points loaded once)
-    const bool multi = MODE == 0 && !g.start_direct && g.kmax > 1;
-    const dim3 grid_multi(g.cmax, g.nprob / (g.kmax > 0 ? g.kmax : 1));
-    for (int j = 0; j <= iters_max; ++j) {
-      if (multi)
-        hipLaunchKernelGGL((gn_eval_lo_multi_kernel<RIG, W>), grid_multi, dim3(kGNThreads), 0, s, g, j);
-      else
-        hipLaunchKernelGGL((gn_eval_kernel<MODE, RIG, W>), grid, dim3(kGNThreads), 0, s, g, j);
-      hipLaunchKernelGGL((gn_decide_kernel<MODE>), dim3(g.nprob), dim3(kGNThreads), 0, s, g, j);
+    if (tid == 0) {
+      long long sum = 0;
+#pragma unroll
+      for (int w = 0; w < kGNWaves; ++w) sum += s_cnt[w];
+      if (sum) atomicAdd((unsigned long long*)&g.bst[q].full_count, (unsigned long long)sum);
     }
   }
 }
 
-hipError_t launch_lo(const QueryDesc* qd, CandBuf cb, const int32_t* sel, const int32_t* n_sel,
-                     const double* start_direct, int nprob, int kmax, int chunks_max, int iters_max, void* scratch,
-                     double* out_pose, double* out_cost, int64_t* out_count, bool any_rig, bool any_weighted,
-                     int gn_mode, hipStream_t s) {
-  if (nprob <= 0) return hipSuccess;
+template <int MODE>
+static void launch_team(const GNArgs& g, const GNLaunch& t, bool any_rig, hipStream_t s) {
+  const dim3 grid(t.members), block(kGNThreads);
+  const size_t lds = t.resident ? sizeof(GNResident) : 0;
+  if (any_rig) {
+    if (t.resident) hipLaunchKernelGGL((gn_team_kernel<MODE, true, true>), grid, block, lds, s, g);
+    else hipLaunchKernelGGL((gn_team_kernel<MODE, true, false>), grid, block, lds, s, g);
+  } else {
+    if (t.resident) hipLaunchKernelGGL((gn_team_kernel<MODE, false, true>), grid, block, lds, s, g);
+    else hipLaunchKernelGGL((gn_team_kernel<MODE, false, false>), grid, block, lds, s, g);
+  }
+}
+
+hipError_t launch_lo(const QueryDesc* qd, const BestState* st, CandBuf cb, const int32_t* sel, const int32_t* n_sel,
+                     const double* start_direct, int nq, int kmax, const GNLaunch& t, double* out_pose,
+                     double* out_cost, int64_t* out_count, bool any_rig, hipStream_t s) {
+  if (t.members <= 0) return hipSuccess;
   GNArgs g{};
-  split_scratch(scratch, nprob, &g.gst, &g.part);
   g.qd = qd;
   g.cb = cb;
   g.sel = sel;
   g.n_sel = n_sel;
   g.start_direct = start_direct;
+  g.bst = const_cast<BestState*>(st);
+  g.box = t.box;
   g.out_pose = out_pose;
   g.out_cost = out_cost;
   g.out_count = out_count;
+  g.ticket = t.teams ? t.ticket : nullptr;
+  g.nq = nq;
   g.kmax = kmax;
-  g.cmax = chunks_max;
-  g.nprob = nprob;
-  const bool fused = use_fused(gn_mode, nprob, chunks_max);
-  // queries without confidences take the unweighted accumulation (same bits)
-  if (any_rig) {
-    if (any_weighted) launch_gn<0, true, true>(g, iters_max, fused, s);
-    else launch_gn<0, true, false>(g, iters_max, fused, s);
-  } else {
-    if (any_weighted) launch_gn<0, false, true>(g, iters_max, fused, s);
-    else launch_gn<0, false, false>(g, iters_max, fused, s);
-  }
+  g.box_groups = t.box_groups;
+  g.team_direct = t.team_direct;
+  g.polls = t.polls;
+  launch_team<0>(g, t, any_rig, s);
   return hipGetLastError();
 }
 
-hipError_t launch_refine(const QueryDesc* qd, BestState* bst, const double* start_direct, int nq, int chunks_max,
-                         int iters_max, uint8_t* in_set, void* scratch, double* out_pose, double* out_cost,
-                         bool any_rig, int gn_mode, bool fuse_mask, bool* mask_done, hipStream_t s) {
-  if (mask_done) *mask_done = false;
-  if (nq <= 0) return hipSuccess;
+hipError_t launch_refine(const QueryDesc* qd, BestState* bst, const double* start_direct, int nq, const GNLaunch& t,
+                         uint8_t* in_set, double* out_pose, double* out_cost, bool any_rig, bool write_mask,
+                         hipStream_t s) {
+  if (t.members <= 0) return hipSuccess;
   GNArgs g{};
-  split_scratch(scratch, nq, &g.gst, &g.part);
   g.qd = qd;
   g.bst = bst;
   g.start_direct = start_direct;
+  g.box = t.box;
   g.in_set_all = in_set;
   g.out_pose = out_pose;
   g.out_cost = out_cost;
+  g.ticket = t.teams ? t.ticket : nullptr;
+  g.nq = nq;
   g.kmax = 1;
-  g.cmax = chunks_max;
-  g.nprob = nq;
-  const bool fused = use_fused(gn_mode, nq, chunks_max);
-  g.fuse_mask = fused && fuse_mask && !start_direct ? 1 : 0;
-  if (mask_done) *mask_done = g.fuse_mask != 0;
-  if (any_rig) launch_gn<1, true, true>(g, iters_max, fused, s);
-  else launch_gn<1, false, true>(g, iters_max, fused, s);
-  return hipGetLastError();
-}
-
-// Inlier mask over all points of every query that just finished, at its final
-// pose (float64), and its count; a query without a pose gets a zero mask.
-__global__ __launch_bounds__(256) void mask_kernel(const QueryDesc* __restrict__ qd, BestState* __restrict__ st,
-                                                   const double* __restrict__ fin_pose, int all) {
-  const int q = blockIdx.y;
-  if (!all && st[q].finished != 1) return;
-  const QueryDesc& d = qd[q];
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if ((int64_t)blockIdx.x * blockDim.x >= d.n) return;
-  const bool have = all || st[q].have != 0;
-  long long in = 0;
-  if (i < d.n && have)
-    in = mask_test(d, fin_pose + 12 * (int64_t)q, gmem(d.full.X)[i], gmem(d.full.Y)[i], gmem(d.full.Z)[i],
-                   gmem(d.full.u)[i], gmem(d.full.v)[i], i) ? 1 : 0;
-  if (i < d.n && d.mask) d.mask[i] = (uint8_t)in;
-  // one add per workgroup to the query's counter (same-address atomics serialise)
-  __shared__ long long s_cnt[256 / kWave];
-  const long long tot = wave_sum(in);
-  if ((threadIdx.x & (kWave - 1)) == 0) s_cnt[threadIdx.x / kWave] = tot;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    long long sum = 0;
-#pragma unroll
-    for (int w = 0; w < 256 / kWave; ++w) sum += s_cnt[w];
-    if (sum) atomicAdd((unsigned long long*)&st[q].full_count, (unsigned long long)sum);
-  }
-}
-
-hipError_t launch_mask(const QueryDesc* qd, BestState* st, const double* fin_pose, int nq, int64_t max_n, int all,
-                       hipStream_t s) {
-  if (nq <= 0 || max_n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(mask_kernel, dim3((unsigned)((max_n + 255) / 256), nq), dim3(256), 0, s, qd, st, fin_pose, all);
+  g.box_groups = t.box_groups;
+  g.team_direct = t.team_direct;
+  g.write_mask = write_mask ? 1 : 0;
+  g.polls = t.polls;
+  launch_team<1>(g, t, any_rig, s);
   return hipGetLastError();
 }
 

@@ -89,14 +89,29 @@ __device__ inline int64_t round_samples(const QueryDesc& d, const BestState& b) 
 // into sixteen partial sums, u = 0..15, so that sixteen loads are in flight;
 // the partials, the waves and the workgroup are combined in a fixed order).
 // With `begin`, also set up the first round (samples, candidate counter).
+// The workgroups of grid rows 1 and up clear the query's mailboxes.
 constexpr int kInitThreads = 1024;
+constexpr int kClearRows = 8;  // at most; a row clears 16 words per thread and turn
+
+__device__ inline void clear_words(uint64_t* p, int64_t n, int row, int rows) {
+  for (int64_t i = (int64_t)row * kInitThreads + threadIdx.x; i < n; i += (int64_t)rows * kInitThreads) p[i] = 0;
+}
 
 __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryDesc* __restrict__ qd,
                                                                     BestState* __restrict__ st,
-                                                                    int32_t* __restrict__ n_cand, int begin) {
+                                                                    int32_t* __restrict__ n_cand, int begin,
+                                                                    GNClear clear) {
   const int q = blockIdx.x;
   QueryDesc& d = qd[q];
+  if (q == 0 && blockIdx.y == 0 && threadIdx.x < 2) clear.tickets[threadIdx.x] = 0;
   if (!d.fresh) return;
+  if (blockIdx.y > 0) {
+    const int row = blockIdx.y - 1, rows = gridDim.y - 1;
+    if (clear.lo && (clear.all || d.lo_team > 1)) clear_words(clear.lo + q * clear.lo_words, clear.lo_words, row, rows);
+    if (clear.fin && (clear.all || d.fin_team > 1))
+      clear_words(clear.fin + q * clear.fin_words, clear.fin_words, row, rows);
+    return;
+  }
   double p[16];
 #pragma unroll
   for (int u = 0; u < 16; ++u) p[u] = 0.0;
@@ -156,9 +171,13 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryDesc* _
   }
 }
 
-hipError_t launch_init_queries(QueryDesc* qd, BestState* st, int32_t* n_cand, int nq, bool begin, hipStream_t s) {
+hipError_t launch_init_queries(QueryDesc* qd, BestState* st, int32_t* n_cand, int nq, bool begin,
+                               const GNClear& clear, hipStream_t s) {
   if (nq <= 0) return hipSuccess;
-  hipLaunchKernelGGL(init_queries_kernel, dim3(nq), dim3(kInitThreads), 0, s, qd, st, n_cand, begin ? 1 : 0);
+  const int64_t words = (clear.lo ? clear.lo_words : 0) + (clear.fin ? clear.fin_words : 0);
+  const int64_t rows = (words + 16 * kInitThreads - 1) / (16 * kInitThreads);
+  hipLaunchKernelGGL(init_queries_kernel, dim3(nq, 1 + (unsigned)(rows < kClearRows ? rows : kClearRows)),
+                     dim3(kInitThreads), 0, s, qd, st, n_cand, begin ? 1 : 0, clear);
   return hipGetLastError();
 }
 

@@ -124,7 +124,8 @@ struct imloc_ctx {
   size_t next_event = 0;
   ScoreTune tune{0, 0, 2048};  // ct == 0, blocks == 0: the tile and the grid are picked per round (round_tune)
   int cus = 256;
-  int gn_mode = 0;  // Gauss-Newton launch form: 0 by size, 1 fused, 2 split
+  int gn_mode = 0;  // Gauss-Newton teams: 0 by size, 1 the widest, 2 one workgroup per problem
+  int gn_polls = kGNPolls;
   // hipGraph replay of the fixed-sample pipeline
   bool graphs = false;
   hipStream_t gstream = nullptr;
@@ -289,8 +290,8 @@ QPlan plan_query(int64_t n, const imloc_ransac_params* p, int ncam = 0) {
 
 // Device buffers of one batch, carved from the workspace.
 struct Engine {
-  int nq = 0, kmax = 1, chunks_lo = 1, chunks_fin = 1, lo_iters = 0, fin_iters = 0;
-  int64_t max_batch = 1, max_n = 0, slots = 0, max_rounds = 0;
+  int nq = 0, kmax = 1, groups_lo = 1, groups_fin = 1;  // groups: of the largest problem
+  int64_t max_batch = 1, slots = 0, max_rounds = 0;
   bool all_fixed = true;
   bool any_rig = false;
   bool any_single = false;  // some query has one camera (the P3P sampler has work)
@@ -310,8 +311,9 @@ struct Engine {
   double* fin_pose;
   double* fin_cost;
   uint8_t* in_set;
-  void* gn_lo;
-  void* gn_fin;
+  uint64_t* gn_lo;   // Gauss-Newton mailboxes
+  uint64_t* gn_fin;
+  int32_t* tickets;  // [2]: local optimisation, final refinement
   float* subset;
   SmallVec<int64_t, 4> cand_off, in_set_off, subset_off, proj_off, rig_off;
 };
@@ -339,12 +341,9 @@ void plan_engine(Engine& e, int nq, const QPlan* pl, const imloc_ransac_params* 
     e.subset_off[q] = sub;
     if (pl[q].subset) sub += 6 * pl[q].m;
     e.kmax = std::max(e.kmax, pl[q].k);
-    e.chunks_lo = std::max(e.chunks_lo, gn_chunks(pl[q].m));
-    e.chunks_fin = std::max(e.chunks_fin, gn_chunks(pl[q].n));
-    e.lo_iters = std::max(e.lo_iters, (int)pp[q]->lo_iters);
-    e.fin_iters = std::max(e.fin_iters, (int)pp[q]->final_iters);
+    e.groups_lo = std::max(e.groups_lo, gn_most_groups(pl[q].m));
+    e.groups_fin = std::max(e.groups_fin, gn_most_groups(pl[q].n));
     e.max_batch = std::max(e.max_batch, pl[q].batch);
-    e.max_n = std::max(e.max_n, pl[q].n);
     e.max_rounds = std::max(e.max_rounds, (pl[q].total + pl[q].batch - 1) / pl[q].batch);
     if (pp[q]->fixed_samples <= 0) e.all_fixed = false;
   }
@@ -386,9 +385,66 @@ void carve_engine(Arena& a, Engine& e) {
   e.lo_cost = a.take<double>((size_t)nq * e.kmax);
   e.lo_count = a.take<int64_t>((size_t)nq * e.kmax);
   e.in_set = a.take<uint8_t>((size_t)std::max<int64_t>(e.in_set_off.back(), 1));
-  e.gn_lo = a.take<char>(gn_scratch_bytes(nq * e.kmax, e.chunks_lo));
-  e.gn_fin = a.take<char>(gn_scratch_bytes(nq, e.chunks_fin));
+  e.tickets = a.take<int32_t>(2);
+  e.gn_lo = a.take<uint64_t>(gn_scratch_bytes(nq * e.kmax, e.groups_lo) / sizeof(uint64_t));
+  e.gn_fin = a.take<uint64_t>(gn_scratch_bytes(nq, e.groups_fin) / sizeof(uint64_t));
   e.subset = a.take<float>((size_t)std::max<int64_t>(e.subset_off.back(), 1));
+}
+
+// The two Gauss-Newton launches of a table of queries: the workgroup slots of
+// the chip are shared out over the queries' problems (d.k local optimisations
+// and one refinement each), and every descriptor gets its team sizes and
+// first tickets.  An unused slot of a server has k = 0 and no workgroup.
+struct GNTeams {
+  GNLaunch lo{}, fin{};
+};
+int team_slots(const imloc_ctx* c) { return 2 * c->cus; }  // two workgroups with their points in LDS fit a compute unit
+GNTeams plan_teams(const imloc_ctx* c, const Engine& e, QueryDesc* htab, int nq) {
+  const int slots = team_slots(c);
+  int64_t tot_lo = 0, tot_fin = 0;
+  for (int q = 0; q < nq; ++q) {
+    if (htab[q].k <= 0) continue;
+    tot_lo += (int64_t)htab[q].k * gn_groups(htab[q].m);
+    tot_fin += gn_groups(htab[q].n);
+  }
+  GNTeams t;
+  int64_t lo0 = 0, fin0 = 0;
+  for (int q = 0; q < nq; ++q) {
+    QueryDesc& d = htab[q];
+    d.lo_team = gn_team(gn_groups(d.m), tot_lo, slots, kLoGroupsPerMember, c->gn_mode);
+    d.fin_team = gn_team(gn_groups(d.n), tot_fin, slots, kFinGroupsPerMember, c->gn_mode);
+    d.lo_team0 = (int32_t)lo0;
+    d.fin_team0 = (int32_t)fin0;
+    if (d.k <= 0) continue;
+    lo0 += (int64_t)d.k * d.lo_team;
+    fin0 += d.fin_team;
+    t.lo.teams |= d.lo_team > 1;
+    t.fin.teams |= d.fin_team > 1;
+  }
+  t.lo.box = e.gn_lo;
+  t.lo.box_groups = e.groups_lo;
+  t.lo.ticket = e.tickets;
+  t.lo.members = (int)lo0;
+  t.fin.box = e.gn_fin;
+  t.fin.box_groups = e.groups_fin;
+  t.fin.ticket = e.tickets + 1;
+  t.fin.members = (int)fin0;
+  t.lo.polls = t.fin.polls = c->gn_polls;
+  t.lo.resident = lo0 <= slots;
+  t.fin.resident = true;  // one group per member (but for the largest problems)
+  return t;
+}
+
+// The mailboxes an initialisation clears: those of launches with teams.
+GNClear team_clear(const Engine& e, const GNTeams& t, bool all) {
+  GNClear c{};
+  c.tickets = e.tickets;
+  c.all = all;
+  if (all || t.lo.teams) c.lo = e.gn_lo;
+  if (all || t.fin.teams) c.fin = e.gn_fin;
+  c.lo_words = e.kmax * gn_box_words(e.groups_lo);
+  c.fin_words = gn_box_words(e.groups_fin);
+  return c;
 }
 
 // Host staging of the context: at least `bytes` of it, else an error naming
@@ -549,10 +605,10 @@ QueryDesc make_desc(const imloc_corr* pts, int64_t n, const imloc_camera* K, con
   d.min_iters = p->min_iters;
   d.fixed = p->fixed_samples > 0 ? 1 : 0;
   d.exhaustive = p->exhaustive ? 1 : 0;
-  d.precision = p->precision;
-  d.k = pl.k;
-  d.lo_iters = p->lo_iters;
-  d.final_iters = p->final_iters;
+  d.precision = (uint8_t)p->precision;
+  d.k = (uint8_t)pl.k;
+  d.lo_iters = (int16_t)p->lo_iters;  // at most 1000
+  d.final_iters = (int16_t)p->final_iters;
   d.cand_off = e.cand_off[q];
   d.cap = pl.cap;
   d.in_set_off = e.in_set_off[q];
@@ -646,10 +702,7 @@ int run_batch(imloc_ctx* ctx, int nq, const imloc_corr* pts, const int64_t* n, c
   for (int q = 0; q < nq; ++q)
     if (pl[q].subset) max_m_sub = std::max(max_m_sub, pl[q].m);
 
-  // a query with confidences needs the weighted local optimisation (the
-  // unweighted one gives the same bits when every weight is 1)
-  bool any_w = false;
-  for (int q = 0; q < nq; ++q) any_w = any_w || (n[q] > 0 && pts[q].w != nullptr);
+  const GNTeams teams = plan_teams(ctx, e, htab, nq);
   Timer tm(ctx);
   int rounds = 0;
   EstList est(nq);
@@ -663,13 +716,14 @@ int run_batch(imloc_ctx* ctx, int nq, const imloc_corr* pts, const int64_t* n, c
     HIP_TRY(ctx, hipMemcpyAsync(e.qd, htab, tab, hipMemcpyHostToDevice, st_));
     if (rigb) HIP_TRY(ctx, hipMemcpyAsync(e.rig, hrig, rigb, hipMemcpyHostToDevice, st_));
     HIP_TRY(ctx, launch_gather_subsets(e.qd, nq, max_m_sub, st_));
-    HIP_TRY(ctx, launch_init_queries(e.qd, e.st, e.cb.n, nq, true, st_));  // and the first round's setup
+    HIP_TRY(ctx, launch_init_queries(e.qd, e.st, e.cb.n, nq, true, team_clear(e, teams, false),
+                                     st_));  // and the first round's setup
     rounds = 0;
     for (int64_t r = 0; r < e.max_rounds; ++r) {
       hipEvent_t e0 = tm.begin();
       if (e.any_single) HIP_TRY(ctx, launch_sample_p3p(e.qd, e.st, e.cb, nq, e.max_batch, nullptr, st_));
       if (e.any_rig) HIP_TRY(ctx, launch_sample_gp3p(e.qd, e.st, e.cb, nq, e.max_batch, nullptr, st_));
-      HIP_TRY(ctx, launch_worklist(e.qd, e.cb, nq, tune, e.item_off, st_));
+      HIP_TRY(ctx, launch_worklist(e.qd, e.cb, nq, tune, e.item_off, e.tickets, st_));
       tm.end(kStSample, e0);
       hipEvent_t e1 = tm.begin();  // the scoring span holds the scoring kernel alone
       HIP_TRY(ctx, launch_score(e.qd, e.cb, e.st, nq, e.item_off, tune, 0, st_));
@@ -678,8 +732,8 @@ int run_batch(imloc_ctx* ctx, int nq, const imloc_corr* pts, const int64_t* n, c
       HIP_TRY(ctx, launch_select(e.qd, e.st, e.cb, nq, e.kmax, e.max_cap, e.sel_part, e.sel, e.n_sel, st_));
       tm.end(kStSelect, e2);
       hipEvent_t e3 = tm.begin();
-      HIP_TRY(ctx, launch_lo(e.qd, e.cb, e.sel, e.n_sel, nullptr, nq * e.kmax, e.kmax, e.chunks_lo, e.lo_iters,
-                             e.gn_lo, e.lo_pose, e.lo_cost, e.lo_count, e.any_rig, any_w, ctx->gn_mode, st_));
+      HIP_TRY(ctx, launch_lo(e.qd, e.st, e.cb, e.sel, e.n_sel, nullptr, nq, e.kmax, teams.lo, e.lo_pose, e.lo_cost,
+                             e.lo_count, e.any_rig, st_));
       HIP_TRY(ctx, launch_round_end(e.qd, e.cb, e.sel, e.n_sel, e.lo_pose, e.lo_cost, e.lo_count, nq, e.kmax, e.st,
                                     e.active_count, true, st_));
       tm.end(kStLO, e3);
@@ -692,10 +746,8 @@ int run_batch(imloc_ctx* ctx, int nq, const imloc_corr* pts, const int64_t* n, c
       }
     }
     hipEvent_t e4 = tm.begin();
-    bool mask_done = false;  // the fused final refinement writes the masks itself
-    HIP_TRY(ctx, launch_refine(e.qd, e.st, nullptr, nq, e.chunks_fin, e.fin_iters, e.in_set, e.gn_fin, e.fin_pose,
-                               e.fin_cost, e.any_rig, ctx->gn_mode, true, &mask_done, st_));
-    if (!mask_done) HIP_TRY(ctx, launch_mask(e.qd, e.st, e.fin_pose, nq, e.max_n, 0, st_));
+    HIP_TRY(ctx, launch_refine(e.qd, e.st, nullptr, nq, teams.fin, e.in_set, e.fin_pose, e.fin_cost, e.any_rig, true,
+                               st_));
     tm.end(kStRefine, e4);
     tm.total_end(ev_total);
     HIP_TRY(ctx, hipMemcpyAsync(hst, e.st, result_bytes(nq), hipMemcpyDeviceToHost, st_));
@@ -707,7 +759,7 @@ int run_batch(imloc_ctx* ctx, int nq, const imloc_corr* pts, const int64_t* n, c
     std::string key;
     char buf[160];
     snprintf(buf, sizeof(buf), "%d|%p|%p|%d|%d|%d|%d|%d|%d|", nq, (void*)ws.base, (void*)ctx->pinned, tune.ct,
-             tune.blocks, tune.pts, e.lo_iters, e.fin_iters, ctx->gn_mode);
+             tune.blocks, tune.pts, teams.lo.members, teams.fin.members, ctx->gn_polls);
     key += buf;
     for (int q = 0; q < nq; ++q) {
       snprintf(buf, sizeof(buf), "%lld,%lld,%d,%lld,%lld,%d,%d;", (long long)pl[q].n, (long long)pl[q].m,
@@ -817,21 +869,22 @@ void stage_setup(StageQuery& sq, int64_t n, int64_t cap, double tau, int precisi
   const imloc_ransac_params* pp = &sq.p;
   plan_engine(sq.e, 1, &sq.pl, &pp);
   sq.e.kmax = 1;
-  sq.e.chunks_lo = gn_chunks(n);
+  sq.e.groups_lo = gn_most_groups(n);
   (void)nprob_lo;
 }
 
 size_t stage_bytes(StageQuery& sq, int nprob_lo) {
   Arena a{nullptr, (size_t)-1};
   carve_engine(a, sq.e);
-  a.take<char>(gn_scratch_bytes(nprob_lo, sq.e.chunks_lo));
+  a.take<char>(gn_scratch_bytes(nprob_lo, sq.e.groups_lo));
   return a.off + 256;
 }
 
 // Upload the one-query table (and optionally an initial state) and return the
 // device pointers.
 int stage_upload(imloc_ctx* ctx, StageQuery& sq, const imloc_corr* pts, int64_t n, const imloc_camera* K,
-                 int64_t B, int64_t drawn, uint8_t* mask, const RigHost* rig = nullptr) {
+                 int64_t B, int64_t drawn, uint8_t* mask, const RigHost* rig = nullptr,
+                 const GNClear* clear = nullptr) {
   const size_t rig_at = 256 * ((sizeof(QueryDesc) + sizeof(BestState) + 512 + 255) / 256);
   int rc = staging_check(ctx, rig_at + (size_t)sq.e.rig_doubles * sizeof(double));
   if (rc) return rc;
@@ -847,7 +900,9 @@ int stage_upload(imloc_ctx* ctx, StageQuery& sq, const imloc_corr* pts, int64_t 
     HIP_TRY(ctx, hipMemcpyAsync(sq.e.rig, hrig, (size_t)sq.e.rig_doubles * sizeof(double), hipMemcpyHostToDevice,
                                 ctx->stream));
   }
-  HIP_TRY(ctx, launch_init_queries(sq.e.qd, sq.e.st, sq.e.cb.n, 1, false, ctx->stream));
+  GNClear none{};
+  none.tickets = sq.e.tickets;
+  HIP_TRY(ctx, launch_init_queries(sq.e.qd, sq.e.st, sq.e.cb.n, 1, false, clear ? *clear : none, ctx->stream));
   if (drawn) {
     BestState* hb = reinterpret_cast<BestState*>(ctx->pinned + 256 * ((sizeof(QueryDesc) + 255) / 256));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
@@ -979,9 +1034,17 @@ int imloc_set_score_tuning(imloc_ctx* c, int32_t candidates_per_item, int32_t wo
   return IMLOC_OK;
 }
 
+// Polls of a wait within a Gauss-Newton team before a member works alone
+// (not part of the interface: the tests set 0, so that every member does).
+int gn_set_team_polls(imloc_ctx* c, int32_t polls) {
+  if (!c || polls < 0) return IMLOC_EINVAL;
+  c->gn_polls = polls;
+  return IMLOC_OK;
+}
+
 int imloc_set_gn_mode(imloc_ctx* c, int32_t mode) {
   if (!c) return IMLOC_EINVAL;
-  if (mode < 0 || mode > 2) return set_err(c, IMLOC_EINVAL, "Gauss-Newton launch form must be 0, 1 or 2");
+  if (mode < 0 || mode > 2) return set_err(c, IMLOC_EINVAL, "Gauss-Newton team mode must be 0, 1 or 2");
   c->gn_mode = mode;
   return IMLOC_OK;
 }
@@ -1362,7 +1425,7 @@ int imloc_rig_score(imloc_ctx* ctx, const imloc_corr* pts, int64_t n, const imlo
   HIP_TRY(ctx, launch_set_candidates(sq.e.qd, poses, np, sq.e.cb, s));
   const std::pair<int64_t, int64_t> est1{np, est_points(sq.pl)};
   const ScoreTune tune = round_tune(ctx, &est1, 1);
-  HIP_TRY(ctx, launch_worklist(sq.e.qd, sq.e.cb, 1, tune, sq.e.item_off, s));
+  HIP_TRY(ctx, launch_worklist(sq.e.qd, sq.e.cb, 1, tune, sq.e.item_off, sq.e.tickets, s));
   HIP_TRY(ctx, launch_score(sq.e.qd, sq.e.cb, sq.e.st, 1, sq.e.item_off, tune, precision, s));
   HIP_TRY(ctx, launch_candidate_costs(sq.e.qd, sq.e.st, sq.e.cb, np, count, msac, s));
   return IMLOC_OK;
@@ -1406,7 +1469,7 @@ int imloc_score(imloc_ctx* ctx, const imloc_corr* pts, int64_t n, const imloc_ca
   HIP_TRY(ctx, launch_set_candidates(sq.e.qd, poses, np, sq.e.cb, s));
   const std::pair<int64_t, int64_t> est1{np, est_points(sq.pl)};
   const ScoreTune tune = round_tune(ctx, &est1, 1);
-  HIP_TRY(ctx, launch_worklist(sq.e.qd, sq.e.cb, 1, tune, sq.e.item_off, s));
+  HIP_TRY(ctx, launch_worklist(sq.e.qd, sq.e.cb, 1, tune, sq.e.item_off, sq.e.tickets, s));
   HIP_TRY(ctx, launch_score(sq.e.qd, sq.e.cb, sq.e.st, 1, sq.e.item_off, tune, precision, s));
   HIP_TRY(ctx, launch_candidate_costs(sq.e.qd, sq.e.st, sq.e.cb, np, count, msac, s));
   return IMLOC_OK;
@@ -1442,7 +1505,7 @@ int imloc_select_top_k(imloc_ctx* ctx, const imloc_corr* pts, int64_t n, const i
   HIP_TRY(ctx, launch_set_candidates(sq.e.qd, poses, np, sq.e.cb, s));
   const std::pair<int64_t, int64_t> est1{np, est_points(sq.pl)};
   const ScoreTune tune = round_tune(ctx, &est1, 1);
-  HIP_TRY(ctx, launch_worklist(sq.e.qd, sq.e.cb, 1, tune, sq.e.item_off, s));
+  HIP_TRY(ctx, launch_worklist(sq.e.qd, sq.e.cb, 1, tune, sq.e.item_off, sq.e.tickets, s));
   HIP_TRY(ctx, launch_score(sq.e.qd, sq.e.cb, sq.e.st, 1, sq.e.item_off, tune, precision, s));
   HIP_TRY(ctx, launch_select(sq.e.qd, sq.e.st, sq.e.cb, 1, k, std::max<int64_t>(np, 1), sq.e.sel_part, sel, n_sel, s));
   HIP_TRY(ctx, hipStreamSynchronize(s));  // the staging buffer held the gate
@@ -1464,12 +1527,26 @@ int imloc_local_optimize(imloc_ctx* ctx, const imloc_corr* pts, int64_t n, const
   stage_setup(sq, n, 1, tau, 0, iters, 0, 1.0, np);
   Arena a{ctx->ws, ctx->ws_bytes};
   carve_engine(a, sq.e);
-  void* scratch = a.take<char>(gn_scratch_bytes(np, sq.e.chunks_lo));
+  uint64_t* boxes = a.take<uint64_t>(gn_scratch_bytes(np, sq.e.groups_lo) / sizeof(uint64_t));
   if (!a.ok) return set_err(ctx, IMLOC_ENOMEM, "workspace too small: need %zu bytes", a.off);
-  int rc = stage_upload(ctx, sq, pts, n, K, 0, 0, nullptr);
+  GNLaunch t{};
+  t.team_direct = gn_team(gn_groups(n), (int64_t)np * gn_groups(n), team_slots(ctx), kLoGroupsPerMember, ctx->gn_mode);
+  t.teams = t.team_direct > 1;
+  t.members = np * t.team_direct;
+  t.box = boxes;
+  t.box_groups = sq.e.groups_lo;
+  t.ticket = sq.e.tickets;
+  t.polls = ctx->gn_polls;
+  t.resident = t.members <= team_slots(ctx);
+  GNClear clear{};
+  clear.tickets = sq.e.tickets;
+  clear.all = true;
+  clear.lo = t.teams ? boxes : nullptr;
+  clear.lo_words = np * gn_box_words(sq.e.groups_lo);
+  int rc = stage_upload(ctx, sq, pts, n, K, 0, 0, nullptr, nullptr, &clear);
   if (rc) return rc;
-  HIP_TRY(ctx, launch_lo(sq.e.qd, sq.e.cb, nullptr, nullptr, start, np, 1, sq.e.chunks_lo, iters, scratch, out_poses,
-                         cost, count, false, n > 0 && pts->w != nullptr, ctx->gn_mode, ctx->stream));
+  HIP_TRY(ctx, launch_lo(sq.e.qd, sq.e.st, sq.e.cb, nullptr, nullptr, start, 1, 1, t, out_poses, cost, count, false,
+                         ctx->stream));
   return IMLOC_OK;
 }
 
@@ -1487,11 +1564,24 @@ int imloc_refine(imloc_ctx* ctx, const imloc_corr* pts, int64_t n, const imloc_c
   Arena a{ctx->ws, ctx->ws_bytes};
   carve_engine(a, sq.e);
   if (!a.ok) return set_err(ctx, IMLOC_ENOMEM, "workspace too small: need %zu bytes", a.off);
-  int rc = stage_upload(ctx, sq, pts, n, K, 0, 0, mask);
+  GNLaunch t{};
+  t.team_direct = gn_team(gn_groups(n), gn_groups(n), team_slots(ctx), kFinGroupsPerMember, ctx->gn_mode);
+  t.teams = t.team_direct > 1;
+  t.members = t.team_direct;
+  t.box = sq.e.gn_fin;
+  t.box_groups = sq.e.groups_fin;
+  t.ticket = sq.e.tickets + 1;
+  t.polls = ctx->gn_polls;
+  t.resident = t.members <= team_slots(ctx);
+  GNClear clear{};
+  clear.tickets = sq.e.tickets;
+  clear.all = true;
+  clear.fin = t.teams ? sq.e.gn_fin : nullptr;
+  clear.fin_words = gn_box_words(sq.e.groups_fin);
+  int rc = stage_upload(ctx, sq, pts, n, K, 0, 0, mask, nullptr, &clear);
   if (rc) return rc;
-  HIP_TRY(ctx, launch_refine(sq.e.qd, sq.e.st, start, 1, sq.e.chunks_fin, iters, sq.e.in_set, sq.e.gn_fin, out_pose,
-                             cost, false, ctx->gn_mode, false, nullptr, ctx->stream));
-  if (mask) HIP_TRY(ctx, launch_mask(sq.e.qd, sq.e.st, out_pose, 1, n, 1, ctx->stream));
+  HIP_TRY(ctx, launch_refine(sq.e.qd, sq.e.st, start, 1, t, sq.e.in_set, out_pose, cost, false, mask != nullptr,
+                             ctx->stream));
   return IMLOC_OK;
 }
 
@@ -1615,8 +1705,8 @@ bool config_ok(const imloc_server_config* c) {
 void server_engine(Engine& e, const imloc_server_config* c) {
   e.nq = c->max_slots;
   e.kmax = c->max_top_k;
-  e.chunks_lo = gn_chunks(c->max_n);
-  e.chunks_fin = gn_chunks(c->max_n);
+  e.groups_lo = gn_most_groups(c->max_n);
+  e.groups_fin = e.groups_lo;
   e.slots = c->candidate_pool;
   e.proj_floats = 16 * std::max<int64_t>(c->candidate_pool, 1);
   e.rig_doubles = 0;
@@ -1680,8 +1770,10 @@ int imloc_server_create(imloc_ctx* ctx, const imloc_server_config* cfg, imloc_se
   std::memset(htab, 0, tab);
   for (int q = 0; q < cfg->max_slots; ++q) htab[q].fresh = 1;
   hipStream_t s = ctx->stream;
+  GNClear none{};
+  none.tickets = srv->e.tickets;
   if (hipMemcpyAsync(srv->e.qd, htab, tab, hipMemcpyHostToDevice, s) != hipSuccess ||
-      launch_init_queries(srv->e.qd, srv->e.st, srv->e.cb.n, cfg->max_slots, false, s) != hipSuccess ||
+      launch_init_queries(srv->e.qd, srv->e.st, srv->e.cb.n, cfg->max_slots, false, none, s) != hipSuccess ||
       launch_retire(srv->e.st, cfg->max_slots, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
     imloc_server_destroy(srv);
     return set_err(ctx, IMLOC_EHIP, "server initialisation failed");
@@ -1826,27 +1918,21 @@ int imloc_server_step(imloc_server* srv, int64_t* done_tickets, int32_t capacity
     sl.byte_len = bl;
     srv->queue.pop_front();
   }
-  int nq = 0, kmax = 1, chunks_lo = 1, chunks_fin = 1, lo_iters = 0, fin_iters = 0;
-  int64_t max_batch = 1, max_n = 0, max_m_sub = 0;
-  bool any_w = false;  // a resident query with confidences: the weighted local optimisation
+  int nq = 0;
+  bool any_fresh = false;
+  int64_t max_batch = 1, max_m_sub = 0;
   EstList est;
   for (int i = 0; i < S; ++i) {
     const ServerSlot& sl = srv->slots[i];
     if (!sl.used) continue;
-    any_w = any_w || (sl.q.n > 0 && sl.q.pts.w != nullptr);
+    any_fresh = any_fresh || sl.fresh;
     est.push_back({std::min(sl.pl.batch, sl.pl.total), est_points(sl.pl)});
     nq = i + 1;
-    kmax = std::max(kmax, sl.pl.k);
-    chunks_lo = std::max(chunks_lo, gn_chunks(sl.pl.m));
-    chunks_fin = std::max(chunks_fin, gn_chunks(sl.pl.n));
-    lo_iters = std::max(lo_iters, (int)sl.q.p.lo_iters);
-    fin_iters = std::max(fin_iters, (int)sl.q.p.final_iters);
     max_batch = std::max(max_batch, sl.pl.batch);
-    max_n = std::max(max_n, sl.pl.n);
     if (sl.pl.subset && sl.fresh) max_m_sub = std::max(max_m_sub, sl.pl.m);
   }
   if (nq > 0) {
-    kmax = srv->cfg.max_top_k;  // problem index layout of the LO buffers
+    const int kmax = srv->cfg.max_top_k;  // problem index layout of the LO buffers
     const size_t tab = (size_t)nq * sizeof(QueryDesc);
     int rc = staging_check(ctx, 2 * server_half_bytes(S));
     if (rc) return rc;
@@ -1879,23 +1965,25 @@ int imloc_server_step(imloc_server* srv, int64_t* done_tickets, int32_t capacity
     }
     hipSetDevice(ctx->device);
     hipStream_t s = ctx->stream;
+    const GNTeams teams = plan_teams(ctx, e, htab, nq);
+    // a query's teams change from round to round with the queries around it,
+    // so its mailboxes are cleared at its admission whatever its first team
+    GNClear clear = team_clear(e, teams, true);
+    if (!any_fresh) clear.lo = clear.fin = nullptr;
     HIP_TRY(ctx, hipMemcpyAsync(e.qd, htab, tab, hipMemcpyHostToDevice, s));
     HIP_TRY(ctx, launch_gather_subsets(e.qd, nq, max_m_sub, s));
-    HIP_TRY(ctx, launch_init_queries(e.qd, e.st, e.cb.n, nq, false, s));
+    HIP_TRY(ctx, launch_init_queries(e.qd, e.st, e.cb.n, nq, false, clear, s));
     HIP_TRY(ctx, launch_begin_round(e.qd, e.st, e.cb, nq, s));
     HIP_TRY(ctx, launch_sample_p3p(e.qd, e.st, e.cb, nq, max_batch, nullptr, s));
     const ScoreTune tune = round_tune(ctx, est.data(), est.size());
-    HIP_TRY(ctx, launch_worklist(e.qd, e.cb, nq, tune, e.item_off, s));
+    HIP_TRY(ctx, launch_worklist(e.qd, e.cb, nq, tune, e.item_off, e.tickets, s));
     HIP_TRY(ctx, launch_score(e.qd, e.cb, e.st, nq, e.item_off, tune, 0, s));
     HIP_TRY(ctx, launch_select(e.qd, e.st, e.cb, nq, kmax, 4 * max_batch, e.sel_part, e.sel, e.n_sel, s));
-    HIP_TRY(ctx, launch_lo(e.qd, e.cb, e.sel, e.n_sel, nullptr, nq * kmax, kmax, chunks_lo, lo_iters, e.gn_lo,
-                           e.lo_pose, e.lo_cost, e.lo_count, false, any_w, ctx->gn_mode, s));
+    HIP_TRY(ctx, launch_lo(e.qd, e.st, e.cb, e.sel, e.n_sel, nullptr, nq, kmax, teams.lo, e.lo_pose, e.lo_cost,
+                           e.lo_count, false, s));
     HIP_TRY(ctx, launch_round_end(e.qd, e.cb, e.sel, e.n_sel, e.lo_pose, e.lo_cost, e.lo_count, nq, kmax, e.st,
                                   e.active_count, false, s));
-    bool mask_done = false;  // the fused final refinement writes the masks itself
-    HIP_TRY(ctx, launch_refine(e.qd, e.st, nullptr, nq, chunks_fin, fin_iters, e.in_set, e.gn_fin, e.fin_pose,
-                               e.fin_cost, false, ctx->gn_mode, true, &mask_done, s));
-    if (!mask_done) HIP_TRY(ctx, launch_mask(e.qd, e.st, e.fin_pose, nq, max_n, 0, s));
+    HIP_TRY(ctx, launch_refine(e.qd, e.st, nullptr, nq, teams.fin, e.in_set, e.fin_pose, e.fin_cost, false, true, s));
     HIP_TRY(ctx, launch_retire(e.st, nq, s));
     // the results block is laid out for all e.nq slots (the table may be shorter)
     HIP_TRY(ctx, hipMemcpyAsync(half + (size_t)S * sizeof(QueryDesc), e.st, result_bytes(e.nq),

@@ -96,10 +96,13 @@ __device__ inline ChunkRange chunk_range(const QueryDesc& d, int64_t chunk, int 
 
 // Work list: items_q = tiles_q * chunks_q for queries sampling this round;
 // item_off = exclusive prefix, item_off[nq] = total (one workgroup).  Also
-// zeroes the round's selection counters (the selection follows the scoring).
+// zeroes the round's selection counters (the selection follows the scoring)
+// and the tickets of its Gauss-Newton launches.
 __global__ __launch_bounds__(1024) void worklist_kernel(const QueryDesc* __restrict__ qd,
                                                         const int32_t* __restrict__ n_cand, int nq, int ct, int pts,
-                                                        int64_t* __restrict__ item_off, int32_t* __restrict__ sel_done) {
+                                                        int64_t* __restrict__ item_off, int32_t* __restrict__ sel_done,
+                                                        int32_t* __restrict__ tickets) {
+  if (threadIdx.x < 2) tickets[threadIdx.x] = 0;
   __shared__ long long s[1024];
   const int seg = (nq + 1023) / 1024;
   const int q0 = threadIdx.x * seg, q1 = min(nq, q0 + seg);
@@ -127,9 +130,9 @@ __global__ __launch_bounds__(1024) void worklist_kernel(const QueryDesc* __restr
 }
 
 hipError_t launch_worklist(const QueryDesc* qd, CandBuf cb, int nq, ScoreTune tune, int64_t* item_off,
-                           hipStream_t s) {
+                           int32_t* tickets, hipStream_t s) {
   hipLaunchKernelGGL(worklist_kernel, dim3(1), dim3(1024), 0, s, qd, cb.n, nq, tune.ct, tune.pts, item_off,
-                     cb.sel_done);
+                     cb.sel_done, tickets);
   return hipGetLastError();
 }
 
