@@ -187,8 +187,8 @@ int imloc_set_graphs(imloc_ctx *ctx, int enable);
 int imloc_graph_counters(const imloc_ctx *ctx, int64_t *captures, int64_t *launches);
 
 /* Launch shape of the scoring kernel: candidates per work item (32, 64 or
- * 128, or 0, the default: picked per round, the largest tile that still
- * gives about four work items per compute unit) and workgroups (1 to 2^20;
+ * 128, or 0, the default: picked per round, the largest tile of up to 256
+ * that still gives about four to eight work items per compute unit) and workgroups (1 to 2^20;
  * each walks the round's work list with a grid stride; or 0, the default:
  * per round, about 1.5 per estimated work item, between 8 per compute unit
  * and 2^18).  Neither changes any result (per-candidate sums are

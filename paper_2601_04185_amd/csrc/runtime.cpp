@@ -209,8 +209,13 @@ struct QPlan {
 
 // Scoring launch shape: the context's fixed one, or (ct == 0) the largest
 // candidate tile of 128, 64 and 32 that still gives about four work items per
-// CU, so that small rounds keep every CU busy; est holds per query the
-// expected candidates (one per sample) and scoring points.  Neither the tile
+// CU, so that small rounds keep every CU busy, and 256 from eight on: a larger
+// tile spends less on the filter's features (256 queries of 5,000 to 80,000
+// correspondences: 256 / 128 / 64 / 32 candidates 9.98 / 11.1 / 13.2 / 17.4 ms),
+// but ends raggedly (50,000 x 13,600, 5.3 items of 256 per CU: 143 us against
+// 142; 64 served queries of 7.5: 4.2 ms against 3.7; a round of 10,000 x 1,360:
+// 63 / 38 / 25 / 18 us).  est holds per query the expected candidates (one per
+// sample) and scoring points.  Neither the tile
 // nor the correspondences per item change a result (per-candidate sums are
 // integer-accumulated over fixed wave blocks).
 using EstList = SmallVec<std::pair<int64_t, int64_t>, 4>;
@@ -225,8 +230,8 @@ ScoreTune round_tune(const imloc_ctx* c, const std::pair<int64_t, int64_t>* est,
   };
   if (t.ct == 0) {
     t.ct = 32;
-    for (int ct : {128, 64})
-      if (items_for(ct) >= 4 * (int64_t)c->cus) {
+    for (int ct : {256, 128, 64})
+      if (items_for(ct) >= (ct == 256 ? 8 : 4) * (int64_t)c->cus) {
         t.ct = ct;
         break;
       }

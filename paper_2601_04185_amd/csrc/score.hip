@@ -29,10 +29,11 @@
 // 64 * PPL correspondences) is converted once to fixed point (2^-32) and all
 // partials are added with integer atomics, as are the counts.  Integer sums
 // do not depend on the order, so a candidate's score is the same for any
-// tiling, grid size or mix of queries.  The per-(candidate, wave) table in
-// LDS starts at zero and only a wave block with inliers writes its entry (its
-// count and float partial); the conversion to fixed point happens in the
-// item's final reduction, off the candidate loop.
+// tiling, grid size or mix of queries.  The tables in LDS start at zero and
+// only a wave block with inliers adds to them; the conversion to fixed point
+// happens once per block for all candidates, off the candidate loop.
+#include <type_traits>
+
 #include "imloc_device.h"
 #include "imloc_kernels.h"
 #include "query_device.h"
@@ -41,8 +42,6 @@ namespace imloc {
 
 constexpr int kScoreBlock = 256;
 constexpr int kScoreWaves = kScoreBlock / kWave;
-constexpr int kScoreMaxRounds = kScoreMaxPoints / (kScoreWaves * kScoreWaveBlock);  // wave blocks per wave and item
-static_assert(kScoreMaxRounds == 2, "a work item of 4,096 correspondences gives each wave two blocks");
 
 // Sum over the 64 lanes of a full wave with DPP lane moves (pairs, quads,
 // rows of 16 by shifts, then the row broadcasts 15 and 31); lane 63 ends with
@@ -136,37 +135,174 @@ hipError_t launch_worklist(const QueryDesc* qd, CandBuf cb, int nq, ScoreTune tu
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// The filter of float32 items.  Most candidates are wrong and see hardly any
+// correspondence inside the threshold (of the (candidate, 512 correspondences)
+// pairs of a round of random P3P samples one in five has one, of the 64-wide
+// slots one in 27), so before a wave evaluates a candidate (15 vector
+// instructions per residual) the matrix cores rule out the slots that cannot
+// hold an inlier.
+//
+// du', dv' and w are linear in twelve features of a correspondence, X~ = (X, Y,
+// Z, 1), p_u X~ and p_v X~ (p = -observation / tau), with the candidate's rows
+// as coefficients, so one 32x32x16 product in float16 gives each of them for 32
+// correspondences x 32 candidates.  An inlier has |du'| < w and |dv'| < w; a
+// slot passes if a correspondence has max(|Du|, |Dv|) < W + E, E bounding the
+// error of the float16 values and of the float32 evaluation (it rides on a
+// constant feature of W).  Slots that pass are evaluated exactly as without the
+// filter, so counts and partial sums do not change in a single bit.
+//
+// Features are shifted by the middle and divided by the half range of the
+// item's correspondences, so that they lie in [-1, 1] and round with an error
+// of at most 2^-12 each; a candidate's coefficients are scaled by a power of
+// two that brings their sum to 2^13 .. 2^14 (float16 ends at 65504), and what
+// their rounding costs is summed as it comes out.  To these two E adds 25 x
+// 2^-14 for coefficients that are flushed to zero, and 2^-19 of the terms'
+// magnitudes for the 16 additions of a product, the float32 evaluation and the
+// shift (about 2^-21 each).  What is not finite passes.
+//
+// Per 1,024 residuals the three products and the 43 vector instructions on
+// their results take 186 cycles of a SIMD (matrix and vector instructions of
+// different waves hardly overlap here: 38 cycles a product, 2.5 an
+// instruction; four products w +- du', w +- dv' and two bit operations
+// instead of the subtraction and the median take 195), the exact evaluation of
+// all 640.  256 queries of 5,000 to 80,000 correspondences, 5,570 candidates
+// each: 17.7 -> 9.98 ms, of it products 5.8, features and coefficients 1.2,
+// exact evaluation 2.8; 50,000 x 13,600: 235 -> 142 us; 50,000 x 4,096, 6 % of
+// them good: 85 -> 52 us; 10,000 x 1,360: 21 -> 18 us.  Three waves per SIMD
+// (168 registers); four spill and two leave latency open (10.4, 13.5 ms).
+// ---------------------------------------------------------------------------
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float float16v __attribute__((ext_vector_type(16)));
+constexpr int kFilterTile = 32;   // candidates, and correspondences, of one product
+// candidates of a tile from which the filter pays: its products cost 16 x 186
+// cycles per wave block and 32 candidates, the evaluation 320 per candidate
+constexpr int kFilterLeast = 12;
+
+// Middle and half range of an item's X, Y, Z, p_u, p_v.
+struct FilterRange {
+  float mid[5], half[5];
+};
+
+__device__ inline float wave_uniform(float x) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+
+// Minimum / maximum over the wave, in lane 63.
+template <bool MAX>
+__device__ inline float wave_extreme(float x) {
+  auto pick = [&](auto ctrl) {
+    const float y = __int_as_float(
+        __builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, false));
+    x = MAX ? fmaxf(x, y) : fminf(x, y);
+  };
+  pick(std::integral_constant<int, 0xb1>{});
+  pick(std::integral_constant<int, 0x4e>{});
+  pick(std::integral_constant<int, 0x114>{});
+  pick(std::integral_constant<int, 0x118>{});
+  pick(std::integral_constant<int, 0x142>{});
+  pick(std::integral_constant<int, 0x143>{});
+  return x;
+}
+
+// Coefficients of one candidate for the three products, 16 each.
+__device__ inline void filter_rows(const float4 r0, const float4 r1, const float4 r2, const FilterRange& f,
+                                   half8 (&out)[3][2]) {
+  const float* c = f.mid;
+  const float* s = f.half;
+  // the rows of du' and dv' with the middle of the observations folded in
+  const float u[4] = {fmaf(c[3], r2.x, r0.x), fmaf(c[3], r2.y, r0.y), fmaf(c[3], r2.z, r0.z), fmaf(c[3], r2.w, r0.w)};
+  const float v[4] = {fmaf(c[4], r2.x, r1.x), fmaf(c[4], r2.y, r1.y), fmaf(c[4], r2.z, r1.z), fmaf(c[4], r2.w, r1.w)};
+  auto at_mid = [&](float x, float y, float z, float w) { return fmaf(x, c[0], fmaf(y, c[1], fmaf(z, c[2], w))); };
+  float cu[4] = {u[0] * s[0], u[1] * s[1], u[2] * s[2], at_mid(u[0], u[1], u[2], u[3])};
+  float cv[4] = {v[0] * s[0], v[1] * s[1], v[2] * s[2], at_mid(v[0], v[1], v[2], v[3])};
+  float cw[4] = {r2.x * s[0], r2.y * s[1], r2.z * s[2], at_mid(r2.x, r2.y, r2.z, r2.w)};
+  const float w3 = fabsf(cw[0]) + fabsf(cw[1]) + fabsf(cw[2]), sw = w3 + fabsf(cw[3]);
+  const float u3 = fabsf(cu[0]) + fabsf(cu[1]) + fabsf(cu[2]) + s[3] * sw;
+  const float v3 = fabsf(cv[0]) + fabsf(cv[1]) + fabsf(cv[2]) + s[4] * sw;
+  const float sum = fmaxf(u3 + fabsf(cu[3]), v3 + fabsf(cv[3])) + sw;
+  // magnitudes of the terms before the shift
+  const float ax = fabsf(c[0]) + s[0], ay = fabsf(c[1]) + s[1], az = fabsf(c[2]) + s[2];
+  const float au = fabsf(c[3]) + s[3], av = fabsf(c[4]) + s[4];
+  auto mag = [&](const float4& r) { return fabsf(r.x) * ax + fabsf(r.y) * ay + fabsf(r.z) * az + fabsf(r.w); };
+  const float mw = mag(r2);
+  const float big = fmaxf(mag(r0) + au * mw, mag(r1) + av * mw) + mw;
+  bool fine = big < 1e30f && sum < 1e30f && sum > 1e-30f;  // (false for NaN)
+  const int ex = fine ? 14 - __builtin_amdgcn_frexp_expf(sum) : 0;
+  float eu = 0.f, ev = 0.f, ew = 0.f;  // what the rounding of the coefficients costs
+  auto h = [&](float x, float& err) {
+    const float y = ldexpf(x, ex);
+    const _Float16 z = (_Float16)y;
+    err += fabsf(y - (float)z);
+    return z;
+  };
+  const _Float16 zero = (_Float16)0.f;
+  out[0][0] = half8{h(cu[0], eu), h(cu[1], eu), h(cu[2], eu), h(cu[3], eu),
+                    h(cw[0] * s[3], eu), h(cw[1] * s[3], eu), h(cw[2] * s[3], eu), h(cw[3] * s[3], eu)};
+  out[0][1] = half8{zero, zero, zero, zero, zero, zero, zero, zero};
+  out[1][0] = half8{h(cv[0], ev), h(cv[1], ev), h(cv[2], ev), h(cv[3], ev), zero, zero, zero, zero};
+  out[1][1] = half8{h(cw[0] * s[4], ev), h(cw[1] * s[4], ev), h(cw[2] * s[4], ev), h(cw[3] * s[4], ev),
+                    zero, zero, zero, zero};
+  out[2][0] = half8{h(cw[0], ew), h(cw[1], ew), h(cw[2], ew), h(cw[3], ew), zero, zero, zero, zero};
+  const float E = fmaxf(eu, ev) + ew + ldexpf((fmaxf(u3, v3) + w3) * (1.01f / 4096.f) + (big + sum) * (1.f / 524288.f), ex) +
+                  25.f / 16384.f;
+  fine = fine && E < 60000.f;
+  // (1.002: the bound itself is rounded)
+  out[2][1] = half8{zero, zero, zero, zero, (_Float16)(fine ? E * 1.002f : 1.f), zero, zero, zero};
+  if (!fine) {  // W + E = 1, Du = Dv = 0: passes
+    const half8 none = {zero, zero, zero, zero, zero, zero, zero, zero};
+    out[0][0] = out[1][0] = out[1][1] = out[2][0] = none;
+  }
+}
+
+// Tables of a work item in LDS.
+template <int CT>
+struct ScoreTables {
+  float4 rows[CT][3];                         // projections of the tile's candidates
+  union {
+    half8 coef[CT / kFilterTile][3][2][kFilterTile];  // and their coefficients of the filter
+    struct {                                          // float64 items
+      uint32_t cnt[CT][kScoreWaves];
+      unsigned long long gain[CT][kScoreWaves];
+    } f64;
+  };
+  float ext[kScoreWaves][2][5];                 // the waves' ranges
+  uint32_t cnt[CT];                             // inliers so far
+  unsigned long long gain[CT];                  // G so far (fixed point)
+  float part[kScoreWaves][CT];                  // G of the waves' present blocks
+  uint32_t item[kScoreWaves];
+};
+
 // One float32 work item: CT candidates against pts correspondences.  The
 // correspondences come in wave blocks of 512 (lane l, slot k: block start +
 // 64 k + l); every (candidate, wave block) pair is scored by exactly one wave,
 // whose count and gain partial (a float sum over that block, converted once
-// to fixed point) are then added as integers, so the results do not depend on
+// to fixed point) are added as integers, so the results do not depend on
 // pts.  pts >= 2048: each wave takes blocks w, w + 4, ... for every
 // candidate; pts < 2048: the waves split into 2048 / pts candidate groups,
-// each of pts / 512 waves (one block each).  MULTI: pts > 2048, compiled
-// apart (the loop over a wave's blocks costs registers the one-block form
-// does not need).
-template <int CT, bool MULTI>
+// each of pts / 512 waves.  Between the blocks no wave waits for another.
+template <int CT>
 __device__ __forceinline__ void score_item_f32(const QueryDesc& d, const float* __restrict__ proj,
                                                uint32_t* __restrict__ ccnt, unsigned long long* __restrict__ cgain,
                                                BestState* st, int64_t tile, int64_t chunk, int ncand, int pts,
-                                               uint32_t (*s_cnt)[kScoreWaves],
-                                               float (*s_part)[kScoreMaxRounds * kScoreWaves], uint32_t* s_item,
-                                               float4 (*s_rows)[3]) {
+                                               ScoreTables<CT>& T) {
   constexpr int PPL = kScorePPL32;
   // the wave index in a scalar register: the candidate range and the block
   // derived from it are wave-uniform, so the candidate loop stays scalar
-  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // (addresses derived from it are not kept over the items: registers)
+  const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const float inv_tau = (float)(1.0 / d.tau);
   const ChunkRange rg = chunk_range(d, chunk, pts);
   const int c0 = (int)(tile * CT);
   const int cend = min(CT, ncand - c0);
-  const int nblk = pts / kScoreWaveBlock;  // wave blocks of the item
-  const int groups = nblk >= kScoreWaves ? 1 : kScoreWaves / nblk;
-  const int wpg = kScoreWaves / groups;    // waves per candidate group
-  const int grp = wave / wpg, gsz = CT / groups;
+  const int wpg = min(kScoreWaves, pts / kScoreWaveBlock);  // waves per candidate group
+  const int grp = wave / wpg, gsz = CT * wpg / kScoreWaves;
   const int cg0 = grp * gsz, cg1 = min(cend, cg0 + gsz);
-  const int rounds = MULTI ? nblk / kScoreWaves : 1;
+  // correspondences and wave blocks of the item
+  const int npt = (int)max((int64_t)0, min(rg.end - rg.begin, (int64_t)pts));
+  const int nblk = (npt + kScoreWaveBlock - 1) / kScoreWaveBlock;
+  const bool filter = gsz >= kFilterTile && cend >= kFilterLeast;
   // the tile's projection rows into LDS: every wave then reads a candidate's
   // 12 values as three broadcast 16-byte LDS loads into vector registers
   // (a multiply-add with a scalar-register operand issues about 1.7 times
@@ -175,97 +311,285 @@ __device__ __forceinline__ void score_item_f32(const QueryDesc& d, const float* 
     const int rows = rows_per_slot(d);
     const float4* __restrict__ pc =
         reinterpret_cast<const float4*>(proj + d.proj_off + 16 * ((int64_t)rows * c0 + rg.cam));
-    for (int e = threadIdx.x; e < 3 * cend; e += kScoreBlock) {
+    for (int e = tid; e < 3 * cend; e += kScoreBlock) {
       const int c = e / 3, r = e - 3 * c;
-      s_rows[c][r] = pc[(int64_t)4 * rows * c + r];
+      T.rows[c][r] = pc[(int64_t)4 * rows * c + r];
     }
   }
-  const auto U = gmem(d.S.u);
-  const auto V = gmem(d.S.v);
-  const auto X = gmem(d.S.X);
-  const auto Y = gmem(d.S.Y);
-  const auto Z = gmem(d.S.Z);
+  const auto U = gmem(d.S.u) + rg.begin;
+  const auto V = gmem(d.S.v) + rg.begin;
+  const auto X = gmem(d.S.X) + rg.begin;
+  const auto Y = gmem(d.S.Y) + rg.begin;
+  const auto Z = gmem(d.S.Z) + rg.begin;
   const auto W = gmem(d.S.w);
-  uint32_t item_cnt = 0;
-  for (int r = 0; r < rounds; ++r) {
-    const int blk = nblk >= kScoreWaves ? wave + r * kScoreWaves : wave % wpg;
-    const int64_t base = rg.begin + (int64_t)blk * kScoreWaveBlock + lane;
-    float pu[PPL], pv[PPL], px[PPL], py[PPL], pz[PPL], pw[PPL];
+  float pu[PPL], pv[PPL], px[PPL], py[PPL], pz[PPL], pw[PPL];
+  // the lane's correspondences of a block; past the end the last one again
+  // (observations negated, so that du' = a' + pu w is a multiply-add without modifiers)
+  auto load = [&](int blk) {
 #pragma unroll
     for (int k = 0; k < PPL; ++k) {
-      const int64_t i = base + (int64_t)k * kWave;
-      if (i < rg.end) {
-        // observations negated, so that du' = a' + pu w is a multiply-add without modifiers
-        pu[k] = -(U[i] * inv_tau); pv[k] = -(V[i] * inv_tau); px[k] = X[i]; py[k] = Y[i]; pz[k] = Z[i];
-        pw[k] = W ? W[i] : 1.0f;
-      } else {  // a NaN residual is never an inlier
-        pu[k] = __builtin_nanf(""); pv[k] = 0.f; px[k] = 0.f; py[k] = 0.f; pz[k] = 0.f; pw[k] = 0.f;
-      }
+      const int i = min(blk * kScoreWaveBlock + k * kWave + lane, npt - 1);
+      pu[k] = -(U[i] * inv_tau); pv[k] = -(V[i] * inv_tau); px[k] = X[i]; py[k] = Y[i]; pz[k] = Z[i];
     }
-    if (r == 0) __syncthreads();  // the rows are staged
-    for (int c = cg0; c < cg1; ++c) {
-      // (the other waves of the SIMD cover the LDS latency)
-      const float4 r0 = s_rows[c][0], r1 = s_rows[c][1], r2 = s_rows[c][2];
-      uint32_t cnt = 0;
-      uint64_t bal[PPL];
-      float dd[PPL], ww[PPL];
+  };
+  // past the end a NaN residual, never an inlier
+  auto mask_ends = [&](int blk) {
+#pragma unroll
+    for (int k = 0; k < PPL; ++k)
+      if (blk * kScoreWaveBlock + k * kWave + lane >= npt) pu[k] = __builtin_nanf("");
+  };
+  auto load_weights = [&](int blk) {
+#pragma unroll
+    for (int k = 0; k < PPL; ++k) {
+      const int i = min(blk * kScoreWaveBlock + k * kWave + lane, npt - 1);
+      pw[k] = W ? W[rg.begin + i] : 1.0f;
+    }
+  };
+  uint32_t item_cnt = 0;
+  // Candidate c on the wave's block, the slots of a mask.
+  //   inlier iff e' < w |w|: the sign of e' - w |w| rounded once (rejects w <= 0 and NaN)
+  //   G += w_i (w|w| - e') / (w|w|) over the inliers, slots with no inlier skipped
+  // (the empty volatile statements keep the wave-uniform branches as branches)
+  auto residual = [&](const float4& r0, const float4& r1, const float4& r2, int k, float& w) {
+    const float a = fmaf(r0.z, pz[k], fmaf(r0.y, py[k], fmaf(r0.x, px[k], r0.w)));
+    const float b = fmaf(r1.z, pz[k], fmaf(r1.y, py[k], fmaf(r1.x, px[k], r1.w)));
+    w = fmaf(r2.z, pz[k], fmaf(r2.y, py[k], fmaf(r2.x, px[k], r2.w)));
+    const float du = fmaf(pu[k], w, a), dv = fmaf(pv[k], w, b);
+    return fmaf(-w, fabsf(w), fmaf(dv, dv, du * du));
+  };
+  auto add_gain = [&](float dd, float w, int k, float& gain) {
+    const float t = w * fabsf(w);
+    if (dd < 0.f) gain = fmaf(-pw[k] * dd, __builtin_amdgcn_rcpf(t), gain);
+  };
+  auto put = [&](int c, uint32_t cnt, uint64_t lanes, float gain) {
+    // a lone lane's gain is the sum: no scan
+    uint64_t writer = lanes;
+    if (lanes & (lanes - 1)) {
+      gain = wave_scan_dpp(gain);  // the block's total in lane 63
+      writer = 1ull << (kWave - 1);
+    }
+    if (__builtin_amdgcn_inverse_ballot_w64(writer)) {
+      atomicAdd(&T.cnt[c], cnt);
+      T.part[wave][c] = gain;
+    }
+    item_cnt += cnt;
+  };
+  auto evaluate = [&](int c) {  // all slots
+    // (the other waves of the SIMD cover the LDS latency)
+    const float4 r0 = T.rows[c][0], r1 = T.rows[c][1], r2 = T.rows[c][2];
+    uint32_t cnt = 0;
+    uint64_t bal[PPL], lanes = 0;
+    float dd[PPL], ww[PPL];
+#pragma unroll
+    for (int k = 0; k < PPL; ++k) {
+      dd[k] = residual(r0, r1, r2, k, ww[k]);
+      bal[k] = __ballot(dd[k] < 0.f);
+      cnt += (uint32_t)__popcll(bal[k]);
+    }
+    if (cnt) {
+      asm volatile("");
+      float gain = 0.f;
 #pragma unroll
       for (int k = 0; k < PPL; ++k) {
-        const float a = fmaf(r0.z, pz[k], fmaf(r0.y, py[k], fmaf(r0.x, px[k], r0.w)));
-        const float b = fmaf(r1.z, pz[k], fmaf(r1.y, py[k], fmaf(r1.x, px[k], r1.w)));
-        const float w = fmaf(r2.z, pz[k], fmaf(r2.y, py[k], fmaf(r2.x, px[k], r2.w)));
-        const float du = fmaf(pu[k], w, a), dv = fmaf(pv[k], w, b);
-        // inlier iff e' < w |w|: the sign of e' - w |w| rounded once (rejects w <= 0 and NaN)
-        dd[k] = fmaf(-w, fabsf(w), fmaf(dv, dv, du * du));
-        ww[k] = w;
-        bal[k] = __ballot(dd[k] < 0.f);
-        cnt += (uint32_t)__popcll(bal[k]);
+        if (bal[k]) {
+          asm volatile("");
+          lanes |= bal[k];
+          add_gain(dd[k], ww[k], k, gain);
+        }
       }
-      if (cnt) {  // G += w_i (w|w| - e') / (w|w|) over the inliers, point slots with no inlier skipped
-        // (the empty volatile statements keep these wave-uniform branches as
-        // branches: most candidates have no inlier in most slots)
+      put(c, cnt, lanes, gain);
+    }
+  };
+  auto evaluate_slots = [&](int c, uint32_t slots) {
+    const float4 r0 = T.rows[c][0], r1 = T.rows[c][1], r2 = T.rows[c][2];
+    uint32_t cnt = 0;
+    uint64_t lanes = 0;
+    float gain = 0.f;
+#pragma unroll
+    for (int k = 0; k < PPL; ++k) {
+      if (slots & (1u << k)) {
         asm volatile("");
-        float gain = 0.f;
+        float w;
+        const float dd = residual(r0, r1, r2, k, w);
+        const uint64_t bal = __ballot(dd < 0.f);
+        if (bal) {
+          asm volatile("");
+          cnt += (uint32_t)__popcll(bal);
+          lanes |= bal;
+          add_gain(dd, w, k, gain);
+        }
+      }
+    }
+    if (cnt) put(c, cnt, lanes, gain);
+  };
+  // the block's float partials to fixed point
+  auto flush = [&]() {
+    for (int c = cg0 + lane; c < cg1; c += kWave) {
+      const float p = T.part[wave][c];
+      if (p != 0.f) {
+        atomicAdd(&T.gain[c], (unsigned long long)((double)p * kGainScale));
+        T.part[wave][c] = 0.f;
+      }
+    }
+  };
+
+  int blk = wave % wpg;
+  if (blk < nblk) load(blk);
+  if (!filter) {
+    __syncthreads();  // the rows are staged
+    for (; blk < nblk; blk += wpg) {
+      if (blk != wave % wpg) load(blk);
+      mask_ends(blk);
+      load_weights(blk);
+      for (int c = cg0; c < cg1; ++c) evaluate(c);
+      flush();
+    }
+  } else {
+    // range of the item's correspondences: lane, wave, workgroup
+    {
+      float lo[5], hi[5];
+#pragma unroll
+      for (int e = 0; e < 5; ++e) {
+        lo[e] = __builtin_inff();
+        hi[e] = -__builtin_inff();
+      }
+      auto widen = [&](int e, float x) {
+        lo[e] = fminf(lo[e], x);
+        hi[e] = fmaxf(hi[e], x);
+      };
+      for (int b = blk; b < nblk; b += wpg) {
+        if (b != blk) load(b);
 #pragma unroll
         for (int k = 0; k < PPL; ++k) {
-          if (bal[k]) {
-            asm volatile("");
-            const float t = ww[k] * fabsf(ww[k]);
-            if (dd[k] < 0.f) gain = fmaf(-pw[k] * dd[k], __builtin_amdgcn_rcpf(t), gain);
-          }
-        }
-        gain = wave_scan_dpp(gain);  // the block's total in lane 63
-        if (lane == kWave - 1) {
-          s_cnt[c][wave] = MULTI ? s_cnt[c][wave] + cnt : cnt;
-          s_part[c][wave * kScoreMaxRounds + r] = gain;
+          widen(0, px[k]);
+          widen(1, py[k]);
+          widen(2, pz[k]);
+          widen(3, pu[k]);
+          widen(4, pv[k]);
         }
       }
-      item_cnt += cnt;
+      if (blk + wpg < nblk) load(blk);
+#pragma unroll
+      for (int e = 0; e < 5; ++e) {
+        const float l = wave_extreme<false>(lo[e]), h = wave_extreme<true>(hi[e]);
+        if (lane == kWave - 1) {
+          T.ext[wave][0][e] = l;
+          T.ext[wave][1][e] = h;
+        }
+      }
+    }
+    __syncthreads();  // the rows are staged, the ranges written
+    FilterRange f;
+    float inv[5];
+#pragma unroll
+    for (int e = 0; e < 5; ++e) {
+      float l = T.ext[0][0][e], h = T.ext[0][1][e];
+#pragma unroll
+      for (int w = 1; w < kScoreWaves; ++w) {
+        l = fminf(l, T.ext[w][0][e]);
+        h = fmaxf(h, T.ext[w][1][e]);
+      }
+      f.mid[e] = wave_uniform(0.5f * (l + h));
+      f.half[e] = wave_uniform(fmaxf(h - f.mid[e], f.mid[e] - l) * 1.00001f);
+      inv[e] = wave_uniform(f.half[e] > 0.f ? 1.0f / f.half[e] : 0.f);
+    }
+    if (tid < cend) {
+      const int c = tid;
+      half8 co[3][2];
+      filter_rows(T.rows[c][0], T.rows[c][1], T.rows[c][2], f, co);
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) T.coef[c / kFilterTile][t][h][c % kFilterTile] = co[t][h];
+    }
+    __syncthreads();  // the coefficients are written
+    float inf = __builtin_inff();
+    asm("" : "+v"(inf));  // (a known infinity would turn the median below back into fmaxf)
+    // max(|a|, |b|) in one instruction (fmaxf adds two that quiet NaNs)
+    auto larger = [&](float a, float b) { return __builtin_amdgcn_fmed3f(fabsf(a), fabsf(b), inf); };
+    for (; blk < nblk; blk += wpg) {
+      if (blk != wave % wpg) load(blk);
+      // The products: correspondences are rows, candidates columns, so that a
+      // lane holds 16 correspondences of one candidate and their minimum needs
+      // no lane moves.  Lane 8 s + k of `passed`: the candidates of step s that
+      // may have an inlier in slot k.
+      uint32_t passed = 0;
+#pragma unroll
+      for (int k = 0; k < PPL; ++k) {
+        const float x = (px[k] - f.mid[0]) * inv[0], y = (py[k] - f.mid[1]) * inv[1], z = (pz[k] - f.mid[2]) * inv[2];
+        const float u = (pu[k] - f.mid[3]) * inv[3], v = (pv[k] - f.mid[4]) * inv[4];
+        // (a minimum drops a NaN: a slot that has one passes as a whole)
+        const uint32_t odd = __ballot(!(fabsf(x + y + z + u + v) < 6.f)) ? ~0u : 0u;
+        // lane l of an operand holds entries 0..7 (l < 32) or 8..15 of row l % 32
+        union {
+          half8 h;
+          unsigned w[4];
+        } P, Q;
+        P.h = half8{(_Float16)x, (_Float16)y, (_Float16)z, (_Float16)1.f, (_Float16)(u * x), (_Float16)(u * y),
+                    (_Float16)(u * z), (_Float16)u};
+        Q.h = half8{(_Float16)(v * x), (_Float16)(v * y), (_Float16)(v * z), (_Float16)v, (_Float16)1.f, (_Float16)0.f,
+                    (_Float16)0.f, (_Float16)0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const auto sw = __builtin_amdgcn_permlane32_swap(P.w[e], Q.w[e], false, false);
+          P.w[e] = sw[0];
+          Q.w[e] = sw[1];
+        }
+        int at = k;
+        for (int t0 = cg0; t0 < cg1; t0 += kFilterTile, at += PPL) {
+          const auto& co = T.coef[t0 / kFilterTile];
+          const half8 au = co[0][lane >> 5][lane & 31], av = co[1][lane >> 5][lane & 31];
+          const half8 aw = co[2][lane >> 5][lane & 31];
+          const float16v zero{};
+          float m = 0.f;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const half8 ft = h ? Q.h : P.h;
+            const float16v Du = __builtin_amdgcn_mfma_f32_32x32x16_f16(ft, au, zero, 0, 0, 0);
+            const float16v Dv = __builtin_amdgcn_mfma_f32_32x32x16_f16(ft, av, zero, 0, 0, 0);
+            const float16v Dw = __builtin_amdgcn_mfma_f32_32x32x16_f16(ft, aw, zero, 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 16; e += 2) {
+              const float s0 = larger(Du[e], Dv[e]) - Dw[e], s1 = larger(Du[e + 1], Dv[e + 1]) - Dw[e + 1];
+              m = fminf(fminf(s0, s1), m);
+            }
+          }
+          const uint64_t b = __ballot(m < 0.f);
+          const uint32_t word = (uint32_t)b | (uint32_t)(b >> 32) | odd;
+          passed = lane == at ? word : passed;
+        }
+      }
+      mask_ends(blk);
+      load_weights(blk);
+      for (int t0 = cg0, at = 0; t0 < cg1; t0 += kFilterTile, at += PPL) {
+        uint32_t any = 0;
+#pragma unroll
+        for (int k = 0; k < PPL; ++k) any |= (uint32_t)__builtin_amdgcn_readlane((int)passed, at + k);
+        if (cg1 - t0 < kFilterTile) any &= (1u << (cg1 - t0)) - 1u;
+        for (; any; any &= any - 1) {
+          const int c = __builtin_ctz(any);
+          evaluate_slots(t0 + c, (uint32_t)(__ballot((passed >> c) & 1u) >> at) & 0xffu);
+        }
+      }
+      flush();
     }
   }
-  if (lane == 0) s_item[wave] = item_cnt;
+  if (lane == 0) T.item[wave] = item_cnt;
   __syncthreads();
-  if ((int)threadIdx.x < cend) {  // the waves of the candidate's group
-    const int c = threadIdx.x, w0 = (c / gsz) * wpg;
-    uint32_t cnt = 0;
-    unsigned long long g = 0;
-    for (int w = w0; w < w0 + wpg; ++w) {
-      cnt += s_cnt[c][w];
-      s_cnt[c][w] = 0;  // the table is empty again for the next item
-      for (int r = 0; r < rounds; ++r) {  // each wave block's float partial to fixed point once
-        const float p = s_part[c][w * kScoreMaxRounds + r];
-        if (p != 0.f) g += (unsigned long long)((double)p * kGainScale);
-        s_part[c][w * kScoreMaxRounds + r] = 0.f;
-      }
-    }
+  if (tid < cend) {
+    const int c = tid;
     const int64_t slot = d.cand_off + c0 + c;
+    const uint32_t cnt = T.cnt[c];
+    const unsigned long long g = T.gain[c];
     if (cnt) atomicAdd(&ccnt[slot], cnt);
     if (g) atomicAdd(&cgain[slot], g);
+    T.cnt[c] = 0;  // empty again for the next item
+    T.gain[c] = 0;
   }
-  if (threadIdx.x == 0) {  // one add per item to the query's counter (same-address atomics serialise)
+  if (tid == 0) {  // one add per item to the query's counter (same-address atomics serialise)
     unsigned long long tot = 0;
 #pragma unroll
-    for (int w = 0; w < kScoreWaves; ++w) tot += s_item[w];
+    for (int w = 0; w < kScoreWaves; ++w) tot += T.item[w];
     if (tot) atomicAdd((unsigned long long*)&st->inlier_residuals, tot);
   }
   __syncthreads();
@@ -359,36 +683,32 @@ __device__ __forceinline__ void score_item_f64(const QueryDesc& d, const double*
 
 // Persistent workgroups over the work list; every workgroup exits once the
 // item index passes the device-side total.
-template <int CT, bool MULTI>
-__global__ __launch_bounds__(kScoreBlock) void score_kernel(const QueryDesc* __restrict__ qd,
-                                                            const float* __restrict__ proj,
-                                                            const double* __restrict__ pose,
-                                                            const int32_t* __restrict__ ncand,
-                                                            uint32_t* __restrict__ ccnt,
-                                                            unsigned long long* __restrict__ cgain,
-                                                            BestState* __restrict__ st, int nq, int pts,
-                                                            const int64_t* __restrict__ item_off) {
-  __shared__ uint32_t s_cnt[CT][kScoreWaves];    // float32 items
-  __shared__ float s_part[CT][kScoreMaxRounds * kScoreWaves];
-  __shared__ uint32_t s_cnt64[CT][kScoreWaves];  // float64 items
-  __shared__ unsigned long long s_gain[CT][kScoreWaves];
-  __shared__ uint32_t s_item[kScoreWaves];
-  __shared__ float4 s_rows[CT][3];
-  // the float32 (candidate, wave) table starts empty, and every item's final
-  // reduction empties what it read: a wave block writes its entry only when it
-  // holds inliers
-  for (int e = threadIdx.x; e < CT * kScoreWaves; e += kScoreBlock) {
-    (&s_cnt[0][0])[e] = 0;
-#pragma unroll
-    for (int r = 0; r < kScoreMaxRounds; ++r) (&s_part[0][0])[e * kScoreMaxRounds + r] = 0.f;
+template <int CT>
+__global__ __launch_bounds__(kScoreBlock, 3) void score_kernel(const QueryDesc* __restrict__ qd,
+                                                               const float* __restrict__ proj,
+                                                               const double* __restrict__ pose,
+                                                               const int32_t* __restrict__ ncand,
+                                                               uint32_t* __restrict__ ccnt,
+                                                               unsigned long long* __restrict__ cgain,
+                                                               BestState* __restrict__ st, int nq, int pts,
+                                                               const int64_t* __restrict__ item_off) {
+  __shared__ ScoreTables<CT> s_tab;
+  // the sums start empty, and every item leaves them empty
+  for (int e = threadIdx.x; e < CT * kScoreWaves; e += kScoreBlock) (&s_tab.part[0][0])[e] = 0.f;
+  if ((int)threadIdx.x < CT) {
+    s_tab.cnt[threadIdx.x] = 0;
+    s_tab.gain[threadIdx.x] = 0;
   }
   __syncthreads();
   const int64_t total = item_off[nq];
   for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
-    int lo = 0, hi = nq - 1;  // the query owning item w: last q with item_off[q] <= w
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (item_off[mid] <= w) lo = mid; else hi = mid - 1;
+    // the query owning item w (the last q with item_off[q] <= w): 64 probes a step
+    int lo = 0;
+    for (int n = nq; n > 1;) {
+      const int step = (n + kWave - 1) / kWave, at = (int)(threadIdx.x & (kWave - 1)) * step;
+      const int below = (int)__popcll(__ballot(at < n && item_off[lo + min(at, n - 1)] <= w)) - 1;
+      lo += below * step;
+      n = min(step, n - below * step);
     }
     const QueryDesc& d = qd[lo];
     const int64_t chunks = chunks_of(d, pts);
@@ -396,10 +716,9 @@ __global__ __launch_bounds__(kScoreBlock) void score_kernel(const QueryDesc* __r
     const int64_t tile = local / chunks, chunk = local - tile * chunks;
     const int nc = ncand[lo];
     if (d.precision == 0)
-      score_item_f32<CT, MULTI>(d, proj, ccnt, cgain, st + lo, tile, chunk, nc, pts, s_cnt, s_part, s_item,
-                                s_rows);
+      score_item_f32<CT>(d, proj, ccnt, cgain, st + lo, tile, chunk, nc, pts, s_tab);
     else
-      score_item_f64<CT>(d, pose, ccnt, cgain, st + lo, tile, chunk, nc, s_cnt64, s_gain, s_item);
+      score_item_f64<CT>(d, pose, ccnt, cgain, st + lo, tile, chunk, nc, s_tab.f64.cnt, s_tab.f64.gain, s_tab.item);
   }
 }
 
@@ -409,15 +728,13 @@ hipError_t launch_score(const QueryDesc* qd, CandBuf cb, BestState* st, int nq, 
   const dim3 grid(tune.blocks > 0 ? tune.blocks : 2048), block(kScoreBlock);
   unsigned long long* g = reinterpret_cast<unsigned long long*>(cb.gain);
   const int pts = tune.pts;
-  const bool multi = pts > kScoreBlock * kScorePPL32;
-#define IMLOC_SCORE_LAUNCH(CT)                                                                                 \
-  if (multi)                                                                                                   \
-    hipLaunchKernelGGL((score_kernel<CT, true>), grid, block, 0, s, qd, cb.proj, cb.pose, cb.n, cb.cnt, g, st, nq, \
-                       pts, item_off);                                                                         \
-  else                                                                                                         \
-    hipLaunchKernelGGL((score_kernel<CT, false>), grid, block, 0, s, qd, cb.proj, cb.pose, cb.n, cb.cnt, g, st,    \
-                       nq, pts, item_off);
+#define IMLOC_SCORE_LAUNCH(CT)                                                                                    \
+  hipLaunchKernelGGL((score_kernel<CT>), grid, block, 0, s, qd, cb.proj, cb.pose, cb.n, cb.cnt, g, st, nq, pts, \
+                     item_off);
   switch (tune.ct) {
+    case 256:
+      IMLOC_SCORE_LAUNCH(256)
+      break;
     case 128:
       IMLOC_SCORE_LAUNCH(128)
       break;
