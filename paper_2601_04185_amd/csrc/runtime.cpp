@@ -1281,7 +1281,10 @@ int imloc_triangulate_depth(imloc_ctx* ctx, int32_t H, int32_t W, const imloc_ca
     centre(T, C);
     for (int c = 0; c < 3; ++c) o[13 + c] = e == 0 ? 0.0 : C0[c] - C[c];
   }
-  HIP_TRY(ctx, hipMemcpyAsync(dviews, h, hb, hipMemcpyHostToDevice, ctx->stream));
+  // the empty refinement queue goes along (the next piece of the workspace)
+  const size_t cnt = (size_t)((char*)n_tasks - (char*)dviews);
+  *reinterpret_cast<int32_t*>((char*)h + cnt) = 0;
+  HIP_TRY(ctx, hipMemcpyAsync(dviews, h, cnt + sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
   rc = staging_mark(ctx);
   if (rc) return rc;
   TriArgs ta;
