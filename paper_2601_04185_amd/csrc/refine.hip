@@ -9,7 +9,7 @@
 //
 // One launch runs every iteration of every problem.  A problem is worked on
 // by a team of workgroups: its points are cut into groups (2,048 points each
-// up to 65,536 points, see gn_group_points), every member evaluates its
+// up to 262,144 points, see gn_group_points), every member evaluates its
 // groups at the current pose -- the 6x6 normal equations (upper triangle), the
 // gradient, the cost and the inlier count of a group, in float64 -- and the
 // members exchange the groups' sums, add them in group order and take the
@@ -55,9 +55,10 @@ constexpr int kGNThreads = 256;
 constexpr int kGNWaves = kGNThreads / kWave;
 constexpr int kGNGroup = 2048;          // points of a group that stays in LDS, at most: eight per thread
 constexpr int kGNGroupMost = 32768;     // of the largest (offsets in a group are 16 bits, 0xffff is none)
-constexpr int kGNGroupsWanted = 32;
+constexpr int kGNHalfGroups = 32;        // groups of half that size, at most
+constexpr int kGNGroupsWanted = 128;     // groups of a problem, until their size grows past kGNGroup
 constexpr int kGNBox = 64;              // mailbox words of a group (58 used)
-constexpr int kGNInBlock = 32;          // groups read together
+constexpr int kGNInBlock = 64;          // groups read together (a bit each in a word)
 constexpr uint16_t kGNNone = 0xffff;
 // waves per SIMD where the points are read from memory (the local optimisation
 // of 256 queries took 3.3 ms with two, 2.73 with three, 3.96 with four, which
@@ -113,15 +114,18 @@ __device__ __forceinline__ double uniform(double x) {
 }
 
 // Points of a group of a problem of n points: one group up to 2,048 points,
-// then 1,024 points each while that makes at most 32 groups, then a 32nd of
-// the points (in steps of 2,048) up to 32,768.  More groups are more compute
-// units for one problem (a lone wave per SIMD issues a float64 instruction
-// every 5.4 cycles, so four points per thread take 2,600 cycles of an
-// evaluation), but each evaluation ends with an exchange of about 3,500
-// cycles once there are two, and 32 mailboxes take 5,000.
+// then 1,024 points each while that makes at most 32 groups, then 2,048, and
+// past 128 groups a 128th of the points (in steps of 2,048) up to 32,768.  More
+// groups are more compute units for one problem (a lone wave per SIMD issues a
+// float64 instruction every 5.4 cycles, so four points per thread take 2,600
+// cycles of an evaluation), but each evaluation ends with an exchange of about
+// 3,500 cycles once there are two, and 32 mailboxes take 5,000.  Larger groups
+// would not stay in LDS: with a 32nd of the points from 65,536 points on, both
+// stages on 66,000 / 90,000 / 200,000 points from one start took 223 / 225 /
+// 352 us, now 159 / 170 / 234.
 __host__ __device__ inline int gn_group_points(int64_t n) {
   if (n <= kGNGroup) return kGNGroup;
-  if (n <= (int64_t)kGNGroupsWanted * kGNGroup / 2) return kGNGroup / 2;
+  if (n <= (int64_t)kGNHalfGroups * kGNGroup / 2) return kGNGroup / 2;
   int64_t s = (n + kGNGroupsWanted - 1) / kGNGroupsWanted;
   s = (s + kGNGroup - 1) / kGNGroup * kGNGroup;
   return (int)(s > kGNGroupMost ? kGNGroupMost : s);
@@ -138,8 +142,10 @@ int gn_groups(int64_t n) { return groups_for(n); }
 // the most groups that a problem of up to n points has (more points can make
 // fewer groups: 32,768 make 32, 32,769 make 17)
 int gn_most_groups(int64_t n) {
-  const int g = groups_for(n);
-  return n > (int64_t)kGNGroupsWanted * kGNGroup / 2 && g < kGNGroupsWanted ? kGNGroupsWanted : g;
+  int g = groups_for(n);
+  if (n > (int64_t)kGNHalfGroups * kGNGroup / 2 && g < kGNHalfGroups) g = kGNHalfGroups;
+  if (n > (int64_t)kGNGroupsWanted * kGNGroup && g < kGNGroupsWanted) g = kGNGroupsWanted;
+  return g;
 }
 
 // The final refinement's in-set where its points do not stay in LDS: 16-bit
@@ -534,7 +540,7 @@ struct GNLds {
   double tot[kAcc];
   GNShared s;
   int kept[kGNGroup / kGNThreads][kGNWaves];
-  unsigned miss;
+  unsigned long long miss;
   int alone, role;
 };
 
@@ -795,7 +801,7 @@ __device__ __forceinline__ void box_get(GNLds& L, const uint64_t* box, int b0, i
     if (n >= most) {
 #pragma unroll
       for (int u = 0; u < kPer; ++u)
-        if (need[u]) atomicOr(&L.miss, 1u << (at[u] / kGNBox));
+        if (need[u]) atomicOr(&L.miss, 1ull << (at[u] / kGNBox));
       break;
     }
   }
@@ -895,11 +901,11 @@ __attribute__((amdgpu_waves_per_eu(RES || RIG ? 2 : kGNWavesMany, RES || RIG ? 2
     // missing ones from their points (alone; the refinement lists their set
     // first).  One loop, so that the evaluation is in the code once.
     int grp = member, b0 = -kGNInBlock, nb = 0;
-    unsigned miss = 0;
+    unsigned long long miss = 0;
     bool own = true, listed = MODE == 0 || j == 0;
     for (;;) {
       if (own ? grp < G : miss != 0) {
-        const int gi = own ? 0 : __builtin_ctz(miss);
+        const int gi = own ? 0 : __builtin_ctzll(miss);
         const int at = own ? grp : b0 + gi;
         const bool list_only = !own && !listed;
         const double sum = gn_eval_group<MODE, RIG, RES>(L, R, v, s_rig, list_only ? L.s.start : L.s.eval, at,

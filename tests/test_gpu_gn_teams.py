@@ -43,7 +43,7 @@ def _starts(q, k, seed):
     return P
 
 
-@pytest.mark.parametrize("n", [3, 255, 2048, 2049, 3073, 32768, 32769, 65537])
+@pytest.mark.parametrize("n", [3, 255, 2048, 2049, 3073, 32768, 32769, 65537, 131073, 262145])
 def test_stages_do_not_depend_on_the_team(pk, n):
     import torch
     q = synth.make_query(940 + n % 89, n, 0.5, 1.0, weights="conf")
