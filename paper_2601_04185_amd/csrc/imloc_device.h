@@ -559,12 +559,25 @@ __device__ inline double log8_level(int c) {
 }
 
 // nearest level in log depth (halves away from zero); 0 for depth not finite or <= 0
-__device__ inline uint8_t log8_code(float f) {
-  double d = f;
-  if (!(d > 0.0 && d <= 3.4028234663852886e38)) return 0;
-  d = fmin(fmax(d, kLog8DMin), kLog8DMin * 512.0);
+__device__ inline uint8_t log8_code_f64(float f) {
+  const double d = fmin(fmax((double)f, kLog8DMin), kLog8DMin * 512.0);
   const double level = kLog8Steps * log2(d / kLog8DMin) / kLog8Log2Range;
   return (uint8_t)(1 + (int)round(level));
+}
+
+// The float64 logarithm only decides near a rounding boundary: the float32
+// level is off by less than 4.5e-5 (the hardware's log2 by an ulp of up to 8,
+// its factor and the multiply-add by 1.5e-5 each), so farther than 2e-4 from a
+// boundary, where all but one depth in 2,500 lie, it rounds to the same code.
+__device__ inline uint8_t log8_code(float f) {
+  if (!(f > 0.0f && f <= 3.402823466e38f)) return 0;
+  constexpr double kPerOctave = kLog8Steps / kLog8Log2Range;
+  const float c = fminf(fmaxf(f, (float)kLog8DMin), (float)(kLog8DMin * 512.0));
+  // the level and a half: log2(c / 0.25) = log2(c) + 2
+  const float x = fmaf(__builtin_amdgcn_logf(c), (float)kPerOctave, (float)(2.0 * kPerOctave + 0.5));
+  const float k = floorf(x);
+  if (fabsf(x - k - 0.5f) < 0.5f - 2e-4f) return (uint8_t)(1 + (int)k);
+  return log8_code_f64(f);
 }
 
 // Folded projection P = K [R | t] rows (a, b, w) = P [X, 1].

@@ -174,22 +174,40 @@ hipError_t launch_lift(const LiftArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+constexpr int kEncodeQuads = 4;
+
 // Encoder of the code maps: nearest level in log depth (halves away from
 // zero), depth clipped to [0.25, 128] m, code 0 for depth not finite or <= 0.
-// Four depths per thread (one float4 load, one 32-bit store) over the first
-// 4 * n4 entries, one per thread over the rest (n4 = 0 when the arrays are
-// not 16- and 4-byte aligned).
+// Four depths per load (float4) and store (32 bits) over the first 4 * n4
+// entries, one per thread over the rest (n4 = 0 when the arrays are not 16- and
+// 4-byte aligned).  A thread takes four such quads, 256 apart, loaded together,
+// and the float64 logarithm is the exception (log8_code): a call on 20 maps of
+// 480 x 640 20.0 -> 8.7 us (31 MB: 6 us at the rate of a copy), on 20 million
+// depths 71 -> 19.5 us.  With one quad per thread, 6,000 short workgroups, the
+// faster logarithm alone gains nothing.
 __global__ __launch_bounds__(256) void log8_encode_kernel(const float* __restrict__ depth, int64_t n, int64_t n4,
                                                            uint8_t* __restrict__ codes) {
-  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (q < n4) {
-    const float4 v = reinterpret_cast<const float4*>(depth)[q];
-    const uint32_t w = (uint32_t)log8_code(v.x) | ((uint32_t)log8_code(v.y) << 8) |
-                       ((uint32_t)log8_code(v.z) << 16) | ((uint32_t)log8_code(v.w) << 24);
-    reinterpret_cast<uint32_t*>(codes)[q] = w;
-  } else {
-    const int64_t i = 4 * n4 + (q - n4);
-    if (i < n) codes[i] = log8_code(depth[i]);
+  constexpr int Q = kEncodeQuads;
+  const int64_t q0 = (int64_t)blockIdx.x * (256 * Q) + threadIdx.x;
+  if (q0 - threadIdx.x < n4) {
+    float4 v[Q];
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      const int64_t q = q0 + 256 * j;
+      v[j] = reinterpret_cast<const float4*>(depth)[q < n4 ? q : n4 - 1];
+    }
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      const int64_t q = q0 + 256 * j;
+      const uint32_t w = (uint32_t)log8_code(v[j].x) | ((uint32_t)log8_code(v[j].y) << 8) |
+                         ((uint32_t)log8_code(v[j].z) << 16) | ((uint32_t)log8_code(v[j].w) << 24);
+      if (q < n4) reinterpret_cast<uint32_t*>(codes)[q] = w;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {  // the rest: entries past the last quad
+    const int64_t i = 4 * n4 + (q0 + 256 * j - n4);
+    if (q0 + 256 * j >= n4 && i < n) codes[i] = log8_code(depth[i]);
   }
 }
 
@@ -198,7 +216,8 @@ hipError_t launch_log8_encode(const float* depth, int64_t n, uint8_t* codes, hip
   const bool vec = reinterpret_cast<uintptr_t>(depth) % 16 == 0 && reinterpret_cast<uintptr_t>(codes) % 4 == 0;
   const int64_t n4 = vec ? n / 4 : 0;
   const int64_t threads = n4 + (n - 4 * n4);
-  hipLaunchKernelGGL(log8_encode_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, depth, n, n4,
+  constexpr int kPer = 256 * kEncodeQuads;
+  hipLaunchKernelGGL(log8_encode_kernel, dim3((unsigned)((threads + kPer - 1) / kPer)), dim3(256), 0, s, depth, n, n4,
                      codes);
   return hipGetLastError();
 }
