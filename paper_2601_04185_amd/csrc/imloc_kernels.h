@@ -120,9 +120,10 @@ struct LiftArgs {
   int32_t* out_src;
   int64_t capacity;
   int32_t* n_out;
-  int32_t* block_counts;  // scratch [blocks]
+  uint64_t* state;        // scratch, zero: what the workgroups publish
+  int polls;              // polls of a wait before a workgroup counts for another
 };
-int lift_blocks(int64_t n);
+int64_t lift_words(int64_t n);  // of the scratch
 hipError_t launch_lift(const LiftArgs& a, hipStream_t s);
 // 8-bit log-depth codes of n float32 depths (depth and codes 16- and 4-byte aligned)
 hipError_t launch_log8_encode(const float* depth, int64_t n, uint8_t* codes, hipStream_t s);

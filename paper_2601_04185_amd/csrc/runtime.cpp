@@ -1039,8 +1039,8 @@ int imloc_set_score_tuning(imloc_ctx* c, int32_t candidates_per_item, int32_t wo
   return IMLOC_OK;
 }
 
-// Polls of a wait within a Gauss-Newton team before a member works alone
-// (not part of the interface: the tests set 0, so that every member does).
+// Polls of a wait within a Gauss-Newton team, or for another workgroup's count
+// in a lift, before a workgroup works alone (not part of the interface: the tests set 0, so that every member does).
 int gn_set_team_polls(imloc_ctx* c, int32_t polls) {
   if (!c || polls < 0) return IMLOC_EINVAL;
   c->gn_polls = polls;
@@ -1149,9 +1149,8 @@ size_t imloc_sample_workspace_bytes(int64_t n, int64_t count) {
 size_t imloc_lift_workspace_bytes(int64_t n_matches, int32_t n_views) {
   if (n_matches < 0 || n_views < 0) return 0;
   Arena a{nullptr, (size_t)-1};
-  const int nb = lift_blocks(n_matches);
   a.take<double>(16 * (size_t)(n_views > 0 ? n_views : 1));
-  a.take<int32_t>((size_t)(nb > 0 ? nb : 1));
+  a.take<uint64_t>((size_t)lift_words(n_matches));
   return a.off + 256;
 }
 
@@ -1175,11 +1174,11 @@ static int lift_impl(imloc_ctx* ctx, const imloc_matches* m, int64_t n_matches, 
   }
   hipSetDevice(ctx->device);
   Arena a{ctx->ws, ctx->ws_bytes};
-  const int nb = lift_blocks(n_matches);
+  const size_t words = (size_t)lift_words(n_matches);
   // the view table: intrinsics of every view, then the poses (one upload)
   double* dcams = a.take<double>(16 * (size_t)(n_views > 0 ? n_views : 1));
   double* dposes = dcams + 4 * (size_t)(n_views > 0 ? n_views : 1);
-  int32_t* blk = a.take<int32_t>((size_t)(nb > 0 ? nb : 1));
+  uint64_t* state = a.take<uint64_t>(words);
   if (!a.ok) return set_err(ctx, IMLOC_ENOMEM, "workspace too small for lift: need %zu bytes", a.off);
   if (n_matches > 0) {
     const size_t hb = (size_t)n_views * 16 * sizeof(double);
@@ -1194,7 +1193,17 @@ static int lift_impl(imloc_ctx* ctx, const imloc_matches* m, int64_t n_matches, 
       for (int e = 0; e < 9; ++e) hp[12 * k + e] = poses[k].R[e];
       for (int e = 0; e < 3; ++e) hp[12 * k + 9 + e] = poses[k].t[e];
     }
-    HIP_TRY(ctx, hipMemcpyAsync(dcams, hc, 16 * (size_t)n_views * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
+    // the zeros of the workgroups' counts go along where the staging has room
+    // (they are the next piece of the workspace)
+    size_t bytes = 16 * (size_t)n_views * sizeof(double);
+    const size_t at = (size_t)((char*)state - (char*)dcams), all = at + words * sizeof(uint64_t);
+    if (words > 0 && all <= ctx->pinned_bytes) {
+      memset((char*)ctx->pinned + at, 0, words * sizeof(uint64_t));
+      bytes = all;
+    } else if (words > 0) {
+      HIP_TRY(ctx, launch_fill_i32(reinterpret_cast<int32_t*>(state), (int64_t)words * 2, 0, ctx->stream));
+    }
+    HIP_TRY(ctx, hipMemcpyAsync(dcams, hc, bytes, hipMemcpyHostToDevice, ctx->stream));
     rc = staging_mark(ctx);
     if (rc) return rc;
   }
@@ -1204,7 +1213,7 @@ static int lift_impl(imloc_ctx* ctx, const imloc_matches* m, int64_t n_matches, 
   la.n = n_matches; la.depth = depth; la.codes = codes; la.n_views = n_views; la.H = H; la.W = W;
   la.cams = dcams; la.poses = dposes; la.subpixel = subpixel; la.min_conf = min_conf;
   la.out_u = out->u; la.out_v = out->v; la.out_X = out->X; la.out_Y = out->Y; la.out_Z = out->Z;
-  la.out_w = out->w; la.out_src = out->src; la.capacity = capacity; la.n_out = n_out; la.block_counts = blk;
+  la.out_w = out->w; la.out_src = out->src; la.capacity = capacity; la.n_out = n_out; la.state = state; la.polls = ctx->gn_polls;
   HIP_TRY(ctx, launch_lift(la, ctx->stream));
   return IMLOC_OK;
 }
