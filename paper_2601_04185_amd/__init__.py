@@ -128,6 +128,9 @@ def lib():
             "imloc_get_score_points": ([vp, vp], C.c_int),
             "imloc_score_workspace_bytes": ([i64, i64, i32], C.c_size_t),
             "imloc_lift_workspace_bytes": ([i64, i32], C.c_size_t),
+            "imloc_lift": ([vp, vp, i64, vp, i32, i32, i32, vp, vp, i32, C.c_float, vp, i64, vp], C.c_int),
+            "imloc_lift_log8": ([vp, vp, i64, vp, i32, i32, i32, vp, vp, i32, C.c_float, vp, i64, vp], C.c_int),
+            "lift_kept": ([vp, vp], C.c_int),  # not part of the interface
             "imloc_lo_workspace_bytes": ([i64, i32], C.c_size_t),
             "imloc_refine_workspace_bytes": ([i64], C.c_size_t),
             "imloc_set_timing": ([vp, C.c_int], C.c_int),
@@ -451,21 +454,24 @@ def imloc_lift(ctx: Context, matches: dict, depth, cams, poses, subpixel=True, m
     # always writes the count)
     c1 = (max(cap, 1) + 63) // 64 * 64  # each array 256-byte aligned
     buf = torch.empty(7 * c1 + 1, dtype=torch.float32, device=dev)
-    out = {k: buf[i * c1:(i + 1) * c1] for i, k in enumerate(("u", "v", "X", "Y", "Z", "w"))}
-    out["src"] = buf[6 * c1:7 * c1].view(torch.int32)
-    n_out = buf[7 * c1:].view(torch.int32)
+    base = buf.data_ptr()
     m = Matches(*[matches[k].data_ptr() for k in ("q_u", "q_v", "db_u", "db_v", "conf", "view")])
-    co = CorrOut(*[out[k].data_ptr() for k in ("u", "v", "X", "Y", "Z", "w", "src")])
+    co = CorrOut(*[base + 4 * i * c1 for i in range(7)])
     # Camera and Pose are rows of 4 and 12 doubles
-    cams_a = np.ascontiguousarray(np.asarray(cams, np.float64).reshape(nv, 4))
-    poses_a = np.ascontiguousarray(np.asarray(poses, np.float64).reshape(nv, 12))
-    ctx.ensure_workspace(lib().imloc_lift_workspace_bytes(n, nv))
-    fn = lib().imloc_lift_log8 if depth.dtype == torch.uint8 else lib().imloc_lift
-    ctx.check(fn(ctx.h, C.byref(m), n, C.c_void_p(depth.data_ptr()), nv, H, W, cams_a.ctypes.data_as(C.c_void_p),
-                 poses_a.ctypes.data_as(C.c_void_p), 1 if subpixel else 0, C.c_float(min_conf), C.byref(co), cap,
-                 C.c_void_p(n_out.data_ptr())))
-    k = int(n_out.item())
-    res = {key: v[:min(k, cap)] for key, v in out.items()}
+    cams_a = np.ascontiguousarray(cams, np.float64).reshape(nv, 4)
+    poses_a = np.ascontiguousarray(poses, np.float64).reshape(nv, 12)
+    L = lib()
+    ctx.ensure_workspace(L.imloc_lift_workspace_bytes(n, nv))
+    fn = L.imloc_lift_log8 if depth.dtype == torch.uint8 else L.imloc_lift
+    ctx.check(fn(ctx.h, C.byref(m), n, depth.data_ptr(), nv, H, W, cams_a.ctypes.data, poses_a.ctypes.data,
+                 1 if subpixel else 0, C.c_float(min_conf), C.byref(co), cap, base + 4 * 7 * c1))
+    kept = C.c_int32()
+    ctx.check(L.lift_kept(ctx.h, C.byref(kept)))
+    k = kept.value if n else 0
+    # seven views of the kept length in two operations (a slice each costs a microsecond)
+    rows = buf[:7 * c1].view(7, c1)[:, :min(k, cap)].unbind(0)
+    res = dict(zip(("u", "v", "X", "Y", "Z", "w"), rows))
+    res["src"] = rows[6].view(torch.int32)
     res["n"] = k
     return res
 

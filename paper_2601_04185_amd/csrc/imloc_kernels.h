@@ -120,6 +120,7 @@ struct LiftArgs {
   int32_t* out_src;
   int64_t capacity;
   int32_t* n_out;
+  int32_t* n_host;        // the same in pinned host memory
   uint64_t* state;        // scratch, zero: what the workgroups publish
   int polls;              // polls of a wait before a workgroup counts for another
 };

@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kLiftBlock) void lift_kernel(LiftArgs a) {
   const unsigned before = lift_before<kCodes>(a, tile, lut);
   if (tid == 0) {
     if (tile > 0 && tile < nb - 1) lift_publish(a.state + tile, 2, before + own);
-    if (tile == nb - 1) *a.n_out = (int32_t)(before + own);
+    if (tile == nb - 1) *a.n_out = *a.n_host = (int32_t)(before + own);
   }
 #pragma unroll
   for (int j = 0; j < kLiftPer; ++j) {

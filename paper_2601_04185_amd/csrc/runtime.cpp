@@ -115,6 +115,7 @@ struct imloc_ctx {
   // that) before writing the buffer again.
   char* pinned = nullptr;
   size_t pinned_bytes = 0;
+  int32_t* kept = nullptr;  // pinned: kept matches of the last lift
   hipEvent_t staging_ev = nullptr;
   bool staging_pending = false;
   // recorded behind a synchronous call's work and polled (wait_stream)
@@ -513,8 +514,12 @@ int staging_alloc(imloc_ctx* c, size_t bytes) {
   c->pinned = nullptr;
   c->pinned_bytes = 0;
   c->staging_pending = false;
-  HIP_TRY(c, hipHostMalloc(reinterpret_cast<void**>(&c->pinned), bytes, hipHostMallocDefault));
+  // and a word behind it for the count of a lift (lift_kept)
+  const size_t up = (bytes + 63) & ~size_t(63);
+  HIP_TRY(c, hipHostMalloc(reinterpret_cast<void**>(&c->pinned), up + 64, hipHostMallocDefault));
   c->pinned_bytes = bytes;
+  c->kept = reinterpret_cast<int32_t*>(c->pinned + up);
+  *c->kept = 0;
   return IMLOC_OK;
 }
 
@@ -1214,6 +1219,7 @@ static int lift_impl(imloc_ctx* ctx, const imloc_matches* m, int64_t n_matches, 
   la.cams = dcams; la.poses = dposes; la.subpixel = subpixel; la.min_conf = min_conf;
   la.out_u = out->u; la.out_v = out->v; la.out_X = out->X; la.out_Y = out->Y; la.out_Z = out->Z;
   la.out_w = out->w; la.out_src = out->src; la.capacity = capacity; la.n_out = n_out; la.state = state; la.polls = ctx->gn_polls;
+  la.n_host = ctx->kept;
   HIP_TRY(ctx, launch_lift(la, ctx->stream));
   return IMLOC_OK;
 }
@@ -1238,6 +1244,17 @@ int imloc_depth_encode_log8(imloc_ctx* ctx, const float* depth, int64_t count, u
   if (count > 0 && (!depth || !codes)) return set_err(ctx, IMLOC_EINVAL, "null depth or code array");
   hipSetDevice(ctx->device);
   HIP_TRY(ctx, launch_log8_encode(depth, count, codes, ctx->stream));
+  return IMLOC_OK;
+}
+
+// Waits for the lift enqueued last and reads how many matches it kept, without
+// a copy (not part of the interface: the Python package's imloc_lift, whose
+// outputs are views of that length).
+int lift_kept(imloc_ctx* ctx, int32_t* n) {
+  if (!ctx || !n) return IMLOC_EINVAL;
+  const int rc = wait_stream(ctx, ctx->stream);
+  if (rc) return rc;
+  *n = *static_cast<volatile int32_t*>(ctx->kept);
   return IMLOC_OK;
 }
 
