@@ -128,8 +128,6 @@ def lib():
             "imloc_get_score_points": ([vp, vp], C.c_int),
             "imloc_score_workspace_bytes": ([i64, i64, i32], C.c_size_t),
             "imloc_lift_workspace_bytes": ([i64, i32], C.c_size_t),
-            "imloc_lift": ([vp, vp, i64, vp, i32, i32, i32, vp, vp, i32, C.c_float, vp, i64, vp], C.c_int),
-            "imloc_lift_log8": ([vp, vp, i64, vp, i32, i32, i32, vp, vp, i32, C.c_float, vp, i64, vp], C.c_int),
             "lift_kept": ([vp, vp], C.c_int),  # not part of the interface
             "imloc_lo_workspace_bytes": ([i64, i32], C.c_size_t),
             "imloc_refine_workspace_bytes": ([i64], C.c_size_t),

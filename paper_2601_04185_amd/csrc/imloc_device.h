@@ -595,9 +595,37 @@ __device__ inline void projection_rows(const Pose& P, const Cam& K, double M[12]
 // ---------------------------------------------------------------------------
 // Wave / block reductions.
 // ---------------------------------------------------------------------------
+// A double moved across lanes by a DPP control (both 32-bit halves).
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// Sum over a full wave in every lane: the butterfly of lane distances 32, 16,
+// 8, 4, 2, 1 by lane moves of the vector unit (a rotation by 8 or 4 lanes of a
+// row is the exchange once the row repeats after 16 or 8 lanes).
 __device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
+  {
+    const long long b = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    v = __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
+        __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+  }
+  {
+    const long long b = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    v = __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
+        __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+  }
+  v += dpp_f64<0x128>(v);  // row_ror:8
+  v += dpp_f64<0x124>(v);  // row_ror:4
+  v += dpp_f64<0x4e>(v);   // quad_perm [2, 3, 0, 1]
+  v += dpp_f64<0xb1>(v);   // quad_perm [1, 0, 3, 2]
   return v;
 }
 __device__ inline float wave_sum(float v) {

@@ -174,15 +174,6 @@ int gn_team(int groups, int64_t total, int slots, int most, int mode) {
   return t < kGNGroupsWanted ? t : kGNGroupsWanted;
 }
 
-// A double moved across lanes by a DPP control (both 32-bit halves).
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
 // Exchange of lanes 32..63 of x with lanes 0..31 of y (swap16: odd 16-lane
 // rows of x with even rows of y); then x + y holds, in a lane with that lane
 // bit clear, the pair sum of x, and with it set, the pair sum of y.

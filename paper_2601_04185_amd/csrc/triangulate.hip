@@ -104,14 +104,6 @@ constexpr int kTriLoadGroup = 16;  // match loads issued together
 
 __host__ __device__ inline int tri_quad_rows(int V) { return (V + kTriQuad - 1) / kTriQuad; }
 
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double x) {
-  const unsigned long long v = (unsigned long long)__double_as_longlong(x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, 0xf, 0xf, false);
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
 __device__ __forceinline__ double quad_sum(double x) {
   x += dpp_f64<0xb1>(x);  // quad_perm [1, 0, 3, 2]
   x += dpp_f64<0x4e>(x);  // quad_perm [2, 3, 0, 1]
