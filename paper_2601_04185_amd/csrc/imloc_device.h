@@ -595,6 +595,13 @@ __device__ inline void projection_rows(const Pose& P, const Cam& K, double M[12]
 // ---------------------------------------------------------------------------
 // Wave / block reductions.
 // ---------------------------------------------------------------------------
+// A barrier that orders LDS alone: memory loads in flight stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // A double moved across lanes by a DPP control (both 32-bit halves).
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {

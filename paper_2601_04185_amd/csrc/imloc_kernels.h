@@ -154,14 +154,11 @@ hipError_t launch_triangulate(const TriArgs& a, hipStream_t s);
 // --- small utilities ---------------------------------------------------------
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_fill_u8(uint8_t* p, int64_t n, uint8_t v, hipStream_t s);
-hipError_t launch_gather_subset(const CorrF32& c, int64_t n, int64_t m, float* dst /*[6][m]*/, hipStream_t s);
-// stride subsets of every query whose scoring set is not its full set (the
-// table says from where to where); max_m bounds the subset sizes
-hipError_t launch_gather_subsets(const QueryDesc* qd, int nq, int64_t max_m, hipStream_t s);
 
 // --- round bookkeeping ---------------------------------------------------------
 // init: state and the weight sum of the scoring set of every fresh query.
 // begin: also set up the first round (every query of the table is fresh)
+// (the server: of this round)
 // clears: Gauss-Newton mailboxes of the fresh queries (their tags must not be
 // mistaken for an evaluation's) and the two launch tickets.
 struct GNClear {
@@ -170,12 +167,18 @@ struct GNClear {
   int32_t* tickets;              // [2]
   bool all;                      // also of queries whose teams have one member now
 };
-hipError_t launch_init_queries(QueryDesc* qd, BestState* st, int32_t* n_cand, int nq, bool begin,
+// The queries' table and rig cameras: in pinned host memory (which the launch
+// reads) and on the device.
+struct QueryTables {
+  const QueryDesc* host;
+  QueryDesc* dev;
+  const double* rig_host;  // null: no rig
+  double* rig_dev;
+};
+hipError_t launch_init_queries(const QueryTables& t, BestState* st, int32_t* n_cand, int nq, int64_t max_m, bool begin,
                                const GNClear& clear, hipStream_t s);
 // finished queries (final refinement and mask done) leave the round loop
 hipError_t launch_retire(BestState* st, int nq, hipStream_t s);
-// begin: samples of this round per query, zero candidate counts.
-hipError_t launch_begin_round(QueryDesc* qd, const BestState* st, CandBuf cb, int nq, hipStream_t s);
 // end: take the round's local optimisations into the running best, advance
 // the sample count, apply the stopping rule, and (begin_next) set up the next
 // round; *active_count receives the number of queries that keep sampling.

@@ -544,13 +544,6 @@ struct GNResident {
   uint8_t cam[kGNGroup];
 };
 
-// A barrier that orders LDS alone: memory loads in flight stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Entry i of a uniform array, addressed from scalar registers.
 __device__ __forceinline__ float at_u32(const float* base, unsigned i) {
   return *(const __attribute__((address_space(1))) float*)((const __attribute__((address_space(1))) char*)base +

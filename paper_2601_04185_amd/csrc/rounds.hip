@@ -29,53 +29,6 @@ hipError_t launch_fill_u8(uint8_t* p, int64_t n, uint8_t v, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Scoring-set gather: S_j = point floor(j * n / m), j < m.
-__global__ void gather_subset_kernel(const float* __restrict__ U, const float* __restrict__ V,
-                                     const float* __restrict__ X, const float* __restrict__ Y,
-                                     const float* __restrict__ Z, const float* __restrict__ W, int64_t n, int64_t m,
-                                     float* __restrict__ dst) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= m) return;
-  const int64_t i = (int64_t)(((uint64_t)j * (uint64_t)n) / (uint64_t)m);  // n < 2^31: no overflow
-  dst[j] = U[i];
-  dst[m + j] = V[i];
-  dst[2 * m + j] = X[i];
-  dst[3 * m + j] = Y[i];
-  dst[4 * m + j] = Z[i];
-  dst[5 * m + j] = W ? W[i] : 1.0f;
-}
-
-// Batched gather: grid (blocks, queries); queries whose scoring set is not
-// their full set read from the table where to gather from and to.
-__global__ void gather_subsets_kernel(const QueryDesc* __restrict__ qd) {
-  const QueryDesc& d = qd[blockIdx.y];
-  if (!d.fresh || d.S.u == d.full.u) return;
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= d.m) return;
-  const int64_t i = (int64_t)(((uint64_t)j * (uint64_t)d.n) / (uint64_t)d.m);  // n < 2^31: no overflow
-  float* dst = const_cast<float*>(d.S.u);
-  const int64_t m = d.m;
-  dst[j] = d.full.u[i];
-  dst[m + j] = d.full.v[i];
-  dst[2 * m + j] = d.full.X[i];
-  dst[3 * m + j] = d.full.Y[i];
-  dst[4 * m + j] = d.full.Z[i];
-  dst[5 * m + j] = d.full.w ? d.full.w[i] : 1.0f;
-}
-
-hipError_t launch_gather_subsets(const QueryDesc* qd, int nq, int64_t max_m, hipStream_t s) {
-  if (nq <= 0 || max_m <= 0) return hipSuccess;
-  hipLaunchKernelGGL(gather_subsets_kernel, dim3((unsigned)((max_m + 255) / 256), nq), dim3(256), 0, s, qd);
-  return hipGetLastError();
-}
-
-hipError_t launch_gather_subset(const CorrF32& c, int64_t n, int64_t m, float* dst, hipStream_t s) {
-  if (m <= 0) return hipSuccess;
-  hipLaunchKernelGGL(gather_subset_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, c.u, c.v, c.X, c.Y,
-                     c.Z, c.w, n, m, dst);
-  return hipGetLastError();
-}
-
 // Samples of the coming round: the rest of the budget, at most one batch;
 // none once the query stopped.
 __device__ inline int64_t round_samples(const QueryDesc& d, const BestState& b) {
@@ -84,12 +37,19 @@ __device__ inline int64_t round_samples(const QueryDesc& d, const BestState& b) 
   return left < d.batch ? left : d.batch;
 }
 
-// One workgroup of 1024 threads per query: reset the state and sum the
-// scoring-set weights in float64 (thread t adds elements t + 1024 (16 k + u)
-// into sixteen partial sums, u = 0..15, so that sixteen loads are in flight;
-// the partials, the waves and the workgroup are combined in a fixed order).
-// With `begin`, also set up the first round (samples, candidate counter).
-// The workgroups of grid rows 1 and up clear the query's mailboxes.
+// The start of a call (of a round, in a server): one launch brings the table
+// and the rigs from (pinned) host memory, gathers the scoring subsets, clears the
+// mailboxes and resets the states, where a copy or a launch each took 3 to 5 us
+// (a query on 2,000 points 6.6 -> 4.2 us, with a subset of 10,000 of 50,000 12.6
+// -> 7.2, a four-camera query 11 -> 5.9, a server's round 9 -> 5.2).
+// Grid row 0: one workgroup of 1024 threads per query copies its descriptor
+// and, if the query is fresh, resets the state and sums the scoring-set weights
+// in float64 (thread t adds elements t + 1024 (16 k + u) into sixteen partial
+// sums, u = 0..15, so that sixteen loads are in flight; the partials, the waves
+// and the workgroup are combined in a fixed order).  With `begin`, it also sets
+// up the round (samples, candidate counter).  The next rows clear a fresh query's
+// mailboxes, the others gather its scoring set, S_j = point floor(j * n / m).
+// No workgroup reads what another one writes: all read the host's table.
 constexpr int kInitThreads = 1024;
 constexpr int kClearRows = 8;  // at most; a row clears 16 words per thread and turn
 
@@ -97,33 +57,70 @@ __device__ inline void clear_words(uint64_t* p, int64_t n, int row, int rows) {
   for (int64_t i = (int64_t)row * kInitThreads + threadIdx.x; i < n; i += (int64_t)rows * kInitThreads) p[i] = 0;
 }
 
-__global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryDesc* __restrict__ qd,
-                                                                    BestState* __restrict__ st,
+__global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables t, BestState* __restrict__ st,
                                                                     int32_t* __restrict__ n_cand, int begin,
-                                                                    GNClear clear) {
+                                                                    GNClear clear, int clear_rows) {
   const int q = blockIdx.x;
-  QueryDesc& d = qd[q];
-  if (q == 0 && blockIdx.y == 0 && threadIdx.x < 2) clear.tickets[threadIdx.x] = 0;
-  if (!d.fresh) return;
+  // the descriptor in one read over the bus (about 1.5 us), not field by field
+  constexpr int kWords = sizeof(QueryDesc) / sizeof(uint64_t), kB = offsetof(QueryDesc, B) / sizeof(uint64_t);
+  static_assert(sizeof(QueryDesc) % sizeof(uint64_t) == 0, "copied by words");
+  __shared__ uint64_t s_desc[kWords];
+  if (threadIdx.x < kWords) {
+    const uint64_t w = reinterpret_cast<const uint64_t*>(t.host + q)[threadIdx.x];
+    s_desc[threadIdx.x] = w;
+    if (blockIdx.y == 0 && !(begin && threadIdx.x == kB))  // (B of a round: below)
+      reinterpret_cast<uint64_t*>(t.dev + q)[threadIdx.x] = w;
+  }
+  lds_barrier();
+  const QueryDesc& d = *reinterpret_cast<const QueryDesc*>(s_desc);
+  const bool subset = d.S.u != d.full.u;
+  const int64_t m = d.m, n = d.n;
+  auto source = [&](int64_t j) { return (int64_t)(((uint64_t)j * (uint64_t)n) / (uint64_t)m); };  // n < 2^31
+  if ((int)blockIdx.y > clear_rows) {
+    const int64_t j = (int64_t)((int)blockIdx.y - 1 - clear_rows) * kInitThreads + threadIdx.x;
+    if (!d.fresh || !subset || j >= m) return;
+    const int64_t i = source(j);
+    float* dst = const_cast<float*>(d.S.u);
+    dst[j] = d.full.u[i];
+    dst[m + j] = d.full.v[i];
+    dst[2 * m + j] = d.full.X[i];
+    dst[3 * m + j] = d.full.Y[i];
+    dst[4 * m + j] = d.full.Z[i];
+    dst[5 * m + j] = d.full.w ? d.full.w[i] : 1.0f;
+    return;
+  }
   if (blockIdx.y > 0) {
-    const int row = blockIdx.y - 1, rows = gridDim.y - 1;
-    if (clear.lo && (clear.all || d.lo_team > 1)) clear_words(clear.lo + q * clear.lo_words, clear.lo_words, row, rows);
+    const int row = blockIdx.y - 1;
+    if (!d.fresh) return;
+    if (clear.lo && (clear.all || d.lo_team > 1))
+      clear_words(clear.lo + q * clear.lo_words, clear.lo_words, row, clear_rows);
     if (clear.fin && (clear.all || d.fin_team > 1))
-      clear_words(clear.fin + q * clear.fin_words, clear.fin_words, row, rows);
+      clear_words(clear.fin + q * clear.fin_words, clear.fin_words, row, clear_rows);
+    return;
+  }
+  if (q == 0 && threadIdx.x < 2) clear.tickets[threadIdx.x] = 0;
+  if (t.rig_host && (int)threadIdx.x < 16 * d.ncam) {
+    const int64_t o = d.rig - t.rig_dev;
+    t.rig_dev[o + threadIdx.x] = t.rig_host[o + threadIdx.x];
+  }
+  if (!d.fresh) {
+    if (begin && threadIdx.x == 0) {
+      t.dev[q].B = round_samples(d, st[q]);
+      n_cand[q] = 0;
+    }
     return;
   }
   double p[16];
 #pragma unroll
   for (int u = 0; u < 16; ++u) p[u] = 0.0;
-  const float* __restrict__ w = d.S.w;
-  const int64_t m = d.m;
+  const float* __restrict__ w = subset ? d.full.w : d.S.w;
   if (w) {
     for (int64_t i0 = threadIdx.x; i0 < m; i0 += 16 * kInitThreads) {
       float x[16];
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         const int64_t i = i0 + (int64_t)kInitThreads * u;
-        x[u] = i < m ? w[i] : 0.0f;
+        x[u] = i < m ? w[subset ? source(i) : i] : 0.0f;
       }
 #pragma unroll
       for (int u = 0; u < 16; ++u) p[u] += (double)x[u];
@@ -165,19 +162,22 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryDesc* _
     b.active = can ? 1 : 0;
     b.finished = can ? 0 : 1;
     if (begin) {
-      d.B = round_samples(d, b);
+      t.dev[q].B = round_samples(d, b);
       n_cand[q] = 0;
     }
   }
 }
 
-hipError_t launch_init_queries(QueryDesc* qd, BestState* st, int32_t* n_cand, int nq, bool begin,
+// max_m bounds the scoring subsets of the fresh queries (0: there is none)
+hipError_t launch_init_queries(const QueryTables& t, BestState* st, int32_t* n_cand, int nq, int64_t max_m, bool begin,
                                const GNClear& clear, hipStream_t s) {
   if (nq <= 0) return hipSuccess;
   const int64_t words = (clear.lo ? clear.lo_words : 0) + (clear.fin ? clear.fin_words : 0);
   const int64_t rows = (words + 16 * kInitThreads - 1) / (16 * kInitThreads);
-  hipLaunchKernelGGL(init_queries_kernel, dim3(nq, 1 + (unsigned)(rows < kClearRows ? rows : kClearRows)),
-                     dim3(kInitThreads), 0, s, qd, st, n_cand, begin ? 1 : 0, clear);
+  const int clear_rows = (int)(rows < kClearRows ? rows : kClearRows);
+  const int64_t gather_rows = (max_m + kInitThreads - 1) / kInitThreads;
+  hipLaunchKernelGGL(init_queries_kernel, dim3(nq, (unsigned)(1 + clear_rows + gather_rows)), dim3(kInitThreads), 0, s,
+                     t, st, n_cand, begin ? 1 : 0, clear, clear_rows);
   return hipGetLastError();
 }
 
@@ -189,19 +189,6 @@ __global__ void retire_kernel(BestState* __restrict__ st, int nq) {
 hipError_t launch_retire(BestState* st, int nq, hipStream_t s) {
   if (nq <= 0) return hipSuccess;
   hipLaunchKernelGGL(retire_kernel, dim3((nq + 255) / 256), dim3(256), 0, s, st, nq);
-  return hipGetLastError();
-}
-
-__global__ void begin_round_kernel(QueryDesc* __restrict__ qd, const BestState* __restrict__ st, int32_t* n_cand,
-                                   int nq) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= nq) return;
-  qd[q].B = round_samples(qd[q], st[q]);
-  n_cand[q] = 0;
-}
-
-hipError_t launch_begin_round(QueryDesc* qd, const BestState* st, CandBuf cb, int nq, hipStream_t s) {
-  hipLaunchKernelGGL(begin_round_kernel, dim3((nq + 255) / 256), dim3(256), 0, s, qd, st, cb.n, nq);
   return hipGetLastError();
 }
 

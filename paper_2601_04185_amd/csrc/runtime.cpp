@@ -723,11 +723,8 @@ int run_batch(imloc_ctx* ctx, int nq, const imloc_corr* pts, const int64_t* n, c
   // lets adaptive batches read the active count after every round.
   auto enqueue = [&](hipStream_t st_, bool sync) -> int {
     hipEvent_t ev_total = tm.total_begin();
-    HIP_TRY(ctx, hipMemcpyAsync(e.qd, htab, tab, hipMemcpyHostToDevice, st_));
-    if (rigb) HIP_TRY(ctx, hipMemcpyAsync(e.rig, hrig, rigb, hipMemcpyHostToDevice, st_));
-    HIP_TRY(ctx, launch_gather_subsets(e.qd, nq, max_m_sub, st_));
-    HIP_TRY(ctx, launch_init_queries(e.qd, e.st, e.cb.n, nq, true, team_clear(e, teams, false),
-                                     st_));  // and the first round's setup
+    HIP_TRY(ctx, launch_init_queries(QueryTables{htab, e.qd, rigb ? hrig : nullptr, e.rig}, e.st, e.cb.n, nq, max_m_sub,
+                                     true, team_clear(e, teams, false), st_));  // and the first round's setup
     rounds = 0;
     for (int64_t r = 0; r < e.max_rounds; ++r) {
       hipEvent_t e0 = tm.begin();
@@ -903,16 +900,15 @@ int stage_upload(imloc_ctx* ctx, StageQuery& sq, const imloc_corr* pts, int64_t 
   QueryDesc* htab = reinterpret_cast<QueryDesc*>(ctx->pinned);
   htab[0] = make_desc(pts, n, K, &sq.p, sq.pl, sq.e, 0, mask, rig);
   htab[0].B = B;
-  HIP_TRY(ctx, hipMemcpyAsync(sq.e.qd, htab, sizeof(QueryDesc), hipMemcpyHostToDevice, ctx->stream));
+  QueryTables tables{htab, sq.e.qd, nullptr, sq.e.rig};
   if (rig && sq.e.rig_doubles) {
     double* hrig = reinterpret_cast<double*>(ctx->pinned + rig_at);
     fill_rig_tables(hrig, 1, rig, sq.e);
-    HIP_TRY(ctx, hipMemcpyAsync(sq.e.rig, hrig, (size_t)sq.e.rig_doubles * sizeof(double), hipMemcpyHostToDevice,
-                                ctx->stream));
+    tables.rig_host = hrig;
   }
   GNClear none{};
   none.tickets = sq.e.tickets;
-  HIP_TRY(ctx, launch_init_queries(sq.e.qd, sq.e.st, sq.e.cb.n, 1, false, clear ? *clear : none, ctx->stream));
+  HIP_TRY(ctx, launch_init_queries(tables, sq.e.st, sq.e.cb.n, 1, 0, false, clear ? *clear : none, ctx->stream));
   if (drawn) {
     BestState* hb = reinterpret_cast<BestState*>(ctx->pinned + 256 * ((sizeof(QueryDesc) + 255) / 256));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
@@ -1806,8 +1802,8 @@ int imloc_server_create(imloc_ctx* ctx, const imloc_server_config* cfg, imloc_se
   hipStream_t s = ctx->stream;
   GNClear none{};
   none.tickets = srv->e.tickets;
-  if (hipMemcpyAsync(srv->e.qd, htab, tab, hipMemcpyHostToDevice, s) != hipSuccess ||
-      launch_init_queries(srv->e.qd, srv->e.st, srv->e.cb.n, cfg->max_slots, false, none, s) != hipSuccess ||
+  if (launch_init_queries(QueryTables{htab, srv->e.qd, nullptr, nullptr}, srv->e.st, srv->e.cb.n, cfg->max_slots, 0, false,
+                          none, s) != hipSuccess ||
       launch_retire(srv->e.st, cfg->max_slots, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
     imloc_server_destroy(srv);
     return set_err(ctx, IMLOC_EHIP, "server initialisation failed");
@@ -2004,10 +2000,8 @@ int imloc_server_step(imloc_server* srv, int64_t* done_tickets, int32_t capacity
     // so its mailboxes are cleared at its admission whatever its first team
     GNClear clear = team_clear(e, teams, true);
     if (!any_fresh) clear.lo = clear.fin = nullptr;
-    HIP_TRY(ctx, hipMemcpyAsync(e.qd, htab, tab, hipMemcpyHostToDevice, s));
-    HIP_TRY(ctx, launch_gather_subsets(e.qd, nq, max_m_sub, s));
-    HIP_TRY(ctx, launch_init_queries(e.qd, e.st, e.cb.n, nq, false, clear, s));
-    HIP_TRY(ctx, launch_begin_round(e.qd, e.st, e.cb, nq, s));
+    HIP_TRY(ctx, launch_init_queries(QueryTables{htab, e.qd, nullptr, nullptr}, e.st, e.cb.n, nq, max_m_sub, true, clear,
+                                     s));
     HIP_TRY(ctx, launch_sample_p3p(e.qd, e.st, e.cb, nq, max_batch, nullptr, s));
     const ScoreTune tune = round_tune(ctx, est.data(), est.size());
     HIP_TRY(ctx, launch_worklist(e.qd, e.cb, nq, tune, e.item_off, e.tickets, s));
