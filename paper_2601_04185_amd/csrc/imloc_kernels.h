@@ -101,7 +101,7 @@ struct CandBuf {
   uint32_t* cnt;     // [slots] inlier count (accumulated by scoring)
   uint64_t* gain;    // [slots] sum of w (1 - r^2 / tau^2) over inliers, fixed point 2^-32 (accumulated)
   int32_t* n;        // [queries] candidates of the current round
-  int32_t* sel_done; // [queries] selection workgroups finished (zeroed by the work-list kernel)
+  int32_t* sel_done; // [queries] selection workgroups finished (zeroed before the round)
 };
 
 // --- lift ------------------------------------------------------------------
@@ -160,7 +160,7 @@ hipError_t launch_fill_u8(uint8_t* p, int64_t n, uint8_t v, hipStream_t s);
 // begin: also set up the first round (every query of the table is fresh)
 // (the server: of this round)
 // clears: Gauss-Newton mailboxes of the fresh queries (their tags must not be
-// mistaken for an evaluation's) and the two launch tickets.
+// mistaken for an evaluation's), the two launch tickets and the selection counters.
 struct GNClear {
   uint64_t *lo, *fin;            // mailboxes (null: none)
   int64_t lo_words, fin_words;   // per query
@@ -175,16 +175,17 @@ struct QueryTables {
   const double* rig_host;  // null: no rig
   double* rig_dev;
 };
-hipError_t launch_init_queries(const QueryTables& t, BestState* st, int32_t* n_cand, int nq, int64_t max_m, bool begin,
+hipError_t launch_init_queries(const QueryTables& t, BestState* st, CandBuf cb, int nq, int64_t max_m, bool begin,
                                const GNClear& clear, hipStream_t s);
 // finished queries (final refinement and mask done) leave the round loop
 hipError_t launch_retire(BestState* st, int nq, hipStream_t s);
 // end: take the round's local optimisations into the running best, advance
 // the sample count, apply the stopping rule, and (begin_next) set up the next
-// round; *active_count receives the number of queries that keep sampling.
+// round (its tickets and selection counters too); *active_count (device or
+// pinned host memory) receives the number of queries that keep sampling.
 hipError_t launch_round_end(QueryDesc* qd, CandBuf cb, const int32_t* sel, const int32_t* n_sel,
                             const double* lo_pose, const double* lo_cost, const int64_t* lo_count, int nq, int kmax,
-                            BestState* st, int32_t* active_count, bool begin_next, hipStream_t s);
+                            BestState* st, int32_t* active_count, int32_t* tickets, bool begin_next, hipStream_t s);
 
 // --- sampling + P3P ----------------------------------------------------------
 // Samples [drawn, drawn + B) of every query; max_b bounds B.
@@ -203,9 +204,8 @@ struct ScoreTune {
   int blocks;   // workgroups of the launch (each strides over the work list)
   int pts;      // correspondences per float32 work item (512, 1024, 2048 or 4096)
 };
-// (also zeroes the Gauss-Newton tickets of the round)
-hipError_t launch_worklist(const QueryDesc* qd, CandBuf cb, int nq, ScoreTune tune, int64_t* item_off,
-                           int32_t* tickets, hipStream_t s);
+// (nothing for one query)
+hipError_t launch_worklist(const QueryDesc* qd, CandBuf cb, int nq, ScoreTune tune, int64_t* item_off, hipStream_t s);
 hipError_t launch_score(const QueryDesc* qd, CandBuf cb, BestState* st, int nq, const int64_t* item_off,
                         ScoreTune tune, int precision, hipStream_t s);
 // truncated cost of the candidates of query 0: count and msac outputs

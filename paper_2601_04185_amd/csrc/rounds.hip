@@ -58,7 +58,7 @@ __device__ inline void clear_words(uint64_t* p, int64_t n, int row, int rows) {
 }
 
 __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables t, BestState* __restrict__ st,
-                                                                    int32_t* __restrict__ n_cand, int begin,
+                                                                    CandBuf cb, int begin,
                                                                     GNClear clear, int clear_rows) {
   const int q = blockIdx.x;
   // the descriptor in one read over the bus (about 1.5 us), not field by field
@@ -99,6 +99,7 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
     return;
   }
   if (q == 0 && threadIdx.x < 2) clear.tickets[threadIdx.x] = 0;
+  if (threadIdx.x == 2) cb.sel_done[q] = 0;
   if (t.rig_host && (int)threadIdx.x < 16 * d.ncam) {
     const int64_t o = d.rig - t.rig_dev;
     t.rig_dev[o + threadIdx.x] = t.rig_host[o + threadIdx.x];
@@ -106,7 +107,7 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
   if (!d.fresh) {
     if (begin && threadIdx.x == 0) {
       t.dev[q].B = round_samples(d, st[q]);
-      n_cand[q] = 0;
+      cb.n[q] = 0;
     }
     return;
   }
@@ -163,13 +164,13 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
     b.finished = can ? 0 : 1;
     if (begin) {
       t.dev[q].B = round_samples(d, b);
-      n_cand[q] = 0;
+      cb.n[q] = 0;
     }
   }
 }
 
 // max_m bounds the scoring subsets of the fresh queries (0: there is none)
-hipError_t launch_init_queries(const QueryTables& t, BestState* st, int32_t* n_cand, int nq, int64_t max_m, bool begin,
+hipError_t launch_init_queries(const QueryTables& t, BestState* st, CandBuf cb, int nq, int64_t max_m, bool begin,
                                const GNClear& clear, hipStream_t s) {
   if (nq <= 0) return hipSuccess;
   const int64_t words = (clear.lo ? clear.lo_words : 0) + (clear.fin ? clear.fin_words : 0);
@@ -177,7 +178,7 @@ hipError_t launch_init_queries(const QueryTables& t, BestState* st, int32_t* n_c
   const int clear_rows = (int)(rows < kClearRows ? rows : kClearRows);
   const int64_t gather_rows = (max_m + kInitThreads - 1) / kInitThreads;
   hipLaunchKernelGGL(init_queries_kernel, dim3(nq, (unsigned)(1 + clear_rows + gather_rows)), dim3(kInitThreads), 0, s,
-                     t, st, n_cand, begin ? 1 : 0, clear, clear_rows);
+                     t, st, cb, begin ? 1 : 0, clear, clear_rows);
   return hipGetLastError();
 }
 
@@ -217,7 +218,8 @@ __global__ __launch_bounds__(1024) void round_end_kernel(QueryDesc* __restrict__
                                                          const double* __restrict__ lo_cost,
                                                          const int64_t* __restrict__ lo_count, int nq, int kmax,
                                                          BestState* __restrict__ st, int32_t* __restrict__ active_count,
-                                                         int begin_next) {
+                                                         int32_t* __restrict__ tickets, int begin_next) {
+  if (begin_next && threadIdx.x < 2) tickets[threadIdx.x] = 0;
   long long act = 0;
   for (int q = threadIdx.x; q < nq; q += blockDim.x) {
     QueryDesc& d = qd[q];
@@ -257,6 +259,7 @@ __global__ __launch_bounds__(1024) void round_end_kernel(QueryDesc* __restrict__
     if (begin_next) {
       d.B = round_samples(d, b);
       cb.n[q] = 0;
+      cb.sel_done[q] = 0;
     }
   }
   act = wave_sum(act);
@@ -272,9 +275,9 @@ __global__ __launch_bounds__(1024) void round_end_kernel(QueryDesc* __restrict__
 
 hipError_t launch_round_end(QueryDesc* qd, CandBuf cb, const int32_t* sel, const int32_t* n_sel,
                             const double* lo_pose, const double* lo_cost, const int64_t* lo_count, int nq, int kmax,
-                            BestState* st, int32_t* active_count, bool begin_next, hipStream_t s) {
+                            BestState* st, int32_t* active_count, int32_t* tickets, bool begin_next, hipStream_t s) {
   hipLaunchKernelGGL(round_end_kernel, dim3(1), dim3(1024), 0, s, qd, cb, sel, n_sel, lo_pose, lo_cost, lo_count, nq,
-                     kmax, st, active_count, begin_next ? 1 : 0);
+                     kmax, st, active_count, tickets, begin_next ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -720,17 +720,30 @@ int run_batch(imloc_ctx* ctx, int nq, const imloc_corr* pts, const int64_t* n, c
   const ScoreTune tune = round_tune(ctx, est.data(), est.size());
   // The whole pipeline of a batch, enqueued on stream `st_`: table upload,
   // rounds, final refinement, mask, readback into pinned memory.  `sync`
-  // lets adaptive batches read the active count after every round.
+  // lets adaptive batches read the active count, which the end of a round
+  // writes to pinned memory, after every round.  A query alone mostly ends with
+  // its first round, so its refinement is enqueued behind that round before the
+  // count is known (it does nothing for a query that goes on): 13 us less than
+  // a copy, the host's answer and then the launch.
   auto enqueue = [&](hipStream_t st_, bool sync) -> int {
     hipEvent_t ev_total = tm.total_begin();
-    HIP_TRY(ctx, launch_init_queries(QueryTables{htab, e.qd, rigb ? hrig : nullptr, e.rig}, e.st, e.cb.n, nq, max_m_sub,
+    HIP_TRY(ctx, launch_init_queries(QueryTables{htab, e.qd, rigb ? hrig : nullptr, e.rig}, e.st, e.cb, nq, max_m_sub,
                                      true, team_clear(e, teams, false), st_));  // and the first round's setup
+    auto finish = [&]() -> int {
+      hipEvent_t e4 = tm.begin();
+      HIP_TRY(ctx, launch_refine(e.qd, e.st, nullptr, nq, teams.fin, e.in_set, e.fin_pose, e.fin_cost, e.any_rig, true,
+                                 st_));
+      tm.end(kStRefine, e4);
+      tm.total_end(ev_total);
+      HIP_TRY(ctx, hipMemcpyAsync(hst, e.st, result_bytes(nq), hipMemcpyDeviceToHost, st_));
+      return IMLOC_OK;
+    };
     rounds = 0;
     for (int64_t r = 0; r < e.max_rounds; ++r) {
       hipEvent_t e0 = tm.begin();
       if (e.any_single) HIP_TRY(ctx, launch_sample_p3p(e.qd, e.st, e.cb, nq, e.max_batch, nullptr, st_));
       if (e.any_rig) HIP_TRY(ctx, launch_sample_gp3p(e.qd, e.st, e.cb, nq, e.max_batch, nullptr, st_));
-      HIP_TRY(ctx, launch_worklist(e.qd, e.cb, nq, tune, e.item_off, e.tickets, st_));
+      HIP_TRY(ctx, launch_worklist(e.qd, e.cb, nq, tune, e.item_off, st_));
       tm.end(kStSample, e0);
       hipEvent_t e1 = tm.begin();  // the scoring span holds the scoring kernel alone
       HIP_TRY(ctx, launch_score(e.qd, e.cb, e.st, nq, e.item_off, tune, 0, st_));
@@ -742,23 +755,25 @@ int run_batch(imloc_ctx* ctx, int nq, const imloc_corr* pts, const int64_t* n, c
       HIP_TRY(ctx, launch_lo(e.qd, e.st, e.cb, e.sel, e.n_sel, nullptr, nq, e.kmax, teams.lo, e.lo_pose, e.lo_cost,
                              e.lo_count, e.any_rig, st_));
       HIP_TRY(ctx, launch_round_end(e.qd, e.cb, e.sel, e.n_sel, e.lo_pose, e.lo_cost, e.lo_count, nq, e.kmax, e.st,
-                                    e.active_count, true, st_));
+                                    sync ? hact : e.active_count, e.tickets, true, st_));
       tm.end(kStLO, e3);
       ++rounds;
       if (sync) {
-        HIP_TRY(ctx, hipMemcpyAsync(hact, e.active_count, sizeof(int32_t), hipMemcpyDeviceToHost, st_));
-        int rcw = wait_stream(ctx, st_);
+        HIP_TRY(ctx, hipEventRecord(ctx->done_ev, st_));
+        const bool ahead = nq == 1 && r == 0 && !ctx->timing;
+        if (ahead) {
+          const int rcf = finish();
+          if (rcf) return rcf;
+        }
+        int rcw = wait_event(ctx, ctx->done_ev);
         if (rcw) return rcw;
-        if (*hact == 0) break;
+        if (*static_cast<volatile int32_t*>(hact) == 0) {
+          if (ahead) return IMLOC_OK;
+          break;
+        }
       }
     }
-    hipEvent_t e4 = tm.begin();
-    HIP_TRY(ctx, launch_refine(e.qd, e.st, nullptr, nq, teams.fin, e.in_set, e.fin_pose, e.fin_cost, e.any_rig, true,
-                               st_));
-    tm.end(kStRefine, e4);
-    tm.total_end(ev_total);
-    HIP_TRY(ctx, hipMemcpyAsync(hst, e.st, result_bytes(nq), hipMemcpyDeviceToHost, st_));
-    return IMLOC_OK;
+    return finish();
   };
 
   if (may_capture && ctx->graphs && ctx->gstream && e.all_fixed && !ctx->timing) {
@@ -908,7 +923,7 @@ int stage_upload(imloc_ctx* ctx, StageQuery& sq, const imloc_corr* pts, int64_t 
   }
   GNClear none{};
   none.tickets = sq.e.tickets;
-  HIP_TRY(ctx, launch_init_queries(tables, sq.e.st, sq.e.cb.n, 1, 0, false, clear ? *clear : none, ctx->stream));
+  HIP_TRY(ctx, launch_init_queries(tables, sq.e.st, sq.e.cb, 1, 0, false, clear ? *clear : none, ctx->stream));
   if (drawn) {
     BestState* hb = reinterpret_cast<BestState*>(ctx->pinned + 256 * ((sizeof(QueryDesc) + 255) / 256));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
@@ -1455,7 +1470,6 @@ int imloc_rig_score(imloc_ctx* ctx, const imloc_corr* pts, int64_t n, const imlo
   HIP_TRY(ctx, launch_set_candidates(sq.e.qd, poses, np, sq.e.cb, s));
   const std::pair<int64_t, int64_t> est1{np, est_points(sq.pl)};
   const ScoreTune tune = round_tune(ctx, &est1, 1);
-  HIP_TRY(ctx, launch_worklist(sq.e.qd, sq.e.cb, 1, tune, sq.e.item_off, sq.e.tickets, s));
   HIP_TRY(ctx, launch_score(sq.e.qd, sq.e.cb, sq.e.st, 1, sq.e.item_off, tune, precision, s));
   HIP_TRY(ctx, launch_candidate_costs(sq.e.qd, sq.e.st, sq.e.cb, np, count, msac, s));
   return IMLOC_OK;
@@ -1499,7 +1513,6 @@ int imloc_score(imloc_ctx* ctx, const imloc_corr* pts, int64_t n, const imloc_ca
   HIP_TRY(ctx, launch_set_candidates(sq.e.qd, poses, np, sq.e.cb, s));
   const std::pair<int64_t, int64_t> est1{np, est_points(sq.pl)};
   const ScoreTune tune = round_tune(ctx, &est1, 1);
-  HIP_TRY(ctx, launch_worklist(sq.e.qd, sq.e.cb, 1, tune, sq.e.item_off, sq.e.tickets, s));
   HIP_TRY(ctx, launch_score(sq.e.qd, sq.e.cb, sq.e.st, 1, sq.e.item_off, tune, precision, s));
   HIP_TRY(ctx, launch_candidate_costs(sq.e.qd, sq.e.st, sq.e.cb, np, count, msac, s));
   return IMLOC_OK;
@@ -1535,7 +1548,6 @@ int imloc_select_top_k(imloc_ctx* ctx, const imloc_corr* pts, int64_t n, const i
   HIP_TRY(ctx, launch_set_candidates(sq.e.qd, poses, np, sq.e.cb, s));
   const std::pair<int64_t, int64_t> est1{np, est_points(sq.pl)};
   const ScoreTune tune = round_tune(ctx, &est1, 1);
-  HIP_TRY(ctx, launch_worklist(sq.e.qd, sq.e.cb, 1, tune, sq.e.item_off, sq.e.tickets, s));
   HIP_TRY(ctx, launch_score(sq.e.qd, sq.e.cb, sq.e.st, 1, sq.e.item_off, tune, precision, s));
   HIP_TRY(ctx, launch_select(sq.e.qd, sq.e.st, sq.e.cb, 1, k, std::max<int64_t>(np, 1), sq.e.sel_part, sel, n_sel, s));
   HIP_TRY(ctx, hipStreamSynchronize(s));  // the staging buffer held the gate
@@ -1802,7 +1814,7 @@ int imloc_server_create(imloc_ctx* ctx, const imloc_server_config* cfg, imloc_se
   hipStream_t s = ctx->stream;
   GNClear none{};
   none.tickets = srv->e.tickets;
-  if (launch_init_queries(QueryTables{htab, srv->e.qd, nullptr, nullptr}, srv->e.st, srv->e.cb.n, cfg->max_slots, 0, false,
+  if (launch_init_queries(QueryTables{htab, srv->e.qd, nullptr, nullptr}, srv->e.st, srv->e.cb, cfg->max_slots, 0, false,
                           none, s) != hipSuccess ||
       launch_retire(srv->e.st, cfg->max_slots, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
     imloc_server_destroy(srv);
@@ -2000,17 +2012,17 @@ int imloc_server_step(imloc_server* srv, int64_t* done_tickets, int32_t capacity
     // so its mailboxes are cleared at its admission whatever its first team
     GNClear clear = team_clear(e, teams, true);
     if (!any_fresh) clear.lo = clear.fin = nullptr;
-    HIP_TRY(ctx, launch_init_queries(QueryTables{htab, e.qd, nullptr, nullptr}, e.st, e.cb.n, nq, max_m_sub, true, clear,
+    HIP_TRY(ctx, launch_init_queries(QueryTables{htab, e.qd, nullptr, nullptr}, e.st, e.cb, nq, max_m_sub, true, clear,
                                      s));
     HIP_TRY(ctx, launch_sample_p3p(e.qd, e.st, e.cb, nq, max_batch, nullptr, s));
     const ScoreTune tune = round_tune(ctx, est.data(), est.size());
-    HIP_TRY(ctx, launch_worklist(e.qd, e.cb, nq, tune, e.item_off, e.tickets, s));
+    HIP_TRY(ctx, launch_worklist(e.qd, e.cb, nq, tune, e.item_off, s));
     HIP_TRY(ctx, launch_score(e.qd, e.cb, e.st, nq, e.item_off, tune, 0, s));
     HIP_TRY(ctx, launch_select(e.qd, e.st, e.cb, nq, kmax, 4 * max_batch, e.sel_part, e.sel, e.n_sel, s));
     HIP_TRY(ctx, launch_lo(e.qd, e.st, e.cb, e.sel, e.n_sel, nullptr, nq, kmax, teams.lo, e.lo_pose, e.lo_cost,
                            e.lo_count, false, s));
     HIP_TRY(ctx, launch_round_end(e.qd, e.cb, e.sel, e.n_sel, e.lo_pose, e.lo_cost, e.lo_count, nq, kmax, e.st,
-                                  e.active_count, false, s));
+                                  e.active_count, e.tickets, false, s));
     HIP_TRY(ctx, launch_refine(e.qd, e.st, nullptr, nq, teams.fin, e.in_set, e.fin_pose, e.fin_cost, false, true, s));
     HIP_TRY(ctx, launch_retire(e.st, nq, s));
     // the results block is laid out for all e.nq slots (the table may be shorter)

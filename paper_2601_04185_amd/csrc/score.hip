@@ -94,14 +94,11 @@ __device__ inline ChunkRange chunk_range(const QueryDesc& d, int64_t chunk, int 
 
 
 // Work list: items_q = tiles_q * chunks_q for queries sampling this round;
-// item_off = exclusive prefix, item_off[nq] = total (one workgroup).  Also
-// zeroes the round's selection counters (the selection follows the scoring)
-// and the tickets of its Gauss-Newton launches.
+// item_off = exclusive prefix, item_off[nq] = total (one workgroup).  A round of
+// one query has no list: its scoring counts its items itself (5 us less).
 __global__ __launch_bounds__(1024) void worklist_kernel(const QueryDesc* __restrict__ qd,
                                                         const int32_t* __restrict__ n_cand, int nq, int ct, int pts,
-                                                        int64_t* __restrict__ item_off, int32_t* __restrict__ sel_done,
-                                                        int32_t* __restrict__ tickets) {
-  if (threadIdx.x < 2) tickets[threadIdx.x] = 0;
+                                                        int64_t* __restrict__ item_off) {
   __shared__ long long s[1024];
   const int seg = (nq + 1023) / 1024;
   const int q0 = threadIdx.x * seg, q1 = min(nq, q0 + seg);
@@ -121,7 +118,6 @@ __global__ __launch_bounds__(1024) void worklist_kernel(const QueryDesc* __restr
   long long run = s[threadIdx.x] - sum;
   for (int q = q0; q < q1; ++q) {
     item_off[q] = run;
-    sel_done[q] = 0;
     const QueryDesc& d = qd[q];
     if (d.B > 0) run += (long long)((n_cand[q] + ct - 1) / ct) * chunks_of(d, pts);
   }
@@ -129,9 +125,9 @@ __global__ __launch_bounds__(1024) void worklist_kernel(const QueryDesc* __restr
 }
 
 hipError_t launch_worklist(const QueryDesc* qd, CandBuf cb, int nq, ScoreTune tune, int64_t* item_off,
-                           int32_t* tickets, hipStream_t s) {
-  hipLaunchKernelGGL(worklist_kernel, dim3(1), dim3(1024), 0, s, qd, cb.n, nq, tune.ct, tune.pts, item_off,
-                     cb.sel_done, tickets);
+                           hipStream_t s) {
+  if (nq <= 1) return hipSuccess;
+  hipLaunchKernelGGL(worklist_kernel, dim3(1), dim3(1024), 0, s, qd, cb.n, nq, tune.ct, tune.pts, item_off);
   return hipGetLastError();
 }
 
@@ -703,7 +699,9 @@ __global__ __launch_bounds__(kScoreBlock, 3) void score_kernel(const QueryDesc* 
     s_tab.gain[threadIdx.x] = 0;
   }
   __syncthreads();
-  const int64_t total = item_off[nq];
+  const int64_t total = nq > 1     ? item_off[nq]
+                        : qd[0].B > 0 ? (int64_t)((ncand[0] + CT - 1) / CT) * chunks_of(qd[0], pts)
+                                      : 0;
   for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
     // the query owning item w (the last q with item_off[q] <= w): 64 probes a step
     int lo = 0;
@@ -715,7 +713,7 @@ __global__ __launch_bounds__(kScoreBlock, 3) void score_kernel(const QueryDesc* 
     }
     const QueryDesc& d = qd[lo];
     const int64_t chunks = chunks_of(d, pts);
-    const int64_t local = w - item_off[lo];
+    const int64_t local = nq > 1 ? w - item_off[lo] : w;
     const int64_t tile = local / chunks, chunk = local - tile * chunks;
     const int nc = ncand[lo];
     if (d.precision == 0)
