@@ -914,7 +914,14 @@ __attribute__((amdgpu_waves_per_eu(RES || RIG ? 2 : kGNWavesMany, RES || RIG ? 2
       if (T == 1) break;
       if (!own) {  // a block is complete
         if (tid < kAcc)
-          for (int gi = 0; gi < nb; ++gi) tot += L.in[gi][tid];
+          for (int g0 = 0; g0 < nb; g0 += 8) {  // eight reads in flight, added in order
+            double x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = L.in[g0 + u][tid];  // (kGNInBlock is a multiple of 8)
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+              if (g0 + u < nb) tot += x[u];
+          }
         if (b0 + kGNInBlock >= G) break;
         __syncthreads();  // before its slots are used again
       }
