@@ -30,8 +30,8 @@ __device__ inline void philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, uint
   const uint64_t W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint64_t hi0 = __umul64hi(M0, c0), lo0 = M0 * c0;
-    const uint64_t hi1 = __umul64hi(M1, c2), lo1 = M1 * c2;
+    const unsigned __int128 p0 = (unsigned __int128)M0 * c0, p1 = (unsigned __int128)M1 * c2;
+    const uint64_t hi0 = (uint64_t)(p0 >> 64), lo0 = (uint64_t)p0, hi1 = (uint64_t)(p1 >> 64), lo1 = (uint64_t)p1;
     const uint64_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
     c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
     k0 += W0; k1 += W1;
@@ -214,15 +214,18 @@ __device__ inline bool chol6_solve_packed(const double Hp[21], const double b[6]
 // passed to emit(root).  The interval is split at the critical points, so
 // the cubic is monotone on each of the (at most three) brackets; every
 // bracket with a sign change is shrunk by 24 bisection steps and then
-// polished by 4 Newton steps kept inside it.  The brackets are refined
-// together, branch-free, as independent chains (a lone wave per SIMD is
-// bound by instruction issue, so one shared loop beats three divergent ones).
+// polished by 4 Newton steps kept inside it.  Two lanes share a cubic, as a
+// round that leaves a wave alone on its SIMD is bound by instruction issue: part
+// 0 refines the first two brackets and emits their roots, part 1 the third
+// (branch-free, one shared loop; all three in every lane took 10,000 of the
+// 35,000 cycles of a workgroup, this 7,500).
 __device__ inline double cubic_at(double c0, double c1, double c2, double c3, double x) {
   return ((c3 * x + c2) * x + c1) * x + c0;
 }
 
 template <class Emit>
-__device__ inline void cubic_roots_in(double c0, double c1, double c2, double c3, double lo, double hi, Emit&& emit) {
+__device__ inline void cubic_roots_in(double c0, double c1, double c2, double c3, double lo, double hi, int part,
+                                      Emit&& emit) {
   // critical points: 3 c3 x^2 + 2 c2 x + c1 = 0
   const double qa = 3.0 * c3, qb = 2.0 * c2, qc = c1;
   double x1 = 0.0, x2 = 0.0;
@@ -248,33 +251,35 @@ __device__ inline void cubic_roots_in(double c0, double c1, double c2, double c3
   const double m1 = u1 ? x1 : (u2 ? x2 : hi);
   const double m2 = (u1 && u2) ? x2 : hi;
   const int nb = 1 + (int)u1 + (int)u2;
-  double A[3] = {lo, m1, m2}, B[3] = {m1, m2, hi};
-  bool run[3], neg[3], at_a[3], at_b[3];
+  double A[2] = {part ? m2 : lo, m1}, B[2] = {part ? hi : m1, m2};
+  bool run[2], neg[2], at_a[2], at_b[2];
 #pragma unroll
-  for (int t = 0; t < 3; ++t) {
-    const double fa = cubic_at(c0, c1, c2, c3, A[t]), fb = cubic_at(c0, c1, c2, c3, B[t]);
-    const bool live = t < nb;
-    at_a[t] = live && fa == 0.0;
-    at_b[t] = live && !at_a[t] && fb == 0.0 && t == nb - 1;
-    run[t] = live && !at_a[t] && !at_b[t] && ((fa < 0.0) != (fb < 0.0));
-    neg[t] = fa < 0.0;
+  for (int e = 0; e < 2; ++e) {
+    const int t = part ? 2 : e;
+    const double fa = cubic_at(c0, c1, c2, c3, A[e]), fb = cubic_at(c0, c1, c2, c3, B[e]);
+    const bool live = t < nb && !(part && e);
+    at_a[e] = live && fa == 0.0;
+    at_b[e] = live && !at_a[e] && fb == 0.0 && t == nb - 1;
+    run[e] = live && !at_a[e] && !at_b[e] && ((fa < 0.0) != (fb < 0.0));
+    neg[e] = fa < 0.0;
   }
-  if (run[0] || run[1] || run[2]) {
+  const double first[2] = {A[0], A[1]};
+  if (run[0] || run[1]) {
     for (int it = 0; it < 24; ++it) {
 #pragma unroll
-      for (int t = 0; t < 3; ++t) {
+      for (int t = 0; t < 2; ++t) {
         const double m = 0.5 * (A[t] + B[t]);
         const bool left = (cubic_at(c0, c1, c2, c3, m) < 0.0) == neg[t];
         A[t] = left ? m : A[t];
         B[t] = left ? B[t] : m;
       }
     }
-    double x[3];
+    double x[2];
 #pragma unroll
-    for (int t = 0; t < 3; ++t) x[t] = 0.5 * (A[t] + B[t]);
+    for (int t = 0; t < 2; ++t) x[t] = 0.5 * (A[t] + B[t]);
     for (int it = 0; it < 4; ++it) {
 #pragma unroll
-      for (int t = 0; t < 3; ++t) {
+      for (int t = 0; t < 2; ++t) {
         const double f = cubic_at(c0, c1, c2, c3, x[t]);
         const double df = (qa * x[t] + qb) * x[t] + qc;
         const double xn = df != 0.0 ? x[t] - f / df : x[t];
@@ -282,11 +287,11 @@ __device__ inline void cubic_roots_in(double c0, double c1, double c2, double c3
       }
     }
 #pragma unroll
-    for (int t = 0; t < 3; ++t) A[t] = x[t];
+    for (int t = 0; t < 2; ++t) A[t] = x[t];
   }
 #pragma unroll
-  for (int t = 0; t < 3; ++t) {
-    if (at_a[t]) emit(t == 0 ? lo : (t == 1 ? m1 : m2));
+  for (int t = 0; t < 2; ++t) {
+    if (at_a[t]) emit(first[t]);
     else if (run[t]) emit(A[t]);
     else if (at_b[t]) emit(hi);
   }
@@ -396,14 +401,14 @@ __device__ inline double p3p_member(const P3PSetup& s, double root, bool from_f,
 
 // One of the two searches for degenerate members: from_f, the roots g of
 // det(D1 + g D2) on [-1, 1]; otherwise the roots e of det(e D1 + D2) with
-// |e| < 1.  Returns the quality of the first member of best quality (0: none)
-// and its root.
-__device__ inline double p3p_best_member(const P3PSetup& s, bool from_f, double& best_root) {
+// |e| < 1, of a part's brackets.  Returns the quality of the first member of
+// best quality (0: none) and its root.
+__device__ inline double p3p_best_member(const P3PSetup& s, bool from_f, int part, double& best_root) {
   double best_q = 0.0;
   best_root = 0.0;
   const double k0 = from_f ? s.c0 : s.c3, k1 = from_f ? s.c1 : s.c2;
   const double k2 = from_f ? s.c2 : s.c1, k3 = from_f ? s.c3 : s.c0;
-  cubic_roots_in(k0, k1, k2, k3, -1.0, 1.0, [&](double r) {
+  cubic_roots_in(k0, k1, k2, k3, -1.0, 1.0, part, [&](double r) {
     if (!from_f && !(fabs(r) < 1.0)) return;
     double M[9], T = 0.0, S = 0.0;
     const double q = p3p_member(s, r, from_f, M, T, S);

@@ -13,8 +13,9 @@ namespace imloc {
 // P3P: four lanes per sample (a workgroup of four waves holds 64 samples).
 // The four lanes of a sample draw the same minimal set and build the same
 // conics; lanes 0 and 2 search det(D1 + g D2) for degenerate members, lanes
-// 1 and 3 det(e D1 + D2), and the pair's better member (the first search's
-// on ties) is exchanged through LDS; lane j then cuts slot j (line j / 2,
+// 1 and 3 det(e D1 + D2), each the roots of its part of the brackets, and the
+// best member (the first search's and the first part's on ties) is exchanged
+// through LDS; lane j then cuts slot j (line j / 2,
 // intersection j % 2), and a scan over the four slots removes duplicates and
 // gives the canonical order.
 constexpr int kP3PLanes = 4;
@@ -61,15 +62,16 @@ __global__ __launch_bounds__(kP3PThreads) void sample_p3p_kernel(const QueryDesc
       }
     }
     if (ok && p3p_setup(y, x, su)) {
-      // the best degenerate member of this lane's search, then of the pair
+      // the best degenerate member of this lane's search, then of the four
       double root = 0.0;
-      const double mq = p3p_best_member(su, (j & 1) == 0, root);
+      const double mq = p3p_best_member(su, (j & 1) == 0, j >> 1, root);
       s_q[threadIdx.x] = mq;
       s_root[threadIdx.x] = root;
       __syncwarp();
-      const double q1 = s_q[g0], q2 = s_q[g0 + 1];
+      const int l1 = s_q[g0 + 2] > s_q[g0] ? g0 + 2 : g0, l2 = s_q[g0 + 3] > s_q[g0 + 1] ? g0 + 3 : g0 + 1;
+      const double q1 = s_q[l1], q2 = s_q[l2];
       const bool from_f = !(q2 > q1);
-      const double best_root = from_f ? s_root[g0] : s_root[g0 + 1];
+      const double best_root = s_root[from_f ? l1 : l2];
       __syncwarp();
       int okj = 0;
       double k0 = __builtin_inf(), k1 = __builtin_inf();
