@@ -790,21 +790,13 @@ __device__ inline bool key_less(const Key& a, const Key& b) {
 
 __device__ inline Key key_none() { return Key{__builtin_inf(), 0x7fffffffffffffffll, -1, -1}; }
 
-__device__ inline Key shfl_key(const Key& k, int lane_xor) {
-  Key o;
-  o.ms = __shfl_xor(k.ms, lane_xor, kWave);
-  o.hj = __shfl_xor(k.hj, lane_xor, kWave);
-  o.cnt = __shfl_xor(k.cnt, lane_xor, kWave);
-  o.idx = __shfl_xor(k.idx, lane_xor, kWave);
-  return o;
-}
-
 constexpr int kSelList = 8;      // per-thread list of the fast path (k <= 8)
 constexpr int kSelUnroll = 4;    // candidates loaded together per thread
 constexpr int kSelThreads = 256;
 constexpr int kSelWaves = kSelThreads / kWave;
-constexpr int kSelGroups = 16;   // phase-1 workgroups per query, at most
-constexpr int kSelPerThread = 4; // phase-1 candidates per thread, about
+constexpr int kSelGroups = 8;    // workgroups per query, at most
+constexpr int kSelPerThread = 4; // candidates per thread, about: one pass of four
+constexpr int kSelWanted = 256;  // workgroups of a launch from which a query gets fewer of its own
 
 __device__ inline Key load_key(const QueryDesc& d, const BestState& b, const CandBuf& cb, int c) {
   const int64_t o = d.cand_off + c;
@@ -852,13 +844,12 @@ __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v)
 }
 
 // k rounds of "pop the smallest list head of the wave" over per-lane sorted
-// lists of L keys; round r writes its key to out[r] (LDS, visible to the wave
+// lists; round r writes its key to out[r] (LDS, visible to the wave
 // after a wave barrier).  A round takes the wave minimum of the 64-bit image
-// of msac; only when several lanes hold that same msac do the full keys
+// of msac; only when several lanes hold that same msac do count and sample
 // decide.  Returns the number of keys popped (< k when the lists run dry).
 // Every lane of the wave must be active.
-template <int L>
-__device__ int wave_pop_k(Key (&list)[L], int k, Key* out) {
+__device__ int wave_pop_k(Key (&list)[kSelList], int k, Key* out) {
   const int lane = threadIdx.x & (kWave - 1);
   int r = 0;
   for (; r < k; ++r) {
@@ -872,39 +863,61 @@ __device__ int wave_pop_k(Key (&list)[L], int k, Key* out) {
     if (__popcll(tie) == 1) {
       wl = __ffsll((long long)tie) - 1;
     } else {
-      // several lanes share the smallest msac: full-key argmin among them
-      Key bk = ((tie >> lane) & 1ull) ? head : key_none();
-      int bl = ((tie >> lane) & 1ull) ? lane : -1;
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) {
-        const Key o = shfl_key(bk, off);
-        const int ol = __shfl_xor(bl, off, kWave);
-        if (ol >= 0 && (bl < 0 || key_less(o, bk))) { bk = o; bl = ol; }
-      }
-      wl = __builtin_amdgcn_readfirstlane(bl);
+      // several lanes share the smallest msac (candidates without an inlier
+      // all do): the most inliers, then the earliest
+      const bool in = (tie >> lane) & 1ull;
+      const unsigned long long mc = wave_min_u64(in ? (unsigned long long)(0x7fffffffll - head.cnt) : ~0ull);
+      const bool in2 = in && (unsigned long long)(0x7fffffffll - head.cnt) == mc;
+      const unsigned long long mh = wave_min_u64(in2 ? (unsigned long long)head.hj : ~0ull);
+      wl = __ffsll((long long)__ballot(in2 && (unsigned long long)head.hj == mh)) - 1;
     }
     if (lane == wl) {
       out[r] = head;
 #pragma unroll
-      for (int e = 0; e + 1 < L; ++e) list[e] = list[e + 1];
-      list[L - 1] = key_none();
+      for (int e = 0; e + 1 < kSelList; ++e) list[e] = list[e + 1];
+      list[kSelList - 1] = key_none();
     }
   }
   __syncwarp();
   return r;
 }
 
-__device__ inline void list_insert(Key (&list)[kSelList], Key x) {
-  if (!key_less(x, list[kSelList - 1])) return;
-  // sorted insertion as a compare-and-swap pass (static register indices)
+__device__ __forceinline__ void key_order(Key& a, Key& b) {
+  const bool swap = key_less(b, a);
+  const Key s = a, t = b;  // member by member: whole selects would go through memory
+  a.ms = swap ? t.ms : s.ms;
+  a.hj = swap ? t.hj : s.hj;
+  a.cnt = swap ? t.cnt : s.cnt;
+  a.idx = swap ? t.idx : s.idx;
+  b.ms = swap ? s.ms : t.ms;
+  b.hj = swap ? s.hj : t.hj;
+  b.cnt = swap ? s.cnt : t.cnt;
+  b.idx = swap ? s.idx : t.idx;
+}
+
+// Four keys into a thread's sorted list (static register indices): sorted by
+// 5 exchanges, and that is the list where it was empty; otherwise the 8
+// smallest of both are a bitonic sequence, which 12 exchanges put in order.
+static_assert(kSelList == 8 && kSelUnroll == 4, "the networks below");
+__device__ __forceinline__ void list_merge4(Key (&list)[kSelList], Key (&x)[kSelUnroll], bool first) {
+  key_order(x[0], x[1]);
+  key_order(x[2], x[3]);
+  key_order(x[0], x[2]);
+  key_order(x[1], x[3]);
+  key_order(x[1], x[2]);
+  if (first) {
 #pragma unroll
-  for (int e = 0; e < kSelList; ++e) {
-    if (key_less(x, list[e])) {
-      const Key t = list[e];
-      list[e] = x;
-      x = t;
-    }
+    for (int e = 0; e < kSelUnroll; ++e) list[e] = x[e];
+    return;
   }
+  if (!__any(key_less(x[0], list[kSelList - 1]))) return;
+#pragma unroll
+  for (int e = 0; e < kSelUnroll; ++e) key_order(list[4 + e], x[3 - e]);
+#pragma unroll
+  for (int st = 4; st > 0; st >>= 1)
+#pragma unroll
+    for (int e = 0; e < kSelList; ++e)
+      if (!(e & st)) key_order(list[e], list[e + st]);
 }
 
 __host__ __device__ inline int select_groups(int64_t n_cand) {
@@ -912,12 +925,46 @@ __host__ __device__ inline int select_groups(int64_t n_cand) {
   return g < 1 ? 1 : (g > kSelGroups ? kSelGroups : (int)g);
 }
 
+// The k smallest of `n` keys in LDS, to out[] in order, by one wave; returns
+// how many are keys at all (at most k).  A lane counts for its key those below
+// it, and that is its place: the reads do not wait for one another, where k
+// pops are a chain (32 keys: 8 pops 1.8 us, this 0.7).  No two keys tie: sample
+// and solution tell them apart.
+__device__ int wave_rank_k(const Key* keys, int n, int k, Key* out) {
+  const int lane = threadIdx.x & (kWave - 1);
+  int got = 0;
+  for (int e0 = 0; e0 < n; e0 += kWave) {
+    const Key mine = e0 + lane < n ? keys[e0 + lane] : key_none();
+    int below = 0, same = 0;
+#pragma unroll 4
+    for (int e = 0; e < n; ++e) {
+      const double ms = keys[e].ms;
+      below += ms < mine.ms ? 1 : 0;
+      same += ms == mine.ms ? 1 : 0;
+    }
+    const bool valid = mine.idx >= 0;
+    if (__ballot(valid && same > 1))  // candidates without an inlier all cost the same
+      for (int e = 0; e < n; ++e) {
+        const Key x = keys[e];
+        if (x.ms == mine.ms && key_less(x, mine)) ++below;
+      }
+    if (valid && below < k) out[below] = mine;
+    got += __popcll(__ballot(valid));
+  }
+  __syncwarp();
+  return got < k ? got : k;
+}
+
 // Top k (k <= 8) in one launch: workgroup b of a query scans candidates
 // b * 256 + t + j * G * 256, every thread keeps its best kSelList in
-// registers, each wave pops its k smallest, wave 0 pops the workgroup's k
-// smallest from the waves' lists and writes them to part[q][b][0..k)
-// (key_none() past the end).  The last of the query's G workgroups to finish
-// (counted in cb.sel_done) merges the G lists into the query's top k.
+// registers, each wave pops its k smallest, wave 0 ranks the waves' lists.  A
+// workgroup alone (G == 1) has the query's top k then; of several, each writes
+// its k smallest to part[q][b][0..k) (key_none() past the end) and the last to
+// finish (counted in cb.sel_done) ranks the G lists.  G follows the candidates
+// found, not the slots.  Bound by the chain of compares of one wave per SIMD:
+// 13,374 candidates 16.1 -> 12.7 us, 1,400 candidates 7.2 -> 5.9, 256 queries
+// 187 -> 30, against one-by-one insertion into lists of 8 in up to 16
+// workgroups by slots and pops at every level.
 __global__ __launch_bounds__(kSelThreads) void select_kernel(const QueryDesc* __restrict__ qd,
                                                              BestState* __restrict__ st, CandBuf cb,
                                                              Key* __restrict__ part, int32_t* __restrict__ sel,
@@ -929,7 +976,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const QueryDesc* __
     return;
   }
   const int nc = cb.n[q];
-  const int G = select_groups(d.cap);
+  const int G = min(select_groups(nc), (int)gridDim.x);
   if (b >= G) return;
   const int k = d.k;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -939,28 +986,33 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const QueryDesc* __
 #pragma unroll
   for (int e = 0; e < kSelList; ++e) list[e] = key_none();
   const int stride = G * kSelThreads;
-  for (int c0 = b * kSelThreads + threadIdx.x; c0 < nc; c0 += kSelUnroll * stride) {
+  for (int c0 = b * kSelThreads; c0 < nc; c0 += kSelUnroll * stride) {
     Key xs[kSelUnroll];
 #pragma unroll
     for (int u = 0; u < kSelUnroll; ++u) {
-      const int c = c0 + u * stride;
+      const int c = c0 + (int)threadIdx.x + u * stride;
       xs[u] = c < nc ? load_key(d, bs, cb, c) : key_none();
+      if (!(xs[u].ms < gate)) xs[u] = key_none();
     }
-#pragma unroll
-    for (int u = 0; u < kSelUnroll; ++u)
-      if (xs[u].idx >= 0 && xs[u].ms < gate) list_insert(list, xs[u]);
+    list_merge4(list, xs, c0 == b * kSelThreads);
   }
-  __shared__ Key s_wave[kSelWaves][kSelList];
-  __shared__ int s_got[kSelWaves];
+  __shared__ Key s_all[kSelGroups * kSelList];
+  Key* s_wave = s_all;  // [kSelWaves * k]
   __shared__ Key s_out[kSelList];
-  const int got = wave_pop_k<kSelList>(list, k, s_wave[wave]);
-  if (lane == 0) s_got[wave] = got;
+  const int got = wave_pop_k(list, k, &s_wave[wave * k]);
+  if (lane >= got && lane < k) s_wave[wave * k + lane] = key_none();
   __syncthreads();
   if (wave != 0) return;
-  // wave 0: the workgroup's k smallest from the waves' lists (one key per lane)
-  Key one[1];
-  one[0] = (lane < kSelWaves * k && lane % k < s_got[lane / k]) ? s_wave[lane / k][lane % k] : key_none();
-  const int got_b = wave_pop_k<1>(one, k, s_out);
+  // wave 0: the workgroup's k smallest from the waves' lists
+  const int got_b = wave_rank_k(s_wave, kSelWaves * k, k, s_out);
+  if (G == 1) {
+    if (lane < got_b) sel[q * kMaxTopK + lane] = s_out[lane].idx;
+    if (lane == 0) {
+      n_sel[q] = got_b;
+      st[q].candidates += nc;
+    }
+    return;
+  }
   Key* mine = part + ((int64_t)q * kSelGroups + b) * kSelList;
   if (lane < k) mine[lane] = lane < got_b ? s_out[lane] : key_none();
   // publish, then count this workgroup; the last one merges
@@ -969,20 +1021,10 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const QueryDesc* __
   if (lane == 0) last = atomicAdd(&cb.sel_done[q], 1) == G - 1;
   if (!__builtin_amdgcn_readfirstlane(last)) return;
   __threadfence();
-  // G * k <= 128 keys, two per lane, each pair sorted
   const Key* all = part + (int64_t)q * kSelGroups * kSelList;
-  Key two[2];
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int e = lane + u * kWave;
-    two[u] = e < G * k ? all[(e / k) * kSelList + e % k] : key_none();
-  }
-  if (two[1].idx >= 0 && (two[0].idx < 0 || key_less(two[1], two[0]))) {
-    const Key t = two[0];
-    two[0] = two[1];
-    two[1] = t;
-  }
-  const int got_q = wave_pop_k<2>(two, k, s_out);
+  for (int e = lane; e < G * k; e += kWave) s_all[e] = all[(e / k) * kSelList + e % k];
+  __syncwarp();
+  const int got_q = wave_rank_k(s_all, G * k, k, s_out);
   if (lane < got_q) sel[q * kMaxTopK + lane] = s_out[lane].idx;
   if (lane == 0) {
     n_sel[q] = got_q;
@@ -1048,7 +1090,11 @@ hipError_t launch_select(const QueryDesc* qd, const BestState* st, CandBuf cb, i
   BestState* stw = const_cast<BestState*>(st);
   if (kmax <= kSelList) {
     Key* part = reinterpret_cast<Key*>(scratch);
-    hipLaunchKernelGGL(select_kernel, dim3(select_groups(max_cap), nq), dim3(kSelThreads), 0, s, qd, stw, cb, part,
+    // One workgroup per query once there are enough of them: each more costs a
+    // fence and the merge (256 queries: 30 us with one each, 112 with up to 8),
+    // which only a query with few beside it gets back.
+    const int most = std::max(1, std::min(select_groups(max_cap), kSelWanted / nq));
+    hipLaunchKernelGGL(select_kernel, dim3(most, nq), dim3(kSelThreads), 0, s, qd, stw, cb, part,
                        sel, n_sel);
   } else {
     hipLaunchKernelGGL(select_rounds_kernel, dim3(nq), dim3(256), 0, s, qd, stw, cb, sel, n_sel);
