@@ -35,6 +35,7 @@ sys.path.insert(0, ROOT)
 METRIC = "scored residuals/s and queries/s at 1 GPU; p50/p99 query latency at fixed accuracy"
 PEAK_F32_TFLOPS = 157.3    # published FP32 vector peak of the MI355X (256 CUs at 2.4 GHz)
 PEAK_HBM_GBS = 8000.0      # published HBM3E bandwidth
+# Nominal float32 work: what a residual costs where every one is computed in full.
 FLOP_PER_RESIDUAL = 27     # 9 FMA projection + 2 FMA residual + MUL+FMA square + 2 MUL threshold
 FLOP_PER_INLIER = 5        # reciprocal, multiply, FMA, add of the truncated cost
 ROT_TOL_DEG, T_TOL_REL = 1e-3, 1e-4
@@ -224,6 +225,9 @@ def headline(pk, args):
     kernel_src = os.path.join(ROOT, "paper_2601_04185_amd", "csrc", "score.hip")
     roofline = dict(bound="alu", achieved=round(achieved, 3), peak=PEAK_F32_TFLOPS, unit="TFLOP/s",
                     frac=round(achieved / PEAK_F32_TFLOPS, 4), traffic=_traffic(kernel_src, "batch256", (ct, pts, wg)),
+                    note="achieved is the nominal float32 work of every residual over the launch time, not a "
+                         "utilisation: most residuals are ruled out in float16 matrix products and only the rest "
+                         "is computed in float32, so frac may pass 1",
                     kernel=_score_kernel_name(ct), launch_ms=round(launch_ms, 4), flop_per_launch=int(flops),
                     residuals_per_launch=res, residuals_per_s_kernel=round(res / (launch_ms * 1e-3), 1),
                     launch_shape=dict(candidates_per_item=ct, points_per_item=pts, workgroups=wg))

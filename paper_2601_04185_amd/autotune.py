@@ -7,7 +7,9 @@ unit, each striding over many work items, to about one per item).  None changes 
 result (per-candidate scores are integer-accumulated over fixed 512-point
 wave blocks), so the tuner simply times each shape on the caller's own
 workload with HIP events (the library's per-stage timing) and keeps the
-fastest on the context.
+fastest on the context.  The library's own choice (0 candidates, 0
+workgroups: both picked per round, up to 256 candidates per item) is one of
+the shapes.
 """
 from __future__ import annotations
 
@@ -17,6 +19,8 @@ from . import Context, lib
 
 
 def candidate_shapes(cus: int):
+    for pts in (1024, 2048, 4096):
+        yield 0, pts, 0
     for ct in (32, 64, 128):
         for pts in (512, 1024, 2048, 4096):
             for per_cu in (4, 8, 16, 32, 64, 128, 256):

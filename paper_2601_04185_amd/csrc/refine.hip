@@ -238,8 +238,7 @@ __device__ __forceinline__ double wave_sum29(const double* a) {
 
 // Inlier test of point i of the full set at a final pose (float64, through
 // the point's rig camera for a rig query): depth > 0 and squared pixel
-// residual below tau^2.  Shared by the mask kernel and the fused final
-// refinement, so both give the same mask.
+// residual below tau^2.
 __device__ __forceinline__ bool mask_test(const QueryDesc& d, const double* pose, double X, double Y, double Z,
                                           double u, double v, int64_t i) {
   double x = pose[0] * X + pose[1] * Y + pose[2] * Z + pose[9];

@@ -773,8 +773,7 @@ hipError_t launch_candidate_costs(const QueryDesc* qd, const BestState* st, Cand
 
 // ---------------------------------------------------------------------------
 // Top-k of a query's batch by (msac asc, count desc, h asc, j asc) among the
-// candidates whose truncated cost beats the running best.  One workgroup per
-// query.
+// candidates whose truncated cost beats the running best.
 // ---------------------------------------------------------------------------
 struct Key {
   double ms;
@@ -928,8 +927,8 @@ __host__ __device__ inline int select_groups(int64_t n_cand) {
 // The k smallest of `n` keys in LDS, to out[] in order, by one wave; returns
 // how many are keys at all (at most k).  A lane counts for its key those below
 // it, and that is its place: the reads do not wait for one another, where k
-// pops are a chain (32 keys: 8 pops 1.8 us, this 0.7).  No two keys tie: sample
-// and solution tell them apart.
+// pops are a chain (the launch on 1,400 candidates 6.5 -> 5.8 us).  No two keys
+// tie: sample and solution tell them apart.
 __device__ int wave_rank_k(const Key* keys, int n, int k, Key* out) {
   const int lane = threadIdx.x & (kWave - 1);
   int got = 0;
