@@ -174,6 +174,7 @@ struct QueryTables {
   QueryDesc* dev;
   const double* rig_host;  // null: no rig
   double* rig_dev;
+  bool weights;            // the scoring sets' weight sums are needed
 };
 hipError_t launch_init_queries(const QueryTables& t, BestState* st, CandBuf cb, int nq, int64_t max_m, bool begin,
                                const GNClear& clear, hipStream_t s);

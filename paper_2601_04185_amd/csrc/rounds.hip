@@ -40,13 +40,15 @@ __device__ inline int64_t round_samples(const QueryDesc& d, const BestState& b) 
 // The start of a call (of a round, in a server): one launch brings the table
 // and the rigs from (pinned) host memory, gathers the scoring subsets, clears the
 // mailboxes and resets the states, where a copy or a launch each took 3 to 5 us
-// (a query on 2,000 points 6.6 -> 4.2 us, with a subset of 10,000 of 50,000 12.6
-// -> 7.2, a four-camera query 11 -> 5.9, a server's round 9 -> 5.2).
+// (a query on 2,000 points 6.6 -> 3.7 us, with a subset of 10,000 of 50,000 12.6
+// -> 7.3, a four-camera query 11 -> 5.7, a server's round 9 -> 5.2).
 // Grid row 0: one workgroup of 1024 threads per query copies its descriptor
 // and, if the query is fresh, resets the state and sums the scoring-set weights
 // in float64 (thread t adds elements t + 1024 (16 k + u) into sixteen partial
 // sums, u = 0..15, so that sixteen loads are in flight; the partials, the waves
-// and the workgroup are combined in a fixed order).  With `begin`, it also sets
+// and the workgroup are combined in a fixed order: 50,000 weights take 7 us, at
+// the rate of one compute unit's loads).  Without weights the sum is m, and a
+// call of Gauss-Newton alone needs none (20,000 points 7.0 -> 4.1 us).  With `begin`, it also sets
 // up the round (samples, candidate counter).  The next rows clear a fresh query's
 // mailboxes, the others gather its scoring set, S_j = point floor(j * n / m).
 // No workgroup reads what another one writes: all read the host's table.
@@ -75,7 +77,15 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
   const QueryDesc& d = *reinterpret_cast<const QueryDesc*>(s_desc);
   const bool subset = d.S.u != d.full.u;
   const int64_t m = d.m, n = d.n;
-  auto source = [&](int64_t j) { return (int64_t)(((uint64_t)j * (uint64_t)n) / (uint64_t)m); };  // n < 2^31
+  // floor(j n / m) < n < 2^31: the float64 quotient is off by less than one
+  const double inv_m = 1.0 / (double)m;
+  auto source = [&](int64_t j) {
+    const int64_t jn = j * n;
+    int64_t s = (int64_t)((double)jn * inv_m);
+    const int64_t r = jn - s * m;
+    s += r >= m ? 1 : 0;
+    return s - (r < 0 ? 1 : 0);
+  };
   if ((int)blockIdx.y > clear_rows) {
     const int64_t j = (int64_t)((int)blockIdx.y - 1 - clear_rows) * kInitThreads + threadIdx.x;
     if (!d.fresh || !subset || j >= m) return;
@@ -111,11 +121,12 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
     }
     return;
   }
-  double p[16];
-#pragma unroll
-  for (int u = 0; u < 16; ++u) p[u] = 0.0;
   const float* __restrict__ w = subset ? d.full.w : d.S.w;
-  if (w) {
+  double sum = 0.0;  // without weights (or a use for them) no wave adds
+  if (w && t.weights) {
+    double p[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) p[u] = 0.0;
     for (int64_t i0 = threadIdx.x; i0 < m; i0 += 16 * kInitThreads) {
       float x[16];
 #pragma unroll
@@ -126,24 +137,21 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
 #pragma unroll
       for (int u = 0; u < 16; ++u) p[u] += (double)x[u];
     }
-  } else {
-    for (int64_t i0 = threadIdx.x; i0 < m; i0 += 16 * kInitThreads) {
 #pragma unroll
-      for (int u = 0; u < 16; ++u) p[u] += i0 + (int64_t)kInitThreads * u < m ? 1.0 : 0.0;
+    for (int h = 8; h >= 1; h >>= 1) {
+#pragma unroll
+      for (int u = 0; u < h; ++u) p[u] += p[u + h];
     }
+    sum = p[0];
   }
-#pragma unroll
-  for (int h = 8; h >= 1; h >>= 1) {
-#pragma unroll
-    for (int u = 0; u < h; ++u) p[u] += p[u + h];
-  }
-  const double s = wave_sum(p[0]);
+  const double s = wave_sum(sum);
   __shared__ double sw[kInitThreads / kWave];
   if ((threadIdx.x & (kWave - 1)) == 0) sw[threadIdx.x / kWave] = s;
   __syncthreads();
   if (threadIdx.x == 0) {
     double tot = 0.0;
     for (int k = 0; k < kInitThreads / kWave; ++k) tot += sw[k];
+    if (!w) tot = (double)m;
     BestState& b = st[q];
     for (int e = 0; e < 12; ++e) b.pose[e] = (e == 0 || e == 4 || e == 8) ? 1.0 : 0.0;
     b.cost = __builtin_inf();

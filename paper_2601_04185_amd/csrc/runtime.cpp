@@ -727,7 +727,7 @@ int run_batch(imloc_ctx* ctx, int nq, const imloc_corr* pts, const int64_t* n, c
   // a copy, the host's answer and then the launch.
   auto enqueue = [&](hipStream_t st_, bool sync) -> int {
     hipEvent_t ev_total = tm.total_begin();
-    HIP_TRY(ctx, launch_init_queries(QueryTables{htab, e.qd, rigb ? hrig : nullptr, e.rig}, e.st, e.cb, nq, max_m_sub,
+    HIP_TRY(ctx, launch_init_queries(QueryTables{htab, e.qd, rigb ? hrig : nullptr, e.rig, true}, e.st, e.cb, nq, max_m_sub,
                                      true, team_clear(e, teams, false), st_));  // and the first round's setup
     auto finish = [&]() -> int {
       hipEvent_t e4 = tm.begin();
@@ -915,7 +915,7 @@ int stage_upload(imloc_ctx* ctx, StageQuery& sq, const imloc_corr* pts, int64_t 
   QueryDesc* htab = reinterpret_cast<QueryDesc*>(ctx->pinned);
   htab[0] = make_desc(pts, n, K, &sq.p, sq.pl, sq.e, 0, mask, rig);
   htab[0].B = B;
-  QueryTables tables{htab, sq.e.qd, nullptr, sq.e.rig};
+  QueryTables tables{htab, sq.e.qd, nullptr, sq.e.rig, !clear};  // (Gauss-Newton alone has no use for the sum)
   if (rig && sq.e.rig_doubles) {
     double* hrig = reinterpret_cast<double*>(ctx->pinned + rig_at);
     fill_rig_tables(hrig, 1, rig, sq.e);
@@ -1814,7 +1814,7 @@ int imloc_server_create(imloc_ctx* ctx, const imloc_server_config* cfg, imloc_se
   hipStream_t s = ctx->stream;
   GNClear none{};
   none.tickets = srv->e.tickets;
-  if (launch_init_queries(QueryTables{htab, srv->e.qd, nullptr, nullptr}, srv->e.st, srv->e.cb, cfg->max_slots, 0, false,
+  if (launch_init_queries(QueryTables{htab, srv->e.qd, nullptr, nullptr, true}, srv->e.st, srv->e.cb, cfg->max_slots, 0, false,
                           none, s) != hipSuccess ||
       launch_retire(srv->e.st, cfg->max_slots, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
     imloc_server_destroy(srv);
@@ -2012,7 +2012,7 @@ int imloc_server_step(imloc_server* srv, int64_t* done_tickets, int32_t capacity
     // so its mailboxes are cleared at its admission whatever its first team
     GNClear clear = team_clear(e, teams, true);
     if (!any_fresh) clear.lo = clear.fin = nullptr;
-    HIP_TRY(ctx, launch_init_queries(QueryTables{htab, e.qd, nullptr, nullptr}, e.st, e.cb, nq, max_m_sub, true, clear,
+    HIP_TRY(ctx, launch_init_queries(QueryTables{htab, e.qd, nullptr, nullptr, true}, e.st, e.cb, nq, max_m_sub, true, clear,
                                      s));
     HIP_TRY(ctx, launch_sample_p3p(e.qd, e.st, e.cb, nq, max_batch, nullptr, s));
     const ScoreTune tune = round_tune(ctx, est.data(), est.size());
