@@ -39,7 +39,7 @@ struct BestState {
   int64_t lo_runs;
   int64_t candidates;        // candidates scored so far
   int64_t inlier_residuals;  // inside-threshold residuals seen by scoring
-  double weight_sum;         // sum of weights over the scoring set
+  double weight_sum;         // sum of weights over the scoring set (set by the selection)
   double final_cost;
   int64_t full_count;
   int64_t drawn;             // samples drawn so far
@@ -92,6 +92,8 @@ __host__ __device__ inline int cam_of(const int64_t* seg, int ncam, int64_t i) {
 __host__ __device__ inline int rows_per_slot(const QueryDesc& d) { return d.ncam > 0 ? d.ncam : 1; }
 
 // Candidate arrays of all queries of a batch (device), indexed by slot.
+constexpr int kWeightParts = 16;  // part u: points 1024 (u + 16 k) + 0..1023
+
 struct CandBuf {
   double* pose;      // [slots][12]
   float* proj;       // per query from proj_off: [slots][cameras][16] float32 rows of K [R | t] (rig: of
@@ -102,6 +104,7 @@ struct CandBuf {
   uint64_t* gain;    // [slots] sum of w (1 - r^2 / tau^2) over inliers, fixed point 2^-32 (accumulated)
   int32_t* n;        // [queries] candidates of the current round
   int32_t* sel_done; // [queries] selection workgroups finished (zeroed before the round)
+  double* wsum;      // [queries][kWeightParts] sums of parts of the scoring set's weights (none: not written)
 };
 
 // --- lift ------------------------------------------------------------------
@@ -210,8 +213,8 @@ hipError_t launch_worklist(const QueryDesc* qd, CandBuf cb, int nq, ScoreTune tu
 hipError_t launch_score(const QueryDesc* qd, CandBuf cb, BestState* st, int nq, const int64_t* item_off,
                         ScoreTune tune, int precision, hipStream_t s);
 // truncated cost of the candidates of query 0: count and msac outputs
-hipError_t launch_candidate_costs(const QueryDesc* qd, const BestState* st, CandBuf cb, int64_t np, int32_t* count,
-                                  double* msac, hipStream_t s);
+hipError_t launch_candidate_costs(const QueryDesc* qd, CandBuf cb, int64_t np, int32_t* count, double* msac,
+                                  hipStream_t s);
 
 // --- selection / local optimisation / refinement ------------------------------
 // scratch: select_scratch_bytes(nq); max_cap bounds the queries' candidate slots

@@ -5,6 +5,8 @@
 #include "imloc_device.h"
 #include "imloc_kernels.h"
 
+#include <algorithm>
+
 namespace imloc {
 
 __global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
@@ -40,19 +42,22 @@ __device__ inline int64_t round_samples(const QueryDesc& d, const BestState& b) 
 // The start of a call (of a round, in a server): one launch brings the table
 // and the rigs from (pinned) host memory, gathers the scoring subsets, clears the
 // mailboxes and resets the states, where a copy or a launch each took 3 to 5 us
-// (a query on 2,000 points 6.6 -> 3.7 us, with a subset of 10,000 of 50,000 12.6
-// -> 7.3, a four-camera query 11 -> 5.7, a server's round 9 -> 5.2).
+// (a query on 2,000 points 6.6 -> 3.1 us, with a subset of 10,000 of 50,000 12.6
+// -> 6.0, a four-camera query 11 -> 5.7, a server's round 9 -> 5.2).
 // Grid row 0: one workgroup of 1024 threads per query copies its descriptor
-// and, if the query is fresh, resets the state and sums the scoring-set weights
-// in float64 (thread t adds elements t + 1024 (16 k + u) into sixteen partial
-// sums, u = 0..15, so that sixteen loads are in flight; the partials, the waves
-// and the workgroup are combined in a fixed order: 50,000 weights take 7 us, at
-// the rate of one compute unit's loads).  Without weights the sum is m, and a
-// call of Gauss-Newton alone needs none (20,000 points 7.0 -> 4.1 us).  With `begin`, it also sets
-// up the round (samples, candidate counter).  The next rows clear a fresh query's
-// mailboxes, the others gather its scoring set, S_j = point floor(j * n / m).
+// and, if the query is fresh, resets the state.  With `begin`, it also sets
+// up the round (samples, candidate counter).  The next rows sum a fresh query's
+// scoring-set weights in float64, in kWeightParts parts whatever the number of
+// rows: one compute unit loads at 14 GB/s what another kernel has just written
+// (126,000 weights in one workgroup took the launch 41 us, now 7.2; 50,000 that
+// were read before 11.1, now 4.9); who needs the total adds the parts.  Without
+// weights it is the number of points (one query on 50,000 6.7 -> 4.8), and a call
+// of Gauss-Newton alone needs none (20,000 points 7.0 -> 4.2).
+// Then come the rows that clear a fresh query's mailboxes, and the others gather
+// its scoring set, S_j = point floor(j * n / m).
 // No workgroup reads what another one writes: all read the host's table.
 constexpr int kInitThreads = 1024;
+constexpr int kSumGroups = 512;  // workgroups of a launch that sum weights, about (two per compute unit)
 constexpr int kClearRows = 8;  // at most; a row clears 16 words per thread and turn
 
 __device__ inline void clear_words(uint64_t* p, int64_t n, int row, int rows) {
@@ -60,7 +65,7 @@ __device__ inline void clear_words(uint64_t* p, int64_t n, int row, int rows) {
 }
 
 __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables t, BestState* __restrict__ st,
-                                                                    CandBuf cb, int begin,
+                                                                    CandBuf cb, int begin, int sum_rows,
                                                                     GNClear clear, int clear_rows) {
   const int q = blockIdx.x;
   // the descriptor in one read over the bus (about 1.5 us), not field by field
@@ -86,8 +91,9 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
     s += r >= m ? 1 : 0;
     return s - (r < 0 ? 1 : 0);
   };
-  if ((int)blockIdx.y > clear_rows) {
-    const int64_t j = (int64_t)((int)blockIdx.y - 1 - clear_rows) * kInitThreads + threadIdx.x;
+  const int row = (int)blockIdx.y - 1 - sum_rows;
+  if (row >= clear_rows) {
+    const int64_t j = (int64_t)(row - clear_rows) * kInitThreads + threadIdx.x;
     if (!d.fresh || !subset || j >= m) return;
     const int64_t i = source(j);
     float* dst = const_cast<float*>(d.S.u);
@@ -99,13 +105,40 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
     dst[5 * m + j] = d.full.w ? d.full.w[i] : 1.0f;
     return;
   }
-  if (blockIdx.y > 0) {
-    const int row = blockIdx.y - 1;
+  if (row >= 0) {
     if (!d.fresh) return;
     if (clear.lo && (clear.all || d.lo_team > 1))
       clear_words(clear.lo + q * clear.lo_words, clear.lo_words, row, clear_rows);
     if (clear.fin && (clear.all || d.fin_team > 1))
       clear_words(clear.fin + q * clear.fin_words, clear.fin_words, row, clear_rows);
+    return;
+  }
+  if (blockIdx.y > 0) {
+    const float* __restrict__ w = d.full.w;
+    if (!d.fresh || !w) return;
+    __shared__ double sw[kInitThreads / kWave];
+    for (int u = (int)blockIdx.y - 1; u < kWeightParts; u += sum_rows) {
+      double p = 0.0;
+      for (int64_t i0 = (int64_t)u * kInitThreads + threadIdx.x; i0 < m; i0 += 8 * kWeightParts * kInitThreads) {
+        float x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const int64_t i = i0 + (int64_t)k * kWeightParts * kInitThreads;
+          x[k] = i < m ? w[subset ? source(i) : i] : 0.0f;
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) p += (double)x[k];
+      }
+      p = wave_sum(p);
+      if ((threadIdx.x & (kWave - 1)) == 0) sw[threadIdx.x / kWave] = p;
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        double tot = 0.0;
+        for (int k = 0; k < kInitThreads / kWave; ++k) tot += sw[k];
+        cb.wsum[q * kWeightParts + u] = tot;
+      }
+      __syncthreads();
+    }
     return;
   }
   if (q == 0 && threadIdx.x < 2) clear.tickets[threadIdx.x] = 0;
@@ -121,37 +154,7 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
     }
     return;
   }
-  const float* __restrict__ w = subset ? d.full.w : d.S.w;
-  double sum = 0.0;  // without weights (or a use for them) no wave adds
-  if (w && t.weights) {
-    double p[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) p[u] = 0.0;
-    for (int64_t i0 = threadIdx.x; i0 < m; i0 += 16 * kInitThreads) {
-      float x[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int64_t i = i0 + (int64_t)kInitThreads * u;
-        x[u] = i < m ? w[subset ? source(i) : i] : 0.0f;
-      }
-#pragma unroll
-      for (int u = 0; u < 16; ++u) p[u] += (double)x[u];
-    }
-#pragma unroll
-    for (int h = 8; h >= 1; h >>= 1) {
-#pragma unroll
-      for (int u = 0; u < h; ++u) p[u] += p[u + h];
-    }
-    sum = p[0];
-  }
-  const double s = wave_sum(sum);
-  __shared__ double sw[kInitThreads / kWave];
-  if ((threadIdx.x & (kWave - 1)) == 0) sw[threadIdx.x / kWave] = s;
-  __syncthreads();
   if (threadIdx.x == 0) {
-    double tot = 0.0;
-    for (int k = 0; k < kInitThreads / kWave; ++k) tot += sw[k];
-    if (!w) tot = (double)m;
     BestState& b = st[q];
     for (int e = 0; e < 12; ++e) b.pose[e] = (e == 0 || e == 4 || e == 8) ? 1.0 : 0.0;
     b.cost = __builtin_inf();
@@ -162,7 +165,7 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
     b.lo_runs = 0;
     b.candidates = 0;
     b.inlier_residuals = 0;
-    b.weight_sum = tot;
+    b.weight_sum = 0.0;
     b.final_cost = 0.0;
     b.full_count = 0;
     b.drawn = 0;
@@ -185,8 +188,14 @@ hipError_t launch_init_queries(const QueryTables& t, BestState* st, CandBuf cb, 
   const int64_t rows = (words + 16 * kInitThreads - 1) / (16 * kInitThreads);
   const int clear_rows = (int)(rows < kClearRows ? rows : kClearRows);
   const int64_t gather_rows = (max_m + kInitThreads - 1) / kInitThreads;
-  hipLaunchKernelGGL(init_queries_kernel, dim3(nq, (unsigned)(1 + clear_rows + gather_rows)), dim3(kInitThreads), 0, s,
-                     t, st, cb, begin ? 1 : 0, clear, clear_rows);
+  // rows for the sums: a part each while the launch has room for them and the sets have points for them
+  int64_t weighted = 0;
+  for (int q = 0; t.weights && q < nq; ++q)
+    if (t.host[q].fresh && t.host[q].full.w) weighted = std::max(weighted, t.host[q].m);
+  const int64_t parts = std::min<int64_t>((weighted + kInitThreads - 1) / kInitThreads, kWeightParts);
+  const int sum_rows = (int)std::min<int64_t>(parts, std::max(1, kSumGroups / nq));
+  hipLaunchKernelGGL(init_queries_kernel, dim3(nq, (unsigned)(1 + sum_rows + clear_rows + gather_rows)),
+                     dim3(kInitThreads), 0, s, t, st, cb, begin ? 1 : 0, sum_rows, clear, clear_rows);
   return hipGetLastError();
 }
 

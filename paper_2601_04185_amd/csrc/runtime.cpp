@@ -382,6 +382,7 @@ void carve_engine(Arena& a, Engine& e) {
   e.cb.gain = a.take<uint64_t>(S);
   e.cb.n = a.take<int32_t>(nq);
   e.cb.sel_done = a.take<int32_t>(nq);
+  e.cb.wsum = a.take<double>((size_t)nq * kWeightParts);
   e.item_off = a.take<int64_t>(nq + 1);
   e.active_count = a.take<int32_t>(1);
   e.sel = a.take<int32_t>((size_t)nq * kMaxTopK);
@@ -784,8 +785,9 @@ int run_batch(imloc_ctx* ctx, int nq, const imloc_corr* pts, const int64_t* n, c
              tune.blocks, tune.pts, teams.lo.members, teams.fin.members, ctx->gn_polls);
     key += buf;
     for (int q = 0; q < nq; ++q) {
-      snprintf(buf, sizeof(buf), "%lld,%lld,%d,%lld,%lld,%d,%d;", (long long)pl[q].n, (long long)pl[q].m,
-               (int)pl[q].subset, (long long)pl[q].total, (long long)pl[q].batch, pl[q].k, pl[q].ncam);
+      snprintf(buf, sizeof(buf), "%lld,%lld,%d,%lld,%lld,%d,%d,%d;", (long long)pl[q].n, (long long)pl[q].m,
+               (int)pl[q].subset, (long long)pl[q].total, (long long)pl[q].batch, pl[q].k, pl[q].ncam,
+               htab[q].full.w ? 1 : 0);
       key += buf;
     }
     if (key != ctx->gkey || !ctx->gexec) {
@@ -1471,7 +1473,7 @@ int imloc_rig_score(imloc_ctx* ctx, const imloc_corr* pts, int64_t n, const imlo
   const std::pair<int64_t, int64_t> est1{np, est_points(sq.pl)};
   const ScoreTune tune = round_tune(ctx, &est1, 1);
   HIP_TRY(ctx, launch_score(sq.e.qd, sq.e.cb, sq.e.st, 1, sq.e.item_off, tune, precision, s));
-  HIP_TRY(ctx, launch_candidate_costs(sq.e.qd, sq.e.st, sq.e.cb, np, count, msac, s));
+  HIP_TRY(ctx, launch_candidate_costs(sq.e.qd, sq.e.cb, np, count, msac, s));
   return IMLOC_OK;
 }
 
@@ -1514,7 +1516,7 @@ int imloc_score(imloc_ctx* ctx, const imloc_corr* pts, int64_t n, const imloc_ca
   const std::pair<int64_t, int64_t> est1{np, est_points(sq.pl)};
   const ScoreTune tune = round_tune(ctx, &est1, 1);
   HIP_TRY(ctx, launch_score(sq.e.qd, sq.e.cb, sq.e.st, 1, sq.e.item_off, tune, precision, s));
-  HIP_TRY(ctx, launch_candidate_costs(sq.e.qd, sq.e.st, sq.e.cb, np, count, msac, s));
+  HIP_TRY(ctx, launch_candidate_costs(sq.e.qd, sq.e.cb, np, count, msac, s));
   return IMLOC_OK;
 }
 

@@ -750,24 +750,38 @@ hipError_t launch_score(const QueryDesc* qd, CandBuf cb, BestState* st, int nq, 
   return hipGetLastError();
 }
 
-__device__ inline double cand_msac(const QueryDesc& d, const BestState& b, uint64_t gain) {
-  return d.tau * d.tau * (b.weight_sum - (double)gain * (1.0 / kGainScale));
+// Sum of the weights of query q's scoring set (without weights: its size).
+__device__ inline double weight_total(const QueryDesc& d, const CandBuf& cb, int q) {
+  if (!d.full.w || d.m == 0) return (double)d.m;
+  double p[kWeightParts];
+#pragma unroll
+  for (int u = 0; u < kWeightParts; ++u) p[u] = cb.wsum[q * kWeightParts + u];
+#pragma unroll
+  for (int h = kWeightParts / 2; h >= 1; h >>= 1) {
+#pragma unroll
+    for (int u = 0; u < h; ++u) p[u] += p[u + h];
+  }
+  return p[0];
 }
 
-__global__ void candidate_costs_kernel(const QueryDesc* __restrict__ qd, const BestState* __restrict__ st, CandBuf cb,
-                                       int64_t np, int32_t* __restrict__ count, double* __restrict__ msac) {
+__device__ inline double cand_msac(const QueryDesc& d, double weights, uint64_t gain) {
+  return d.tau * d.tau * (weights - (double)gain * (1.0 / kGainScale));
+}
+
+__global__ void candidate_costs_kernel(const QueryDesc* __restrict__ qd, CandBuf cb, int64_t np,
+                                       int32_t* __restrict__ count, double* __restrict__ msac) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= np) return;
   const int64_t o = qd[0].cand_off + i;
   count[i] = (int32_t)cb.cnt[o];
-  msac[i] = cand_msac(qd[0], st[0], cb.gain[o]);
+  msac[i] = cand_msac(qd[0], weight_total(qd[0], cb, 0), cb.gain[o]);
 }
 
-hipError_t launch_candidate_costs(const QueryDesc* qd, const BestState* st, CandBuf cb, int64_t np, int32_t* count,
-                                  double* msac, hipStream_t s) {
+hipError_t launch_candidate_costs(const QueryDesc* qd, CandBuf cb, int64_t np, int32_t* count, double* msac,
+                                  hipStream_t s) {
   if (np <= 0) return hipSuccess;
-  hipLaunchKernelGGL(candidate_costs_kernel, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s, qd, st, cb, np,
-                     count, msac);
+  hipLaunchKernelGGL(candidate_costs_kernel, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s, qd, cb, np, count,
+                     msac);
   return hipGetLastError();
 }
 
@@ -797,9 +811,9 @@ constexpr int kSelGroups = 8;    // workgroups per query, at most
 constexpr int kSelPerThread = 4; // candidates per thread, about: one pass of four
 constexpr int kSelWanted = 256;  // workgroups of a launch from which a query gets fewer of its own
 
-__device__ inline Key load_key(const QueryDesc& d, const BestState& b, const CandBuf& cb, int c) {
+__device__ inline Key load_key(const QueryDesc& d, double weights, const CandBuf& cb, int c) {
   const int64_t o = d.cand_off + c;
-  return Key{cand_msac(d, b, cb.gain[o]), (long long)cb.h[o] * 4 + cb.j[o], (int)cb.cnt[o], c};
+  return Key{cand_msac(d, weights, cb.gain[o]), (long long)cb.h[o] * 4 + cb.j[o], (int)cb.cnt[o], c};
 }
 
 // Order-preserving 64-bit image of a double (total order of the non-NaN
@@ -979,8 +993,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const QueryDesc* __
   if (b >= G) return;
   const int k = d.k;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const BestState& bs = st[q];
-  const double gate = bs.cost;
+  const double gate = st[q].cost, weights = weight_total(d, cb, q);
   Key list[kSelList];
 #pragma unroll
   for (int e = 0; e < kSelList; ++e) list[e] = key_none();
@@ -990,7 +1003,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const QueryDesc* __
 #pragma unroll
     for (int u = 0; u < kSelUnroll; ++u) {
       const int c = c0 + (int)threadIdx.x + u * stride;
-      xs[u] = c < nc ? load_key(d, bs, cb, c) : key_none();
+      xs[u] = c < nc ? load_key(d, weights, cb, c) : key_none();
       if (!(xs[u].ms < gate)) xs[u] = key_none();
     }
     list_merge4(list, xs, c0 == b * kSelThreads);
@@ -1009,6 +1022,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const QueryDesc* __
     if (lane == 0) {
       n_sel[q] = got_b;
       st[q].candidates += nc;
+      st[q].weight_sum = weights;
     }
     return;
   }
@@ -1028,6 +1042,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const QueryDesc* __
   if (lane == 0) {
     n_sel[q] = got_q;
     st[q].candidates += nc;
+    st[q].weight_sum = weights;
   }
 }
 
@@ -1048,15 +1063,14 @@ __global__ __launch_bounds__(256) void select_rounds_kernel(const QueryDesc* __r
   }
   const int nc = cb.n[q];
   const int k = d.k;
-  const BestState& b = st[q];
-  const double gate = b.cost;
+  const double gate = st[q].cost, weights = weight_total(d, cb, q);
   __shared__ int s_sel[kMaxTopK];
   __shared__ Key s_red[256];
   int r = 0;
   for (; r < k; ++r) {
     Key bi = key_none();
     for (int c = threadIdx.x; c < nc; c += 256) {
-      const Key x = load_key(d, b, cb, c);
+      const Key x = load_key(d, weights, cb, c);
       if (!(x.ms < gate)) continue;
       bool taken = false;
       for (int t = 0; t < r; ++t) taken |= (s_sel[t] == c);
@@ -1081,6 +1095,7 @@ __global__ __launch_bounds__(256) void select_rounds_kernel(const QueryDesc* __r
   if (threadIdx.x == 0) {
     n_sel[q] = r;
     st[q].candidates += nc;
+    st[q].weight_sum = weights;
   }
 }
 
