@@ -181,7 +181,7 @@ struct QueryTables {
 };
 hipError_t launch_init_queries(const QueryTables& t, BestState* st, CandBuf cb, int nq, int64_t max_m, bool begin,
                                const GNClear& clear, hipStream_t s);
-// finished queries (final refinement and mask done) leave the round loop
+// marks finished queries as gone (a server's slots at its creation; in its rounds the next start launch does it)
 hipError_t launch_retire(BestState* st, int nq, hipStream_t s);
 // end: take the round's local optimisations into the running best, advance
 // the sample count, apply the stopping rule, and (begin_next) set up the next

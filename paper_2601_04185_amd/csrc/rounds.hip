@@ -149,6 +149,7 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
   }
   if (!d.fresh) {
     if (begin && threadIdx.x == 0) {
+      if (st[q].finished == 1) st[q].finished = 2;  // refined in the round before: the query has left
       t.dev[q].B = round_samples(d, st[q]);
       cb.n[q] = 0;
     }

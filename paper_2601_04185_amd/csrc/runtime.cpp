@@ -1877,7 +1877,7 @@ static int server_collect(imloc_server* srv, int64_t r, int nq, int64_t* done_ti
     ServerSlot& sl = srv->slots[i];
     if (!sl.used || sl.first_round > r) continue;
     const BestState& b = hst[i];
-    if (b.finished != 2) continue;
+    if (b.finished == 0) continue;
     Finished f;
     const bool have = b.have != 0;
     f.status = have ? IMLOC_OK : IMLOC_NO_POSE;
@@ -2026,7 +2026,6 @@ int imloc_server_step(imloc_server* srv, int64_t* done_tickets, int32_t capacity
     HIP_TRY(ctx, launch_round_end(e.qd, e.cb, e.sel, e.n_sel, e.lo_pose, e.lo_cost, e.lo_count, nq, kmax, e.st,
                                   e.active_count, e.tickets, false, s));
     HIP_TRY(ctx, launch_refine(e.qd, e.st, nullptr, nq, teams.fin, e.in_set, e.fin_pose, e.fin_cost, false, true, s));
-    HIP_TRY(ctx, launch_retire(e.st, nq, s));
     // the results block is laid out for all e.nq slots (the table may be shorter)
     HIP_TRY(ctx, hipMemcpyAsync(half + (size_t)S * sizeof(QueryDesc), e.st, result_bytes(e.nq),
                                 hipMemcpyDeviceToHost, s));
