@@ -188,7 +188,8 @@ int imloc_graph_counters(const imloc_ctx *ctx, int64_t *captures, int64_t *launc
 
 /* Launch shape of the scoring kernel: candidates per work item (32, 64 or
  * 128, or 0, the default: picked per round, the largest tile of up to 256
- * that still gives about four to eight work items per compute unit) and workgroups (1 to 2^20;
+ * that still gives enough work items to the compute units, and small rounds
+ * are cut at fewer correspondences too) and workgroups (1 to 2^20;
  * each walks the round's work list with a grid stride; or 0, the default:
  * per round, about 1.5 per estimated work item, between 8 per compute unit
  * and 2^18).  Neither changes any result (per-candidate sums are
@@ -203,7 +204,8 @@ int imloc_get_score_tuning(const imloc_ctx *ctx, int32_t *candidates_per_item, i
  * 512 consecutive correspondences against a candidate, and the per-block
  * partial sums are added as integers, so the tile changes no result, only
  * the speed (longer items stage each candidate tile once for more
- * correspondences; shorter ones give more items to small rounds).  Float64
+ * correspondences; shorter ones give more items to small rounds, which take
+ * them where the candidate tile is picked per round).  Float64
  * scoring keeps its own 512-correspondence items.  IMLOC_EINVAL for other
  * values. */
 int imloc_set_score_points(imloc_ctx *ctx, int32_t points_per_item);

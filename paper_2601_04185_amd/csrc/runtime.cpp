@@ -208,34 +208,49 @@ struct QPlan {
   int ncam = 0;  // 0: one camera; else the cameras of a rig
 };
 
-// Scoring launch shape: the context's fixed one, or (ct == 0) the largest
-// candidate tile of 128, 64 and 32 that still gives about four work items per
-// CU, so that small rounds keep every CU busy, and 256 from eight on: a larger
-// tile spends less on the filter's features (256 queries of 5,000 to 80,000
-// correspondences: 256 / 128 / 64 / 32 candidates 9.98 / 11.1 / 13.2 / 17.4 ms),
-// but ends raggedly (50,000 x 13,600, 5.3 items of 256 per CU: 143 us against
-// 142; 64 served queries of 7.5: 4.2 ms against 3.7; a round of 10,000 x 1,360:
-// 63 / 38 / 25 / 18 us).  est holds per query the expected candidates (one per
-// sample) and scoring points.  Neither the tile
-// nor the correspondences per item change a result (per-candidate sums are
+// Tile, grid and correspondences per item of a round's scoring launch where the
+// caller left them open.  A larger tile spends less on the filter's features
+// (256 queries of 5,000 to 80,000 correspondences: 256 / 128 / 64 / 32
+// candidates 9.98 / 11.1 / 13.2 / 17.4 ms), but too few items leave compute units
+// idle and end raggedly.  Candidates of samples, of which most see no inlier,
+// items in brackets at one candidate per sample: 126,000 x 1,024 samples 128 / 64
+// / 32 47 / 51 / 60 us (496 / 992 / 1984); 80,000 41.1 / 41.4 / 46 (320 / 640);
+// 40,000 38 / 27 / 30 (160 / 320 / 640); 20,000 37 / 25 / 20 (80 / 160 / 320): so
+// 128 from one and a half items per CU on, 64 from one and a quarter.  256 against
+// 128 at 784 items 124 : 111, at 1,000 140 : 135, at 1,960 237 : 234, and 64 served
+// queries at 1,920 4.2 : 3.7 ms: from eight per CU.  Given poses may all be good,
+// and a good one is evaluated in full: 50,000 x 4,096, 6 % good, 64 / 128 51.7 /
+// 53.1 us (1,600 / 800 items), so they keep four per CU.
+// Few items of 32 are cut at fewer correspondences, 512 / 1,024 / 2,048: 2,000 x
+// 256 samples 11 / 15 / 23 us (8 items of 2,048), 3,000 x 1,024 13.0 / 14.7 / 21.3
+// (64), 5,000 15.2 / 15.4 / 19.9 (96), 10,000 25.2 / 18.4 / 18.9 (160), 4,000 x
+// 4,096 29.8 / 22.9 / 23.6 (256), 6,000 39 / 33 / 25 (384).  (Of 512, a wave has 8
+// candidates, too few for the filter.)
+// est holds per query the expected candidates (one per sample) and scoring
+// points.  None of the three changes a result (per-candidate sums are
 // integer-accumulated over fixed wave blocks).
 using EstList = SmallVec<std::pair<int64_t, int64_t>, 4>;
-ScoreTune round_tune(const imloc_ctx* c, const std::pair<int64_t, int64_t>* est, size_t n_est) {
+ScoreTune round_tune(const imloc_ctx* c, const std::pair<int64_t, int64_t>* est, size_t n_est, bool given = false) {
   ScoreTune t = c->tune;
   if (t.ct > 0 && t.blocks > 0) return t;
-  const int64_t pts = t.pts;
   auto items_for = [&](int ct) {
     int64_t items = 0;
-    for (size_t q = 0; q < n_est; ++q) items += (est[q].first + ct - 1) / ct * ((est[q].second + pts - 1) / pts);
+    for (size_t q = 0; q < n_est; ++q) items += (est[q].first + ct - 1) / ct * ((est[q].second + t.pts - 1) / t.pts);
     return items;
   };
   if (t.ct == 0) {
     t.ct = 32;
-    for (int ct : {256, 128, 64})
-      if (items_for(ct) >= (ct == 256 ? 8 : 4) * (int64_t)c->cus) {
-        t.ct = ct;
+    const int sampled[3] = {32, 6, 5}, poses[3] = {32, 16, 16};  // items for a tile, in quarters per CU
+    for (int i = 0; i < 3; ++i)
+      if (4 * items_for(256 >> i) >= (given ? poses : sampled)[i] * (int64_t)c->cus) {
+        t.ct = 256 >> i;
         break;
       }
+    if (t.ct == 32) {
+      const int64_t items = items_for(32);
+      if (8 * items <= 3 * (int64_t)c->cus) t.pts = std::min(t.pts, 512);
+      else if (items <= c->cus) t.pts = std::min(t.pts, 1024);
+    }
   }
   if (t.blocks == 0) {
     // About one work item per workgroup: the hardware dispatcher then hands
@@ -248,6 +263,12 @@ ScoreTune round_tune(const imloc_ctx* c, const std::pair<int64_t, int64_t>* est,
     t.blocks = (int)std::min<int64_t>(kScoreMaxBlocks, std::max<int64_t>(8 * (int64_t)c->cus, items + items / 2));
   }
   return t;
+}
+
+// Candidates of a round of `samples` for the estimate above: a generalised P3P
+// sample gives 0.85 on average where a P3P sample gives 1.4.
+int64_t est_candidates(const QPlan& pl, int64_t samples) {
+  return pl.ncam > 0 ? std::max<int64_t>(1, samples * 3 / 5) : samples;
 }
 
 // Scoring points of a query for the estimate above (a rig cuts its segments
@@ -717,7 +738,7 @@ int run_batch(imloc_ctx* ctx, int nq, const imloc_corr* pts, const int64_t* n, c
   Timer tm(ctx);
   int rounds = 0;
   EstList est(nq);
-  for (int q = 0; q < nq; ++q) est[q] = {std::min(pl[q].batch, pl[q].total), est_points(pl[q])};
+  for (int q = 0; q < nq; ++q) est[q] = {est_candidates(pl[q], std::min(pl[q].batch, pl[q].total)), est_points(pl[q])};
   const ScoreTune tune = round_tune(ctx, est.data(), est.size());
   // The whole pipeline of a batch, enqueued on stream `st_`: table upload,
   // rounds, final refinement, mask, readback into pinned memory.  `sync`
@@ -1471,7 +1492,7 @@ int imloc_rig_score(imloc_ctx* ctx, const imloc_corr* pts, int64_t n, const imlo
   hipStream_t s = ctx->stream;
   HIP_TRY(ctx, launch_set_candidates(sq.e.qd, poses, np, sq.e.cb, s));
   const std::pair<int64_t, int64_t> est1{np, est_points(sq.pl)};
-  const ScoreTune tune = round_tune(ctx, &est1, 1);
+  const ScoreTune tune = round_tune(ctx, &est1, 1, true);
   HIP_TRY(ctx, launch_score(sq.e.qd, sq.e.cb, sq.e.st, 1, sq.e.item_off, tune, precision, s));
   HIP_TRY(ctx, launch_candidate_costs(sq.e.qd, sq.e.cb, np, count, msac, s));
   return IMLOC_OK;
@@ -1514,7 +1535,7 @@ int imloc_score(imloc_ctx* ctx, const imloc_corr* pts, int64_t n, const imloc_ca
   hipStream_t s = ctx->stream;
   HIP_TRY(ctx, launch_set_candidates(sq.e.qd, poses, np, sq.e.cb, s));
   const std::pair<int64_t, int64_t> est1{np, est_points(sq.pl)};
-  const ScoreTune tune = round_tune(ctx, &est1, 1);
+  const ScoreTune tune = round_tune(ctx, &est1, 1, true);
   HIP_TRY(ctx, launch_score(sq.e.qd, sq.e.cb, sq.e.st, 1, sq.e.item_off, tune, precision, s));
   HIP_TRY(ctx, launch_candidate_costs(sq.e.qd, sq.e.cb, np, count, msac, s));
   return IMLOC_OK;
@@ -1549,7 +1570,7 @@ int imloc_select_top_k(imloc_ctx* ctx, const imloc_corr* pts, int64_t n, const i
   }
   HIP_TRY(ctx, launch_set_candidates(sq.e.qd, poses, np, sq.e.cb, s));
   const std::pair<int64_t, int64_t> est1{np, est_points(sq.pl)};
-  const ScoreTune tune = round_tune(ctx, &est1, 1);
+  const ScoreTune tune = round_tune(ctx, &est1, 1, true);
   HIP_TRY(ctx, launch_score(sq.e.qd, sq.e.cb, sq.e.st, 1, sq.e.item_off, tune, precision, s));
   HIP_TRY(ctx, launch_select(sq.e.qd, sq.e.st, sq.e.cb, 1, k, std::max<int64_t>(np, 1), sq.e.sel_part, sel, n_sel, s));
   HIP_TRY(ctx, hipStreamSynchronize(s));  // the staging buffer held the gate
