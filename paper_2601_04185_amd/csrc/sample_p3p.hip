@@ -6,6 +6,7 @@
 #include "imloc_device.h"
 #include "imloc_kernels.h"
 #include "query_device.h"
+#include "select_key.h"
 
 namespace imloc {
 
@@ -19,6 +20,7 @@ namespace imloc {
 // intersection j % 2), and a scan over the four slots removes duplicates and
 // gives the canonical order.
 constexpr int kP3PLanes = 4;
+static_assert(kP3PLanes <= kMaxSolutions, "the order of the candidates");
 constexpr int kP3PThreads = 256;  // four waves, 64 samples: one slot reservation per 64 samples
 constexpr int kP3PSamples = kP3PThreads / kP3PLanes;
 
@@ -134,6 +136,7 @@ __global__ __launch_bounds__(kP3PThreads) void sample_p3p_kernel(const QueryDesc
 // and writes solution j, the per-level results being exchanged through LDS
 // within the wave.
 constexpr int kGP3PLanes = 8;
+static_assert(kGP3PLanes <= kMaxSolutions, "the order of the candidates");
 // One wave (eight samples) per workgroup: a round of 2,048 samples is 256
 // waves, and one per CU runs faster than four per CU on a quarter of the CUs.
 constexpr int kGP3PThreads = 64;

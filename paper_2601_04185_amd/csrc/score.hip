@@ -37,6 +37,7 @@
 #include "imloc_device.h"
 #include "imloc_kernels.h"
 #include "query_device.h"
+#include "select_key.h"
 
 namespace imloc {
 
@@ -789,18 +790,6 @@ hipError_t launch_candidate_costs(const QueryDesc* qd, CandBuf cb, int64_t np, i
 // Top-k of a query's batch by (msac asc, count desc, h asc, j asc) among the
 // candidates whose truncated cost beats the running best.
 // ---------------------------------------------------------------------------
-struct Key {
-  double ms;
-  long long hj;   // sample index * 4 + solution index
-  int cnt, idx;
-};
-
-__device__ inline bool key_less(const Key& a, const Key& b) {
-  if (a.ms != b.ms) return a.ms < b.ms;
-  if (a.cnt != b.cnt) return a.cnt > b.cnt;
-  return a.hj < b.hj;
-}
-
 __device__ inline Key key_none() { return Key{__builtin_inf(), 0x7fffffffffffffffll, -1, -1}; }
 
 constexpr int kSelList = 8;      // per-thread list of the fast path (k <= 8)
@@ -813,7 +802,7 @@ constexpr int kSelWanted = 256;  // workgroups of a launch from which a query ge
 
 __device__ inline Key load_key(const QueryDesc& d, double weights, const CandBuf& cb, int c) {
   const int64_t o = d.cand_off + c;
-  return Key{cand_msac(d, weights, cb.gain[o]), (long long)cb.h[o] * 4 + cb.j[o], (int)cb.cnt[o], c};
+  return Key{cand_msac(d, weights, cb.gain[o]), hj_order(cb.h[o], cb.j[o]), (int)cb.cnt[o], c};
 }
 
 // Order-preserving 64-bit image of a double (total order of the non-NaN
@@ -941,8 +930,8 @@ __host__ __device__ inline int select_groups(int64_t n_cand) {
 // The k smallest of `n` keys in LDS, to out[] in order, by one wave; returns
 // how many are keys at all (at most k).  A lane counts for its key those below
 // it, and that is its place: the reads do not wait for one another, where k
-// pops are a chain (the launch on 1,400 candidates 6.5 -> 5.8 us).  No two keys
-// tie: sample and solution tell them apart.
+// pops are a chain (the launch on 1,400 candidates 6.5 -> 5.8 us).  Every place
+// below the number returned is written exactly once, also if keys should tie.
 __device__ int wave_rank_k(const Key* keys, int n, int k, Key* out) {
   const int lane = threadIdx.x & (kWave - 1);
   int got = 0;
@@ -956,11 +945,8 @@ __device__ int wave_rank_k(const Key* keys, int n, int k, Key* out) {
       same += ms == mine.ms ? 1 : 0;
     }
     const bool valid = mine.idx >= 0;
-    if (__ballot(valid && same > 1))  // candidates without an inlier all cost the same
-      for (int e = 0; e < n; ++e) {
-        const Key x = keys[e];
-        if (x.ms == mine.ms && key_less(x, mine)) ++below;
-      }
+    if (__ballot(valid && same > 1) && valid)  // candidates without an inlier all cost the same
+      below = key_place(keys, n, e0 + lane);
     if (valid && below < k) out[below] = mine;
     got += __popcll(__ballot(valid));
   }
