@@ -168,6 +168,15 @@ hipError_t launch_worklist(const QueryDesc* qd, CandBuf cb, int nq, ScoreTune tu
 // exact evaluation 2.8; 50,000 x 13,600: 235 -> 142 us; 50,000 x 4,096, 6 % of
 // them good: 85 -> 52 us; 10,000 x 1,360: 21 -> 18 us.  Three waves per SIMD
 // (168 registers); four spill and two leave latency open (10.4, 13.5 ms).
+//
+// Where most candidates are good (poses given from elsewhere), most slots pass.
+// A wave that sees three quarters of its first 32 candidates pass the first slot
+// lets the others pass too: from 0.71 on, 186 cycles cost more than they save of
+// 640.  And candidates that pass in every slot are evaluated two at a time in
+// straight code, since three waves per SIMD do not cover the latency of a single
+// one's reciprocals and lane sum.  50,000 x 4,096 poses, all of them good: 211 us
+// with neither, 186 with the pairs, 156 with both (130 without a filter at five
+// waves per SIMD); half of them good 117 (108), a third 94 (100), none 47 (83).
 // ---------------------------------------------------------------------------
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
@@ -419,6 +428,52 @@ __device__ __forceinline__ void score_item_f32(const QueryDesc& d, const float* 
       put(c, cnt, lanes, gain);
     }
   };
+  // Two candidates, all slots, both sums at a time (the same terms in the same
+  // order as one by one, so the same bits).
+  auto evaluate_pair = [&](int ca, int cb) {
+    float da[PPL], wa[PPL], db[PPL], wb[PPL];
+    uint32_t na = 0, nb = 0;
+    {
+      const float4 r0 = T.rows[ca][0], r1 = T.rows[ca][1], r2 = T.rows[ca][2];
+#pragma unroll
+      for (int k = 0; k < PPL; ++k) {
+        da[k] = residual(r0, r1, r2, k, wa[k]);
+        na += (uint32_t)__popcll(__ballot(da[k] < 0.f));
+      }
+    }
+    {
+      const float4 r0 = T.rows[cb][0], r1 = T.rows[cb][1], r2 = T.rows[cb][2];
+#pragma unroll
+      for (int k = 0; k < PPL; ++k) {
+        db[k] = residual(r0, r1, r2, k, wb[k]);
+        nb += (uint32_t)__popcll(__ballot(db[k] < 0.f));
+      }
+    }
+    if (na | nb) {
+      float ga = 0.f, gb = 0.f;
+#pragma unroll
+      for (int k = 0; k < PPL; ++k) {
+        asm("" : "+v"(da[k]), "+v"(db[k]));  // (compared again: 32 masks would not fit the scalar registers)
+        const float xa = fmaf(-pw[k] * da[k], __builtin_amdgcn_rcpf(wa[k] * fabsf(wa[k])), ga);
+        const float xb = fmaf(-pw[k] * db[k], __builtin_amdgcn_rcpf(wb[k] * fabsf(wb[k])), gb);
+        ga = da[k] < 0.f ? xa : ga;
+        gb = db[k] < 0.f ? xb : gb;
+      }
+      ga = wave_scan_dpp(ga);
+      gb = wave_scan_dpp(gb);
+      if (lane == kWave - 1) {
+        if (na) {
+          atomicAdd(&T.cnt[ca], na);
+          T.part[wave][ca] = ga;
+        }
+        if (nb) {
+          atomicAdd(&T.cnt[cb], nb);
+          T.part[wave][cb] = gb;
+        }
+      }
+      item_cnt += na + nb;
+    }
+  };
   auto evaluate_slots = [&](int c, uint32_t slots) {
     const float4 r0 = T.rows[c][0], r1 = T.rows[c][1], r2 = T.rows[c][2];
     uint32_t cnt = 0;
@@ -577,14 +632,36 @@ __device__ __forceinline__ void score_item_f32(const QueryDesc& d, const float* 
           const uint32_t word = (uint32_t)b | (uint32_t)(b >> 32) | odd;
           passed = lane == at ? word : passed;
         }
+        if (k == 0) {  // mostly good candidates: all pass
+          const int some = max(0, min(kFilterTile, cg1 - cg0));
+          const uint32_t first = some < kFilterTile ? (1u << some) - 1u : ~0u;
+          if (4 * __popc((uint32_t)__builtin_amdgcn_readlane((int)passed, 0) & first) >= 3 * some) {
+            passed = ~0u;
+            break;
+          }
+        }
       }
       mask_ends(blk);
       load_weights(blk);
       for (int t0 = cg0, at = 0; t0 < cg1; t0 += kFilterTile, at += PPL) {
-        uint32_t any = 0;
+        uint32_t any = 0, full = ~0u;
 #pragma unroll
-        for (int k = 0; k < PPL; ++k) any |= (uint32_t)__builtin_amdgcn_readlane((int)passed, at + k);
-        if (cg1 - t0 < kFilterTile) any &= (1u << (cg1 - t0)) - 1u;
+        for (int k = 0; k < PPL; ++k) {
+          const uint32_t word = (uint32_t)__builtin_amdgcn_readlane((int)passed, at + k);
+          any |= word;
+          full &= word;
+        }
+        const uint32_t here = cg1 - t0 < kFilterTile ? (1u << (cg1 - t0)) - 1u : ~0u;
+        any &= here;
+        full &= here;
+        while (full & (full - 1)) {  // two left
+          const int ca = __builtin_ctz(full);
+          full &= full - 1;
+          const int cb = __builtin_ctz(full);
+          full &= full - 1;
+          any &= ~((1u << ca) | (1u << cb));
+          evaluate_pair(t0 + ca, t0 + cb);
+        }
         for (; any; any &= any - 1) {
           const int c = __builtin_ctz(any);
           evaluate_slots(t0 + c, (uint32_t)(__ballot((passed >> c) & 1u) >> at) & 0xffu);
