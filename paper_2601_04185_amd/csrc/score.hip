@@ -261,6 +261,17 @@ __device__ inline void filter_rows(const float4 r0, const float4 r1, const float
   }
 }
 
+// Candidates of a tile: alike over the ceil(n / CT) tiles, in steps of a
+// product.  Full tiles and a rest would repeat with the queries, in step with the
+// turn in which workgroups go to the parts of the chip, so that some parts get the
+// rests alone: 4,096 queries x 350 candidates x 2,000 correspondences (two tiles
+// of 256) 1,270 -> 995 us, 1,024 x 348 x 8,000 908 -> 706.
+template <int CT>
+__device__ inline int tile_candidates(int n) {
+  const int tiles = (n + CT - 1) / CT;
+  return ((n + tiles - 1) / tiles + kFilterTile - 1) / kFilterTile * kFilterTile;
+}
+
 // Tables of a work item in LDS.
 template <int CT>
 struct ScoreTables {
@@ -322,8 +333,8 @@ __device__ __forceinline__ void score_item_f32(const QueryDesc& d, const float* 
   const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const float inv_tau = (float)(1.0 / d.tau);
   const ChunkRange rg = chunk_range(d, chunk, pts);
-  const int c0 = (int)(tile * CT);
-  const int cend = min(CT, ncand - c0);
+  const int per = tile_candidates<CT>(ncand), c0 = (int)tile * per;
+  const int cend = min(per, ncand - c0);
   const int wpg = min(kScoreWaves, pts / kScoreWaveBlock);  // waves per candidate group
   const int grp = wave / wpg, gsz = CT * wpg / kScoreWaves;
   const int cg0 = grp * gsz, cg1 = min(cend, cg0 + gsz);
@@ -691,8 +702,8 @@ __device__ __forceinline__ void score_item_f64(const QueryDesc& d, const double*
   const ChunkRange rg = chunk_range(d, chunk, 0);
   const int64_t base = rg.begin + wave * (kWave * PPL) + lane;
   const double tau2 = d.tau * d.tau;
-  const int c0 = (int)(tile * CT);
-  const int cend = min(CT, ncand - c0);
+  const int per = tile_candidates<CT>(ncand), c0 = (int)tile * per;
+  const int cend = min(per, ncand - c0);
   double pu[PPL], pv[PPL], px[PPL], py[PPL], pz[PPL], pw[PPL];
 #pragma unroll
   for (int k = 0; k < PPL; ++k) {
