@@ -207,6 +207,7 @@ struct ScoreTune {
   int ct;       // candidates per work item (32, 64, 128 or 256)
   int blocks;   // workgroups of the launch (each strides over the work list)
   int pts;      // correspondences per float32 work item (512, 1024, 2048 or 4096)
+  bool filter;  // the matrix cores rule out what has no inlier (256 candidates: always)
 };
 // (nothing for one query)
 hipError_t launch_worklist(const QueryDesc* qd, CandBuf cb, int nq, ScoreTune tune, int64_t* item_off, hipStream_t s);

@@ -123,7 +123,7 @@ struct imloc_ctx {
   // timing events, created when timing is switched on (imloc_set_timing)
   std::vector<hipEvent_t> events;
   size_t next_event = 0;
-  ScoreTune tune{0, 0, 2048};  // ct == 0, blocks == 0: the tile and the grid are picked per round (round_tune)
+  ScoreTune tune{0, 0, 2048, true};  // ct == 0, blocks == 0: the tile and the grid are picked per round (round_tune)
   int cus = 256;
   int gn_mode = 0;  // Gauss-Newton teams: 0 by size, 1 the widest, 2 one workgroup per problem
   int gn_polls = kGNPolls;
@@ -224,14 +224,25 @@ struct QPlan {
 // Few items of 32 are cut at fewer correspondences, 512 / 1,024 / 2,048: 2,000 x
 // 256 samples 11 / 15 / 23 us (8 items of 2,048), 3,000 x 1,024 13.0 / 14.7 / 21.3
 // (64), 5,000 15.2 / 15.4 / 19.9 (96), 10,000 25.2 / 18.4 / 18.9 (160), 4,000 x
-// 4,096 29.8 / 22.9 / 23.6 (256), 6,000 39 / 33 / 25 (384).  (Of 512, a wave has 8
-// candidates, too few for the filter.)
+// 4,096 29.8 / 22.9 / 23.6 (256), 6,000 39 / 33 / 25 (384).
+//
+// Small sets and few candidates go without the filter, whose features and
+// coefficients are paid per item: in batches of 2,048 queries (with / without it,
+// best tile each) 500 correspondences x 340 candidates 252 / 207 us, 1,000 366 /
+// 356, 1,500 531 / 532, 2,000 501 / 584; 2,000 x 21 candidates 65 / 54, 5,000 x 32
+// 178 / 166, 8,000 x 32 227 / 224, 2,000 x 85 153 / 165.  So without it where most
+// of the round's residuals are of sets of up to 1,024, or a query has up to 32
+// candidates (24 samples).  Items of such sets hold no more than 512 or 1,024, as
+// else only one wave or two of four have work (500 x 340 at 2,048 474 us, at 512
+// 207), and no query gets a tile of twice its candidates (2,000 x 21 in a tile of
+// 256 66 us, of 32 54).
 // est holds per query the expected candidates (one per sample) and scoring
-// points.  None of the three changes a result (per-candidate sums are
+// points.  None of these changes a result (per-candidate sums are
 // integer-accumulated over fixed wave blocks).
 using EstList = SmallVec<std::pair<int64_t, int64_t>, 4>;
 ScoreTune round_tune(const imloc_ctx* c, const std::pair<int64_t, int64_t>* est, size_t n_est, bool given = false) {
   ScoreTune t = c->tune;
+  t.filter = true;
   if (t.ct > 0 && t.blocks > 0) return t;
   auto items_for = [&](int ct) {
     int64_t items = 0;
@@ -239,10 +250,20 @@ ScoreTune round_tune(const imloc_ctx* c, const std::pair<int64_t, int64_t>* est,
     return items;
   };
   if (t.ct == 0) {
+    // the round's residuals of sets of up to 512, of up to 1,024 and of more correspondences
+    int64_t work[3] = {0, 0, 0}, most = 0;
+    for (size_t q = 0; q < n_est; ++q) {
+      work[est[q].second <= 512 ? 0 : est[q].second <= 1024 ? 1 : 2] += est[q].first * est[q].second;
+      most = std::max(most, est[q].first);
+    }
+    const bool small = work[0] + work[1] > work[2];
+    if (small) t.pts = std::min(t.pts, work[0] > work[1] + work[2] ? 512 : 1024);
+    t.filter = !small && most > (given ? 32 : 24);
     t.ct = 32;
     const int sampled[3] = {32, 6, 5}, poses[3] = {32, 16, 16};  // items for a tile, in quarters per CU
-    for (int i = 0; i < 3; ++i)
-      if (4 * items_for(256 >> i) >= (given ? poses : sampled)[i] * (int64_t)c->cus) {
+    for (int i = t.filter ? 0 : 1; i < 3; ++i)
+      if ((256 >> i) < (given ? 2 : 4) * most &&
+          4 * items_for(256 >> i) >= (given ? poses : sampled)[i] * (int64_t)c->cus) {
         t.ct = 256 >> i;
         break;
       }
@@ -250,6 +271,7 @@ ScoreTune round_tune(const imloc_ctx* c, const std::pair<int64_t, int64_t>* est,
       const int64_t items = items_for(32);
       if (8 * items <= 3 * (int64_t)c->cus) t.pts = std::min(t.pts, 512);
       else if (items <= c->cus) t.pts = std::min(t.pts, 1024);
+      if (t.pts < 2048) t.filter = false;  // (8 or 16 candidates per wave, too few for a product)
     }
   }
   if (t.blocks == 0) {
@@ -802,8 +824,8 @@ int run_batch(imloc_ctx* ctx, int nq, const imloc_corr* pts, const int64_t* n, c
     // key of everything a captured graph bakes in: shapes, workspace, staging
     std::string key;
     char buf[160];
-    snprintf(buf, sizeof(buf), "%d|%p|%p|%d|%d|%d|%d|%d|%d|", nq, (void*)ws.base, (void*)ctx->pinned, tune.ct,
-             tune.blocks, tune.pts, teams.lo.members, teams.fin.members, ctx->gn_polls);
+    snprintf(buf, sizeof(buf), "%d|%p|%p|%d|%d|%d|%d|%d|%d|%d|", nq, (void*)ws.base, (void*)ctx->pinned, tune.ct,
+             tune.blocks, tune.pts, (int)tune.filter, teams.lo.members, teams.fin.members, ctx->gn_polls);
     key += buf;
     for (int q = 0; q < nq; ++q) {
       snprintf(buf, sizeof(buf), "%lld,%lld,%d,%lld,%lld,%d,%d,%d;", (long long)pl[q].n, (long long)pl[q].m,

@@ -177,6 +177,9 @@ hipError_t launch_worklist(const QueryDesc* qd, CandBuf cb, int nq, ScoreTune tu
 // one's reciprocals and lane sum.  50,000 x 4,096 poses, all of them good: 211 us
 // with neither, 186 with the pairs, 156 with both (130 without a filter at five
 // waves per SIMD); half of them good 117 (108), a third 94 (100), none 47 (83).
+//
+// Rounds in which the filter does not pay (round_tune) take a kernel without it,
+// which has registers for four waves per SIMD.
 // ---------------------------------------------------------------------------
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
@@ -320,7 +323,7 @@ __device__ __forceinline__ void score_item_end(const QueryDesc& d, uint32_t* __r
 // pts.  pts >= 2048: each wave takes blocks w, w + 4, ... for every
 // candidate; pts < 2048: the waves split into 2048 / pts candidate groups,
 // each of pts / 512 waves.  Between the blocks no wave waits for another.
-template <int CT>
+template <int CT, bool FILTER>
 __device__ __forceinline__ void score_item_f32(const QueryDesc& d, const float* __restrict__ proj,
                                                uint32_t* __restrict__ ccnt, unsigned long long* __restrict__ cgain,
                                                BestState* st, int64_t tile, int64_t chunk, int ncand, int pts,
@@ -341,7 +344,7 @@ __device__ __forceinline__ void score_item_f32(const QueryDesc& d, const float* 
   // correspondences and wave blocks of the item
   const int npt = (int)max((int64_t)0, min(rg.end - rg.begin, (int64_t)pts));
   const int nblk = (npt + kScoreWaveBlock - 1) / kScoreWaveBlock;
-  const bool filter = gsz >= kFilterTile && cend >= kFilterLeast;
+  const bool filter = FILTER && gsz >= kFilterTile && cend >= kFilterLeast;
   // the tile's projection rows into LDS: every wave then reads a candidate's
   // 12 values as three broadcast 16-byte LDS loads into vector registers
   // (a multiply-add with a scalar-register operand issues about 1.7 times
@@ -771,15 +774,11 @@ __device__ __forceinline__ void score_item_f64(const QueryDesc& d, const double*
 
 // Persistent workgroups over the work list; every workgroup exits once the
 // item index passes the device-side total.
-template <int CT>
-__global__ __launch_bounds__(kScoreBlock, 3) void score_kernel(const QueryDesc* __restrict__ qd,
-                                                               const float* __restrict__ proj,
-                                                               const double* __restrict__ pose,
-                                                               const int32_t* __restrict__ ncand,
-                                                               uint32_t* __restrict__ ccnt,
-                                                               unsigned long long* __restrict__ cgain,
-                                                               BestState* __restrict__ st, int nq, int pts,
-                                                               const int64_t* __restrict__ item_off) {
+template <int CT, bool FILTER>
+__global__ __launch_bounds__(kScoreBlock, FILTER ? 3 : 4) void score_kernel(
+    const QueryDesc* __restrict__ qd, const float* __restrict__ proj, const double* __restrict__ pose,
+    const int32_t* __restrict__ ncand, uint32_t* __restrict__ ccnt, unsigned long long* __restrict__ cgain,
+    BestState* __restrict__ st, int nq, int pts, const int64_t* __restrict__ item_off) {
   __shared__ ScoreTables<CT> s_tab;
   // the sums start empty, and every item leaves them empty
   for (int e = threadIdx.x; e < CT * kScoreWaves; e += kScoreBlock) (&s_tab.part[0][0])[e] = 0.f;
@@ -806,7 +805,7 @@ __global__ __launch_bounds__(kScoreBlock, 3) void score_kernel(const QueryDesc* 
     const int64_t tile = local / chunks, chunk = local - tile * chunks;
     const int nc = ncand[lo];
     if (d.precision == 0)
-      score_item_f32<CT>(d, proj, ccnt, cgain, st + lo, tile, chunk, nc, pts, s_tab);
+      score_item_f32<CT, FILTER>(d, proj, ccnt, cgain, st + lo, tile, chunk, nc, pts, s_tab);
     else
       score_item_f64<CT>(d, pose, ccnt, cgain, st + lo, tile, chunk, nc, s_tab);
   }
@@ -818,23 +817,21 @@ hipError_t launch_score(const QueryDesc* qd, CandBuf cb, BestState* st, int nq, 
   const dim3 grid(tune.blocks > 0 ? tune.blocks : 2048), block(kScoreBlock);
   unsigned long long* g = reinterpret_cast<unsigned long long*>(cb.gain);
   const int pts = tune.pts;
-#define IMLOC_SCORE_LAUNCH(CT)                                                                                    \
-  hipLaunchKernelGGL((score_kernel<CT>), grid, block, 0, s, qd, cb.proj, cb.pose, cb.n, cb.cnt, g, st, nq, pts, \
-                     item_off);
+#define IMLOC_SCORE_LAUNCH(CT, FILTER)                                                                             \
+  hipLaunchKernelGGL((score_kernel<CT, FILTER>), grid, block, 0, s, qd, cb.proj, cb.pose, cb.n, cb.cnt, g, st, nq, \
+                     pts, item_off)
+#define IMLOC_SCORE_TILE(CT)                       \
+  do {                                             \
+    if (tune.filter) IMLOC_SCORE_LAUNCH(CT, true); \
+    else IMLOC_SCORE_LAUNCH(CT, false);            \
+  } while (0)
   switch (tune.ct) {
-    case 256:
-      IMLOC_SCORE_LAUNCH(256)
-      break;
-    case 128:
-      IMLOC_SCORE_LAUNCH(128)
-      break;
-    case 64:
-      IMLOC_SCORE_LAUNCH(64)
-      break;
-    default:
-      IMLOC_SCORE_LAUNCH(32)
-      break;
+    case 256: IMLOC_SCORE_LAUNCH(256, true); break;
+    case 128: IMLOC_SCORE_TILE(128); break;
+    case 64: IMLOC_SCORE_TILE(64); break;
+    default: IMLOC_SCORE_TILE(32); break;
   }
+#undef IMLOC_SCORE_TILE
 #undef IMLOC_SCORE_LAUNCH
   return hipGetLastError();
 }
