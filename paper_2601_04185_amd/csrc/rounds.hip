@@ -58,7 +58,10 @@ __device__ inline int64_t round_samples(const QueryDesc& d, const BestState& b) 
 // No workgroup reads what another one writes: all read the host's table.
 constexpr int kInitThreads = 1024;
 constexpr int kSumGroups = 512;  // workgroups of a launch that sum weights, about (two per compute unit)
-constexpr int kClearRows = 8;  // at most; a row clears 16 words per thread and turn
+// Rows that clear, a row for 16 words per thread, at most this many per query or
+// those that make two workgroups per compute unit: 4,096 starts on 20,000 points
+// (84 MB of mailboxes) 143 us with eight rows, 15.5 with 512.
+constexpr int kClearRows = 8;
 
 __device__ inline void clear_words(uint64_t* p, int64_t n, int row, int rows) {
   for (int64_t i = (int64_t)row * kInitThreads + threadIdx.x; i < n; i += (int64_t)rows * kInitThreads) p[i] = 0;
@@ -187,7 +190,7 @@ hipError_t launch_init_queries(const QueryTables& t, BestState* st, CandBuf cb, 
   if (nq <= 0) return hipSuccess;
   const int64_t words = (clear.lo ? clear.lo_words : 0) + (clear.fin ? clear.fin_words : 0);
   const int64_t rows = (words + 16 * kInitThreads - 1) / (16 * kInitThreads);
-  const int clear_rows = (int)(rows < kClearRows ? rows : kClearRows);
+  const int clear_rows = (int)std::min<int64_t>(rows, std::max(kClearRows, kSumGroups / nq));
   const int64_t gather_rows = (max_m + kInitThreads - 1) / kInitThreads;
   // rows for the sums: a part each while the launch has room for them and the sets have points for them
   int64_t weighted = 0;
