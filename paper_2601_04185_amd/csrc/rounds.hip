@@ -44,11 +44,12 @@ __device__ inline int64_t round_samples(const QueryDesc& d, const BestState& b) 
 // mailboxes and resets the states, where a copy or a launch each took 3 to 5 us
 // (a query on 2,000 points 6.6 -> 3.1 us, with a subset of 10,000 of 50,000 12.6
 // -> 6.0, a four-camera query 11 -> 5.7, a server's round 9 -> 5.2).
-// Grid row 0: one workgroup of 1024 threads per query copies its descriptor
-// and, if the query is fresh, resets the state.  With `begin`, it also sets
-// up the round (samples, candidate counter).  The next rows sum a fresh query's
-// scoring-set weights in float64, in kWeightParts parts whatever the number of
-// rows: one compute unit loads at 14 GB/s what another kernel has just written
+// Grid: a query's rows in x (the gather of a large set has more than the 65,536
+// that y can hold), the queries in y.  Row 0: one workgroup of 1024 threads copies
+// the descriptor and, if the query is fresh, resets the state.  With `begin`, it
+// also sets up the round (samples, candidate counter).  The next rows sum a fresh
+// query's scoring-set weights in float64, in kWeightParts parts whatever the number
+// of rows: one compute unit loads at 14 GB/s what another kernel has just written
 // (126,000 weights in one workgroup took the launch 41 us, now 7.2; 50,000 that
 // were read before 11.1, now 4.9); who needs the total adds the parts.  Without
 // weights it is the number of points (one query on 50,000 6.7 -> 4.8), and a call
@@ -70,7 +71,7 @@ __device__ inline void clear_words(uint64_t* p, int64_t n, int row, int rows) {
 __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables t, BestState* __restrict__ st,
                                                                     CandBuf cb, int begin, int sum_rows,
                                                                     GNClear clear, int clear_rows) {
-  const int q = blockIdx.x;
+  const int q = blockIdx.y;
   // the descriptor in one read over the bus (about 1.5 us), not field by field
   constexpr int kWords = sizeof(QueryDesc) / sizeof(uint64_t), kB = offsetof(QueryDesc, B) / sizeof(uint64_t);
   static_assert(sizeof(QueryDesc) % sizeof(uint64_t) == 0, "copied by words");
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
   if (threadIdx.x < kWords) {
     const uint64_t w = reinterpret_cast<const uint64_t*>(t.host + q)[threadIdx.x];
     s_desc[threadIdx.x] = w;
-    if (blockIdx.y == 0 && !(begin && threadIdx.x == kB))  // (B of a round: below)
+    if (blockIdx.x == 0 && !(begin && threadIdx.x == kB))  // (B of a round: below)
       reinterpret_cast<uint64_t*>(t.dev + q)[threadIdx.x] = w;
   }
   lds_barrier();
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
     s += r >= m ? 1 : 0;
     return s - (r < 0 ? 1 : 0);
   };
-  const int row = (int)blockIdx.y - 1 - sum_rows;
+  const int row = (int)blockIdx.x - 1 - sum_rows;
   if (row >= clear_rows) {
     const int64_t j = (int64_t)(row - clear_rows) * kInitThreads + threadIdx.x;
     if (!d.fresh || !subset || j >= m) return;
@@ -116,11 +117,11 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
       clear_words(clear.fin + q * clear.fin_words, clear.fin_words, row, clear_rows);
     return;
   }
-  if (blockIdx.y > 0) {
+  if (blockIdx.x > 0) {
     const float* __restrict__ w = d.full.w;
     if (!d.fresh || !w) return;
     __shared__ double sw[kInitThreads / kWave];
-    for (int u = (int)blockIdx.y - 1; u < kWeightParts; u += sum_rows) {
+    for (int u = (int)blockIdx.x - 1; u < kWeightParts; u += sum_rows) {
       double p = 0.0;
       for (int64_t i0 = (int64_t)u * kInitThreads + threadIdx.x; i0 < m; i0 += 8 * kWeightParts * kInitThreads) {
         float x[8];
@@ -198,7 +199,7 @@ hipError_t launch_init_queries(const QueryTables& t, BestState* st, CandBuf cb, 
     if (t.host[q].fresh && t.host[q].full.w) weighted = std::max(weighted, t.host[q].m);
   const int64_t parts = std::min<int64_t>((weighted + kInitThreads - 1) / kInitThreads, kWeightParts);
   const int sum_rows = (int)std::min<int64_t>(parts, std::max(1, kSumGroups / nq));
-  hipLaunchKernelGGL(init_queries_kernel, dim3(nq, (unsigned)(1 + sum_rows + clear_rows + gather_rows)),
+  hipLaunchKernelGGL(init_queries_kernel, dim3((unsigned)(1 + sum_rows + clear_rows + gather_rows), nq),
                      dim3(kInitThreads), 0, s, t, st, cb, begin ? 1 : 0, sum_rows, clear, clear_rows);
   return hipGetLastError();
 }
