@@ -115,7 +115,7 @@ struct imloc_ctx {
   // that) before writing the buffer again.
   char* pinned = nullptr;
   size_t pinned_bytes = 0;
-  int32_t* kept = nullptr;  // pinned: kept matches of the last lift
+  int32_t* kept = nullptr;  // pinned, as long as the context: kept matches of the last lift
   hipEvent_t staging_ev = nullptr;
   bool staging_pending = false;
   // recorded behind a synchronous call's work and polled (wait_stream)
@@ -558,12 +558,8 @@ int staging_alloc(imloc_ctx* c, size_t bytes) {
   c->pinned = nullptr;
   c->pinned_bytes = 0;
   c->staging_pending = false;
-  // and a word behind it for the count of a lift (lift_kept)
-  const size_t up = (bytes + 63) & ~size_t(63);
-  HIP_TRY(c, hipHostMalloc(reinterpret_cast<void**>(&c->pinned), up + 64, hipHostMallocDefault));
+  HIP_TRY(c, hipHostMalloc(reinterpret_cast<void**>(&c->pinned), bytes, hipHostMallocDefault));
   c->pinned_bytes = bytes;
-  c->kept = reinterpret_cast<int32_t*>(c->pinned + up);
-  *c->kept = 0;
   return IMLOC_OK;
 }
 
@@ -996,10 +992,12 @@ int imloc_create(imloc_ctx** out, int device, void* hip_stream) {
   c->stream = reinterpret_cast<hipStream_t>(hip_stream);
   if (hipEventCreateWithFlags(&c->staging_ev, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&c->done_ev, hipEventDisableTiming) != hipSuccess ||
+      hipHostMalloc(reinterpret_cast<void**>(&c->kept), 64, hipHostMallocDefault) != hipSuccess ||
       staging_alloc(c, kDefaultStaging) != IMLOC_OK) {
     imloc_destroy(c);
     return IMLOC_EHIP;
   }
+  *c->kept = 0;
   int cus = 256;
   hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
   c->cus = cus > 0 ? cus : 256;
@@ -1023,6 +1021,7 @@ void imloc_destroy(imloc_ctx* c) {
     hipStreamDestroy(c->gstream);
   }
   if (c->pinned) hipHostFree(c->pinned);
+  if (c->kept) hipHostFree(c->kept);
   delete c;
 }
 

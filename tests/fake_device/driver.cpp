@@ -8,8 +8,11 @@
 #include <cstdlib>
 #include <cstring>
 #include <initializer_list>
+#include <map>
 
 #include "imloc.h"
+
+extern "C" int lift_kept(imloc_ctx* ctx, int32_t* n);
 
 struct Dim3 {
   uint32_t x, y, z;
@@ -18,6 +21,8 @@ struct Dim3 {
 namespace {
 int fails = 0;
 int launches = 0;
+bool fail_host_malloc = false;
+std::map<void*, size_t> host_blocks;
 struct Config {
   Dim3 grid, block;
   size_t shmem;
@@ -57,10 +62,15 @@ int hipEventSynchronize(void*) { return 0; }
 int hipStreamSynchronize(void*) { return 0; }
 int hipMemcpyAsync(void*, const void*, size_t, int, void*) { return 0; }
 int hipHostMalloc(void** p, size_t n, unsigned) {
+  if (fail_host_malloc) return 2;
   *p = std::calloc(1, n);
+  host_blocks[*p] = n;
   return 0;
 }
-int hipHostFree(void* p) { std::free(p); return 0; }
+int hipHostFree(void* p) {  // stays mapped and says so: a later read is seen
+  std::memset(p, 0x5a, host_blocks[p]);
+  return 0;
+}
 int __hipPushCallConfiguration(Dim3 g, Dim3 b, size_t s, void* st) {
   config = Config{g, b, s, st};
   return 0;
@@ -110,6 +120,17 @@ int main(int argc, char** argv) {
     imloc_pose T{{1, 0, 0, 0, 1, 0, 0, 0, 1}, {0, 0, 0}};
     for (int64_t n : {1, 1024, 1025, 2000000000})
       check(imloc_lift(ctx, &m, n, a, 1, 480, 640, &K, &T, 1, 0.05f, &o, n, (int32_t*)a) == IMLOC_OK, "call");
+  } else if (!std::strcmp(test, "kept")) {
+    what = "staging that could not be replaced";
+    fail_host_malloc = true;
+    check(imloc_set_staging(ctx, 1 << 22) == IMLOC_EHIP, "set_staging fails");
+    check(imloc_get_staging(ctx) == 0, "no staging");
+    const imloc_corr_out o{a, a, a, a, a, a, (int32_t*)a};
+    check(imloc_lift(ctx, nullptr, 0, nullptr, 0, 0, 0, nullptr, nullptr, 1, 0.f, &o, 0, (int32_t*)a) == IMLOC_OK,
+          "a lift of no matches");
+    int32_t n = -1;
+    const int rc = lift_kept(ctx, &n);
+    check(rc != IMLOC_OK || n == 0, "the count of a lift is read from memory that is still there");
   } else {
     return 3;
   }

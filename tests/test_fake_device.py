@@ -2,7 +2,9 @@
 (tests/fake_device/driver.cpp): no GPU is needed.
 
 - grids: the launches of calls on very large inputs stay within the limits of a
-  grid (65,536 in y and z, 2^32 work-items in x)."""
+  grid (65,536 in y and z, 2^32 work-items in x).
+- kept: after a staging buffer that could not be replaced, the count of the last
+  lift is not read from the freed one."""
 import os
 import subprocess
 
@@ -13,7 +15,7 @@ LIB = os.path.join(ROOT, "paper_2601_04185_amd", "libimloc.so")
 
 
 @pytest.mark.skipif(not os.path.exists(LIB), reason="libimloc.so is not built")
-@pytest.mark.parametrize("test", ["grids"])
+@pytest.mark.parametrize("test", ["grids", "kept"])
 def test_host_code(tmp_path, test):
     exe = str(tmp_path / "driver")
     subprocess.run(["g++", "-O1", "-std=c++17", "-rdynamic", "-I", os.path.join(ROOT, "include"),
