@@ -367,8 +367,8 @@ int imloc_lo_ransac_pnp(imloc_ctx *ctx, const imloc_corr *pts, int64_t n, const 
 /* imloc_lo_ransac_pnp for callers that cannot allocate (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same arguments, rules and results, but the device scratch is a fixed
- * array of imloc_noalloc_max_bytes() bytes (32 MiB) inside the library,
- * which every GPU the library runs on holds until the process ends, and the
+ * array of imloc_noalloc_max_bytes() bytes (32 MiB) and 128 KiB inside the
+ * library, which every GPU it runs on holds until the process ends, and the
  * call never captures a graph.  It allocates nothing: no device or host
  * memory, no events, no streams (the context's pinned staging from
  * imloc_create serves the tables).  A query whose scratch would exceed the

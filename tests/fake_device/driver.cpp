@@ -131,6 +131,24 @@ int main(int argc, char** argv) {
     int32_t n = -1;
     const int rc = lift_kept(ctx, &n);
     check(rc != IMLOC_OK || n == 0, "the count of a lift is read from memory that is still there");
+  } else if (!std::strcmp(test, "noalloc")) {
+    // the largest batches of samples that the fixed array held when it was set
+    // (per query: local optimisations, points, samples), and batches past it
+    const struct { int32_t k; int64_t n, samples; bool fits; } q[] = {
+        {32, 30111, 44246, true}, {32, 32768, 44135, true}, {8, 30721, 45141, true}, {1, 30721, 45415, true},
+        {32, 25000, 44467, true}, {1, 30721, 46000, false}, {32, 32768, 46000, false}, {1, 200000, 46000, false}};
+    imloc_ransac_params p;
+    imloc_paper_params(4.0, &p);
+    imloc_pose pose;
+    for (const auto& e : q) {
+      what = e.fits ? "fits" : "does not fit";
+      p.max_score_points = 0;
+      p.lo_top_k = e.k;
+      p.fixed_samples = p.batch = e.samples;
+      const int rc = imloc_lo_ransac_pnp_noalloc(ctx, &corr, e.n, &K, &p, &pose, nullptr, nullptr);
+      check((rc == IMLOC_ENOMEM) == !e.fits, "query of the fixed array");
+    }
+    check(imloc_noalloc_max_bytes() == size_t(32) << 20, "limit");
   } else {
     return 3;
   }
