@@ -152,50 +152,6 @@ __device__ inline void so3_exp(const double w[3], double E[9]) {
   E[8] = 1.0 + B * (z * z - th2);
 }
 
-// x' = Exp(dw) x + dt : R' = Exp(dw) R, t' = Exp(dw) t + dt.
-__device__ inline void pose_left_update(const Pose& P, const double d[6], Pose& o) {
-  double E[9];
-  so3_exp(d, E);
-  for (int r = 0; r < 3; ++r) {
-    for (int c = 0; c < 3; ++c) o.R[3 * r + c] = E[3 * r] * P.R[c] + E[3 * r + 1] * P.R[3 + c] + E[3 * r + 2] * P.R[6 + c];
-    o.t[r] = E[3 * r] * P.t[0] + E[3 * r + 1] * P.t[1] + E[3 * r + 2] * P.t[2] + d[3 + r];
-  }
-}
-
-// Solve H x = b, H symmetric positive definite 6x6 given by its upper triangle
-// packed row-wise (21 entries).  false if a pivot is not positive.
-__device__ inline bool chol6_solve_packed(const double Hp[21], const double b[6], double x[6]) {
-  double L[6][6];
-  int k = 0;
-  double H[6][6];
-  for (int r = 0; r < 6; ++r)
-    for (int c = r; c < 6; ++c) { H[r][c] = Hp[k]; H[c][r] = Hp[k]; ++k; }
-  for (int i = 0; i < 6; ++i) {
-    for (int j = 0; j <= i; ++j) {
-      double s = H[i][j];
-      for (int m = 0; m < j; ++m) s -= L[i][m] * L[j][m];
-      if (i == j) {
-        if (!(s > 0.0)) return false;
-        L[i][i] = sqrt(s);
-      } else {
-        L[i][j] = s / L[j][j];
-      }
-    }
-  }
-  double y[6];
-  for (int i = 0; i < 6; ++i) {
-    double s = b[i];
-    for (int m = 0; m < i; ++m) s -= L[i][m] * y[m];
-    y[i] = s / L[i][i];
-  }
-  for (int i = 5; i >= 0; --i) {
-    double s = y[i];
-    for (int m = i + 1; m < 6; ++m) s -= L[m][i] * x[m];
-    x[i] = s / L[i][i];
-  }
-  return true;
-}
-
 // ---------------------------------------------------------------------------
 // P3P in float64, as an intersection of a pencil of conics.
 //

@@ -39,7 +39,7 @@ struct BestState {
   int64_t lo_runs;
   int64_t candidates;        // candidates scored so far
   int64_t inlier_residuals;  // inside-threshold residuals seen by scoring
-  double weight_sum;         // sum of weights over the scoring set (set by the selection)
+  double unused;             // (keeps the staging of a query at its size)
   double final_cost;
   int64_t full_count;
   int64_t drawn;             // samples drawn so far
@@ -156,7 +156,6 @@ hipError_t launch_triangulate(const TriArgs& a, hipStream_t s);
 
 // --- small utilities ---------------------------------------------------------
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
-hipError_t launch_fill_u8(uint8_t* p, int64_t n, uint8_t v, hipStream_t s);
 
 // --- round bookkeeping ---------------------------------------------------------
 // init: state and the weight sum of the scoring set of every fresh query.

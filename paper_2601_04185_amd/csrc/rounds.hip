@@ -20,17 +20,6 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ void fill_u8_kernel(uint8_t* p, int64_t n, uint8_t v) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
-hipError_t launch_fill_u8(uint8_t* p, int64_t n, uint8_t v, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(fill_u8_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n, v);
-  return hipGetLastError();
-}
-
 // Samples of the coming round: the rest of the budget, at most one batch;
 // none once the query stopped.
 __device__ inline int64_t round_samples(const QueryDesc& d, const BestState& b) {
@@ -173,7 +162,6 @@ __global__ __launch_bounds__(kInitThreads) void init_queries_kernel(QueryTables 
     b.lo_runs = 0;
     b.candidates = 0;
     b.inlier_residuals = 0;
-    b.weight_sum = 0.0;
     b.final_cost = 0.0;
     b.full_count = 0;
     b.drawn = 0;

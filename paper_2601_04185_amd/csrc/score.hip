@@ -1093,7 +1093,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const QueryDesc* __
     if (lane == 0) {
       n_sel[q] = got_b;
       st[q].candidates += nc;
-      st[q].weight_sum = weights;
     }
     return;
   }
@@ -1113,7 +1112,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const QueryDesc* __
   if (lane == 0) {
     n_sel[q] = got_q;
     st[q].candidates += nc;
-    st[q].weight_sum = weights;
   }
 }
 
@@ -1166,7 +1164,6 @@ __global__ __launch_bounds__(256) void select_rounds_kernel(const QueryDesc* __r
   if (threadIdx.x == 0) {
     n_sel[q] = r;
     st[q].candidates += nc;
-    st[q].weight_sum = weights;
   }
 }
 
