@@ -128,7 +128,7 @@ def lib():
             "imloc_get_score_points": ([vp, vp], C.c_int),
             "imloc_score_workspace_bytes": ([i64, i64, i32], C.c_size_t),
             "imloc_lift_workspace_bytes": ([i64, i32], C.c_size_t),
-            "lift_kept": ([vp, vp], C.c_int),  # not part of the interface
+            "imloc_internal_lift_kept": ([vp, vp], C.c_int),  # not part of the interface
             "imloc_lo_workspace_bytes": ([i64, i32], C.c_size_t),
             "imloc_refine_workspace_bytes": ([i64], C.c_size_t),
             "imloc_set_timing": ([vp, C.c_int], C.c_int),
@@ -464,7 +464,7 @@ def imloc_lift(ctx: Context, matches: dict, depth, cams, poses, subpixel=True, m
     ctx.check(fn(ctx.h, C.byref(m), n, depth.data_ptr(), nv, H, W, cams_a.ctypes.data, poses_a.ctypes.data,
                  1 if subpixel else 0, C.c_float(min_conf), C.byref(co), cap, base + 4 * 7 * c1))
     kept = C.c_int32()
-    ctx.check(L.lift_kept(ctx.h, C.byref(kept)))
+    ctx.check(L.imloc_internal_lift_kept(ctx.h, C.byref(kept)))
     k = kept.value if n else 0
     # seven views of the kept length in two operations (a slice each costs a microsecond)
     rows = buf[:7 * c1].view(7, c1)[:, :min(k, cap)].unbind(0)

@@ -1310,7 +1310,7 @@ int imloc_depth_encode_log8(imloc_ctx* ctx, const float* depth, int64_t count, u
 // Waits for the lift enqueued last and reads how many matches it kept, without
 // a copy (not part of the interface: the Python package's imloc_lift, whose
 // outputs are views of that length).
-int lift_kept(imloc_ctx* ctx, int32_t* n) {
+int imloc_internal_lift_kept(imloc_ctx* ctx, int32_t* n) {
   if (!ctx || !n) return IMLOC_EINVAL;
   const int rc = wait_stream(ctx, ctx->stream);
   if (rc) return rc;

@@ -12,7 +12,7 @@
 
 #include "imloc.h"
 
-extern "C" int lift_kept(imloc_ctx* ctx, int32_t* n);
+extern "C" int imloc_internal_lift_kept(imloc_ctx* ctx, int32_t* n);
 
 struct Dim3 {
   uint32_t x, y, z;
@@ -129,7 +129,7 @@ int main(int argc, char** argv) {
     check(imloc_lift(ctx, nullptr, 0, nullptr, 0, 0, 0, nullptr, nullptr, 1, 0.f, &o, 0, (int32_t*)a) == IMLOC_OK,
           "a lift of no matches");
     int32_t n = -1;
-    const int rc = lift_kept(ctx, &n);
+    const int rc = imloc_internal_lift_kept(ctx, &n);
     check(rc != IMLOC_OK || n == 0, "the count of a lift is read from memory that is still there");
   } else if (!std::strcmp(test, "noalloc")) {
     // the largest batches of samples that the fixed array held when it was set
