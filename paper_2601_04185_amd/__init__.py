@@ -515,7 +515,8 @@ def imloc_triangulate_depth(ctx: Context, K_map, T_map, K_views, T_views, mu, mv
     Tv = np.asarray(T_views, np.float64).reshape(V, 12)
     cams = (Camera * V)(*[_cam(k) for k in Kv])
     poses = (Pose * V)(*[_pose12(t) for t in Tv])
-    m = DenseMatches(mu.contiguous().data_ptr(), mv.contiguous().data_ptr(), conf.contiguous().data_ptr())
+    mu, mv, conf = mu.contiguous(), mv.contiguous(), conf.contiguous()  # (kept: the workspace may grow below)
+    m = DenseMatches(mu.data_ptr(), mv.data_ptr(), conf.data_ptr())
     prm = TriangulationParams(float(min_conf), float(angle_deg), int(min_inliers), int(max_refine_iters))
     ctx.ensure_workspace(lib().imloc_triangulate_workspace_bytes(H, W, V))
     k0 = _cam(K_map)
