@@ -85,7 +85,7 @@ def copy_shape(src, dst):
 
 def _score_kernel_name(ct):
     """The scoring kernel's name for a candidate tile (0: the tile is picked per round)."""
-    return f"score_kernel<{ct}>" if ct > 0 else "score_kernel<CT picked per round>"
+    return f"score_kernel<{ct}, true>" if ct > 0 else "score_kernel<CT picked per round>"
 
 
 def _rot_deg(Ra, Rb):
