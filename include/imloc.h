@@ -188,8 +188,10 @@ int imloc_graph_counters(const imloc_ctx *ctx, int64_t *captures, int64_t *launc
 
 /* Launch shape of the scoring kernel: candidates per work item (32, 64 or
  * 128, or 0, the default: picked per round, the largest tile of up to 256
- * that still gives enough work items to the compute units, and small rounds
- * are cut at fewer correspondences too) and workgroups (1 to 2^20;
+ * that still gives enough work items to the compute units and is no larger
+ * than the queries have candidates for; small rounds are cut at fewer
+ * correspondences too, and rounds of small sets or few candidates take a
+ * kernel without the matrix-core filter) and workgroups (1 to 2^20;
  * each walks the round's work list with a grid stride; or 0, the default:
  * per round, about 1.5 per estimated work item, between 8 per compute unit
  * and 2^18).  Neither changes any result (per-candidate sums are
@@ -215,8 +217,9 @@ int imloc_get_score_points(const imloc_ctx *ctx, int32_t *points_per_item);
  * one launch runs every iteration of every problem, a problem's points shared
  * by the workgroups of its team.  0 (default) picks the team's size by the
  * size of the problem and the number of problems, 1 = the widest team (one
- * workgroup per group of 1,024 points or more, at most 32), 2 = one workgroup
- * per problem.  Every team sums the same groups of points in the same order,
+ * workgroup per group of points, at most 128; a problem of up to 2,048 points
+ * is one group, then a group is 1,024 points up to 32,768 and 2,048 or more
+ * beyond), 2 = one workgroup per problem.  Every team sums the same groups of points in the same order,
  * so results are identical; only the speed differs.  Returns IMLOC_EINVAL for
  * another value. */
 int imloc_set_gn_mode(imloc_ctx *ctx, int32_t mode);

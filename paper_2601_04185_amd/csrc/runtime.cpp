@@ -216,7 +216,7 @@ struct QPlan {
 // Tile, grid and correspondences per item of a round's scoring launch where the
 // caller left them open.  A larger tile spends less on the filter's features
 // (256 queries of 5,000 to 80,000 correspondences: 256 / 128 / 64 / 32
-// candidates 9.98 / 11.1 / 13.2 / 17.4 ms), but too few items leave compute units
+// candidates 9.4 / 10.6 / 12.7 / 17.0 ms), but too few items leave compute units
 // idle and end raggedly.  Candidates of samples, of which most see no inlier,
 // items in brackets at one candidate per sample: 126,000 x 1,024 samples 128 / 64
 // / 32 47 / 51 / 60 us (496 / 992 / 1984); 80,000 41.1 / 41.4 / 46 (320 / 640);

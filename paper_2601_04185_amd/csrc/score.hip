@@ -165,9 +165,10 @@ hipError_t launch_worklist(const QueryDesc* qd, CandBuf cb, int nq, ScoreTune tu
 // instead of the subtraction and the median take 195), the exact evaluation of
 // all 640.  256 queries of 5,000 to 80,000 correspondences, 5,570 candidates
 // each: 17.7 -> 9.98 ms, of it products 5.8, features and coefficients 1.2,
-// exact evaluation 2.8; 50,000 x 13,600: 235 -> 142 us; 50,000 x 4,096, 6 % of
-// them good: 85 -> 52 us; 10,000 x 1,360: 21 -> 18 us.  Three waves per SIMD
-// (168 registers); four spill and two leave latency open (10.4, 13.5 ms).
+// exact evaluation 2.8 (with the pairs below 9.6); 50,000 x 13,400: 228 -> 136
+// us; 50,000 x 4,096, 6 % of them good: 85 -> 52 us; 10,000 x 1,360: 21 -> 18 us.
+// Three waves per SIMD (168 registers); four spill and two leave latency open
+// (10.4, 13.5 ms beside the 9.98).
 //
 // Where most candidates are good (poses given from elsewhere), most slots pass.
 // A wave that sees three quarters of its first 32 candidates pass the first slot

@@ -14,7 +14,7 @@
 //      win, ties going to the lowest view;
 //   3. the depth is refined on that inlier set by minimising the
 //      confidence-weighted sum of squared angular errors (1-D Newton, step
-//      halving while the cost rises, to a step below 1e-12 l);
+//      halving while the cost rises, to a step below 1e-9 l);
 //   4. it is kept if the inlier set has at least min_inliers (4) members.
 //
 // Two launches, float64 throughout (on MI355X the
